@@ -110,7 +110,6 @@ int launch_loss_fwd(const float* image, const float* target, int32_t channels, i
                     float lambda, float* loss, void* ws, hipStream_t stream);
 int launch_loss_bwd(const float* image, const float* target, int32_t channels, int32_t height, int32_t width,
                     float lambda, const float* dL_dloss, const void* ws, float* dL_dimage, hipStream_t stream);
-uint32_t launch_l1_partial(const float* image, const float* target, uint64_t n, double* blocks, hipStream_t stream);
 
 // Quadtree initialisation, prune and split of 2D particles.
 int tree_levels_ok(int32_t width, int32_t height, int32_t root, int32_t min_side, uint64_t* root_cells);
