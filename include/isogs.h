@@ -261,12 +261,13 @@ int isogs_render_fwd_ordered(const isogs_projected* proj, const int32_t* n_per_v
  *   grads          host array [V] of output buffers in scene layout; views whose scene
  *                  pointers (pos) are equal must pass equal grads entries: their
  *                  gradients are summed in view order. Outputs are overwritten.
- *   ws, ws_bytes   workspace (query with ws == NULL, 256-byte aligned): 32 bytes per
+ *   ws, ws_bytes   workspace (query with ws == NULL, 256-byte aligned): 33 bytes per
  *                  entry of capacity - each entry's gradient record is stored at its emit
- *                  position, so a particle's records are contiguous - plus a tile queue of
- *                  4 bytes per tile of the largest group of 16 views (one workgroup per
- *                  chunk of a long tile, then per tile, longest entry list first), and
- *                  the chunk list, 8 bytes per ISOGS_CKPT_CHUNK entries of capacity and
+ *                  position, so a particle's records are contiguous, and a byte marks the
+ *                  entries that have one - plus a tile queue of 4 bytes per tile of the
+ *                  largest group of 16 views (one workgroup per chunk of a long tile that
+ *                  some pixel reached, then per tile, longest entry list first), and the
+ *                  chunk list, 8 bytes per ISOGS_CKPT_CHUNK entries of capacity and
  *                  per tile
  * Errors: ISOGS_ERR_INVALID, ISOGS_ERR_WORKSPACE, ISOGS_ERR_DEVICE. */
 int isogs_render_bwd(const isogs_scene* scenes, const isogs_camera* cams, int32_t n_views,

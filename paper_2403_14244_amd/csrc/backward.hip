@@ -3,22 +3,21 @@
 //
 //   1. composite_bwd  per tile: walk each pixel's entries in reverse from n_last,
 //                     recovering T before each entry as T_after / (1 - alpha); reduce each
-//                     entry's screen-space gradient over the tile's pixels (wavefront DPP
-//                     sums, then the four waves in fixed order) into one record per entry,
-//                     stored at the entry's emit position.
+//                     entry's screen-space gradient over the tile's pixels (matrix cores
+//                     over the 16 pixels of a sub-block, then the sub-blocks in fixed
+//                     order) into one record per entry, stored at the entry's emit position.
 //   2. grad_project   per particle: sum its records (consecutive in emit order, views in
 //                     order) and chain them to mu, sigma, o and the colour coefficients.
 // There are no floating-point atomics: every sum has a fixed order.
 #include <algorithm>
+#include <type_traits>
 
 #include "raster.h"
 
 namespace isogs {
 
-// Entries staged per round, one per lane of a wave (the other lanes idle in staging): 48
-// keeps LDS at about 25 KB per workgroup and measured faster than 32 or 64.
-constexpr int kBwdBatch = 48;
-static_assert(kBwdBatch <= kWave, "one staged entry per lane");
+// Entries staged per round, one per thread: a checkpoint chunk is one round.
+constexpr int kBwdBatch = 256;
 constexpr int kBwdDummy = kBwdBatch;   // staged slot of the zero-opacity pad record
 
 // Per-entry gradient sums over a tile's pixels (dx = x - u, dy = y - v; k = dL/dalpha
@@ -28,93 +27,228 @@ constexpr int kBwdDummy = kBwdBatch;   // staged slot of the zero-opacity pad re
 // (the anisotropic centre and conic gradients are these sums times the entry's conic,
 // applied per particle). A record holds them in kRecVec4<AN> float4s at the entry's emit
 // position.
+//
+// The sums over a sub-block's 16 pixels are a contraction: of k with the pixel's monomials
+// 1, X, Y and X^2 + Y^2 (anisotropic: X^2, XY, Y^2), X and Y measured from the sub-block's
+// centre, and of w with dL/dcolour. A step of the walk (four entries of each of a wave's four
+// sub-blocks) holds k and w as one pixel per lane; they are passed through 1.25 KB of LDS
+// into the A operand of v_mfma_f32_16x16x4_f32 (rows: sub-block and entry, K: pixel), whose B
+// columns are the monomials (shared by the sub-blocks) and each sub-block's dL/dcolour: eight
+// matrix instructions per step replace about 90 cross-lane additions and selects, and the
+// products of k with dx, dy and d^2. The moments are moved to the entry's centre when the
+// sub-blocks are combined. The products and sums are FP32.
+// Measured with the list layout below, one 1080p view of 1M particles: 254 -> 187 us, 110M ->
+// 60M vector instructions; anisotropic 392 -> 339 us; 6M particles, eight 4K views, where most
+// entries lie behind the last one composited: 8.1 -> 4.9 ms.
+// 
 template <bool AN>
 constexpr int kGradTerms = AN ? 9 : 7;
 template <bool AN>
+constexpr int kMoments = AN ? 6 : 4;   // part[][q]: the moments of k, then dr w, dg w, db w
+template <bool AN>
 constexpr int kRecVec4 = AN ? 3 : 2;
 
-// One batch of a tile's entries in LDS, back to front, with the 16 sub-block lists.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kTransPitch = 20;   // floats per row of the transposing buffer: bank-conflict free both ways
+
+// Pairs (entry, sub-block that it may touch) of a round, held in LDS list by list: the lists
+// of the 16 sub-blocks lie back to back, each padded to a multiple of four, and the sums of
+// the pair at list index i are part[i]. A 4x4 sub-block is touched by few of a round's
+// entries (about 2 sub-blocks per entry on 1080p views of 1M particles), so a round of 256
+// entries with its pairs takes less LDS than 48 entries with all 16 sub-blocks each, and the
+// longer lists leave less of a wave idle: with 48 entries a wave's four lists had 2.2
+// four-entry steps between two barriers. A round whose pairs exceed the capacity keeps only
+// its first entries; the rest go to the next round.
+template <bool AN>
+constexpr uint32_t kPairCap = AN ? 480 : 640;   // four workgroups' LDS per CU
+constexpr uint32_t kPairPad = 16 * 3;   // padding of the 16 lists at most
+template <bool AN>
+constexpr int kPartPitch = AN ? 12 : 8;
+
 template <bool AN>
 struct StagedBwdT {
     float4 fp[kBwdBatch + 1];            // staged kernel (staged_kernel: {u, v, q or nA, log2(o)})
     float4 col[kBwdBatch + 1];           // {r, g, b, 1/o}
     float2 cn[AN ? kBwdBatch + 1 : 1];   // anisotropic: {nB2, nC}
-    uint16_t list[16][kBwdBatch + 4];    // per sub-block, staged slots in walk order
-    uint32_t slot[kBwdBatch];            // emit position of each staged entry
-    uint8_t mask[4][kBwdBatch];          // [wave] which of its sub-blocks listed the entry
-    float part[16][kGradTerms<AN>][kBwdBatch];   // per-sub-block gradient sums of each entry
-    uint32_t gmax[16];                   // largest n_last of each sub-block
+    union {
+        __align__(16) float part[kPairCap<AN>][kPartPitch<AN>];   // gradient sums of each pair
+        __align__(16) float dL[4][3][kWave];                      // before the walk: dL/dcolour of each wave
+    };
+    __align__(16) float trans[4][16 * kTransPitch];   // [wave] k or w of one step: row 4 g + e, column pixel
+    __align__(16) uint32_t cnt[4][16];   // [wave][sub-block]: the wave's entries of each list
+    __align__(8) uint16_t list[kPairCap<AN>];   // byte offsets (16 x staged slot) in walk order
+    uint16_t link[kPairCap<AN>];         // the entry's pair before this one (kLinkEnd: none)
+    __align__(16) uint32_t gmax[16];     // largest n_last of each sub-block
+    uint32_t kept[4];
 };
 
-// Stages the nb entries below list position `hi` back to front (staged slot l holds entry
-// hi - 1 - l, 1-based tile position pos_hi - l) and builds the 16 sub-block lists. Every
-// wave tests the entries against its own quadrant's four sub-blocks, so the lists of a
-// wave are built from its own ballots. An entry joins a sub-block's list when its binning
-// disk touches the sub-block and its position is at most the sub-block's largest n_last
-// (no later entry was composited there). Returns the number of list steps of the calling
-// wave; `len` receives the padded length of this lane's row list. Contains __syncthreads.
+// An entry's pairs are chained through `link`, a chain word holding the pair's list index
+// and, above it, its sub-block.
+constexpr uint32_t kLinkShift = 10, kLinkEnd = 0xFFFFu;
+static_assert(kPairCap<false> <= 1u << kLinkShift && kPairCap<true> <= 1u << kLinkShift, "list index bits");
+static_assert((kBwdBatch + 1) * kSlotBytes <= 0xFFFFu, "staged byte offsets fit 16 bits");
+
+// An entry of a round as its thread holds it.
+struct BwdEntry {
+    EntryLoad e;
+    uint32_t slot;   // emit position (all ones: none)
+    uint32_t head;   // its last pair (chain word)
+};
+
+// A wave's view of the staged lists.
+struct BwdLists {
+    uint32_t kept;    // entries of this round
+    uint32_t steps;   // list steps of the wave (the longest of its four padded lists)
+    uint32_t base;    // this lane's sub-block: first list index
+    uint32_t len;     // and padded length
+};
+
+// Loads the entry of this thread: staged slot t holds list position hi - 1 - t (back to front).
 template <bool AN>
-__device__ __forceinline__ uint32_t stage_bwd(StagedBwdT<AN>& sb, const float4* __restrict__ record,
-                                              const float2* __restrict__ conic, const uint32_t* __restrict__ pidx,
-                                              const uint32_t* __restrict__ offsets, uint32_t n_particles,
-                                              uint32_t hi, uint32_t nb, uint32_t pos_hi, int tx, int ty,
-                                              int tiles_x, int tiles_y, float w_lim, float h_lim, uint32_t& len) {
-    const uint32_t t = threadIdx.x, w = t >> 6, l = lane_id();
-    const uint32_t g = l < nb ? pidx[hi - 1 - l] : 0xFFFFFFFFu;
-    uint32_t mask = 0;
-    if (g < n_particles) {
-        const float4 f = record[2 * (size_t)g];
-        const float4 c = record[2 * (size_t)g + 1];
-        if (w == 0) {
-            sb.fp[l] = staged_kernel<AN>(f);
-            sb.col[l] = make_float4(c.x, c.y, c.z, __builtin_amdgcn_rcpf(f.w));   // once per entry
-        } else if (w == 1) {
-            sb.slot[l] = emit_slot(offsets[g], f.x, f.y, c.w, tx, ty, tiles_x, tiles_y, w_lim, h_lim);
-        } else if (AN && w == 2) {
-            sb.cn[l] = staged_conic(conic[g]);
+__device__ __forceinline__ BwdEntry load_bwd(const float4* __restrict__ record, const float2* __restrict__ conic,
+                                             const uint32_t* __restrict__ pidx, const uint32_t* __restrict__ offsets,
+                                             uint32_t n_particles, uint32_t hi, uint32_t nb) {
+    BwdEntry b;
+    const uint32_t t = threadIdx.x;
+    const uint32_t g = t < nb ? pidx[hi - 1 - t] : 0xFFFFFFFFu;
+    b.e = load_entry<AN>(record, g, n_particles, conic);
+    b.slot = g < n_particles ? offsets[g] : 0xFFFFFFFFu;   // the particle's first; see stage_bwd
+    b.head = kLinkEnd;
+    return b;
+}
+
+__device__ __forceinline__ float4 staged_at(const float4* v, uint32_t off) {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(v) + off);
+}
+
+// Inclusive scan over each 16-lane row.
+__device__ __forceinline__ uint32_t row_inclusive_scan(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
+    return x;
+}
+
+// Lanes l of wave w whose thread index 64 w + l is at least `first` (scalar arithmetic).
+__device__ __forceinline__ uint64_t lanes_from(uint32_t first, uint32_t w) {
+    const uint32_t s = first > 64u * w ? first - 64u * w : 0u;
+    return s < 64u ? ~0ull << s : 0ull;
+}
+
+// Stages a round's entries and builds the 16 sub-block lists. An entry joins a sub-block's
+// list when its binning disk touches the sub-block (sub_block_touched, with the squared
+// offsets of the four columns and rows formed once) and its position (pos_hi - t, 1-based) is
+// at most the sub-block's largest n_last (no later entry was composited there). Contains
+// __syncthreads.
+template <bool AN>
+__device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, uint32_t nb, uint32_t pos_hi, int tx,
+                                              int ty, int tiles_x, int tiles_y, float w_lim, float h_lim) {
+    const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = lane_id();
+    float dxx[4], dyy[4], r2 = __builtin_nanf("");   // no entry: no comparison holds
+    {
+        const float4 f = b.e.f, c = b.e.c;
+        if (b.e.ok) {
+            sb.fp[t] = staged_kernel<AN>(f);
+            sb.col[t] = make_float4(c.x, c.y, c.z, __builtin_amdgcn_rcpf(f.w));   // once per entry
+            if (AN) sb.cn[t] = staged_conic(b.e.k);
+            r2 = c.w * c.w;
         }
-        const float r2 = c.w * c.w;
-        const uint32_t pos1 = pos_hi - l;
+        // (a sub-block without pixels has gmax 0 and keeps no entry)
+        const float xb = (float)(tx * kTile) + 0.5f, yb = (float)(ty * kTile) + 0.5f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int k = 4 * (int)w + r;
-            if (pos1 <= sb.gmax[k] && sub_block_touched(f.x, f.y, r2, k, tx * kTile, ty * kTile, w_lim, h_lim))
-                mask |= 1u << r;
+        for (int q = 0; q < 4; ++q) {
+            const float x_lo = xb + (float)(4 * q), y_lo = yb + (float)(4 * q);
+            const float x_hi = fminf(x_lo + 3.0f, w_lim), y_hi = fminf(y_lo + 3.0f, h_lim);
+            const float dx = fmaxf(fmaxf(x_lo - f.x, f.x - x_hi), 0.0f);
+            const float dy = fmaxf(fmaxf(y_lo - f.y, f.y - y_hi), 0.0f);
+            dxx[q] = dx * dx;
+            dyy[q] = dy * dy;
         }
-    } else if (w == 1 && l < (uint32_t)kBwdBatch) {
-        sb.slot[l] = 0xFFFFFFFFu;
     }
     if (t == 0) {
         sb.fp[kBwdDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());
         sb.col[kBwdDummy] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (AN) sb.cn[kBwdDummy] = make_float2(0.0f, 0.0f);
+        if (AN) sb.cn[AN ? kBwdDummy : 0] = make_float2(0.0f, 0.0f);
     }
-    if (l < (uint32_t)kBwdBatch) sb.mask[w][l] = (uint8_t)mask;
-    uint64_t bal[4];
-    uint32_t cnt[4];
+    BwdLists L;
+    L.kept = nb;
+    uint64_t bal[16];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        bal[r] = ballot64((mask >> r) & 1u);
-        cnt[r] = (uint32_t)__popcll(bal[r]);
-        if ((mask >> r) & 1u) sb.list[4 * w + r][rank_below(bal[r])] = (uint16_t)l;
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t gm = __builtin_amdgcn_readfirstlane(sb.gmax[k]);
+        const int qx = ((k >> 2) & 1) * 2 + (k & 1), qy = ((k >> 2) >> 1) * 2 + ((k & 3) >> 1);
+        bal[k] = ballot64(dxx[qx] + dyy[qy] <= r2) & lanes_from(pos_hi > gm ? pos_hi - gm : 0u, w);
     }
-    if (l < 16) {
-        // pad row l / 4 of this wave with dummies up to a multiple of four
-        const uint32_t r = l >> 2;
-        const uint32_t n = r == 0 ? cnt[0] : r == 1 ? cnt[1] : r == 2 ? cnt[2] : cnt[3];
-        if (n + (l & 3u) < ((n + 3u) & ~3u)) sb.list[4 * w + r][n + (l & 3u)] = (uint16_t)kBwdDummy;
+    uint32_t n = 0, before = 0, total = 0;   // lane k (mod 16): list k's length, entries of earlier waves
+    for (int attempt = 0;; ++attempt) {
+        if (l == 0) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) sb.cnt[w][k] = (uint32_t)__popcll(bal[k]);
+        }
+        __syncthreads();
+        const uint32_t c0 = sb.cnt[0][l & 15u], c1 = sb.cnt[1][l & 15u], c2 = sb.cnt[2][l & 15u],
+                       c3 = sb.cnt[3][l & 15u];
+        n = c0 + c1 + c2 + c3;
+        before = (w > 0 ? c0 : 0u) + (w > 1 ? c1 : 0u) + (w > 2 ? c2 : 0u);
+        total = __builtin_amdgcn_readlane(row_inclusive_scan(n), 15);
+        if (attempt || total + kPairPad <= kPairCap<AN>) break;
+        // too many pairs: keep the first entries that fit (at least (cap - pad) / 16)
+        uint32_t incl = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) incl += (uint32_t)(bal[k] >> l) & 1u;
+#pragma unroll
+        for (uint32_t o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, 64);
+            if (l >= o) incl += y;
+        }
+        if (l == 63) sb.kept[w] = incl;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < 3; ++q) incl += q < w ? sb.kept[q] : 0u;
+        const uint64_t keep = ballot64(t < nb && incl + kPairPad <= kPairCap<AN>);
+        __syncthreads();   // the wave totals have been read
+        if (l == 0) sb.kept[w] = (uint32_t)__popcll(keep);
+        __syncthreads();
+        L.kept = sb.kept[0] + sb.kept[1] + sb.kept[2] + sb.kept[3];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) bal[k] &= keep;
     }
-    const uint32_t row = l >> 4;
-    const uint32_t mine = row == 0 ? cnt[0] : row == 1 ? cnt[1] : row == 2 ? cnt[2] : cnt[3];
-    len = (mine + 3u) & ~3u;
-    const uint32_t most = max(max(cnt[0], cnt[1]), max(cnt[2], cnt[3]));
+    // lists back to back: lane k (mod 16) holds list k's padded length and first index
+    const uint32_t padded = (n + 3u) & ~3u;
+    const uint32_t base = row_inclusive_scan(padded) - padded, at = base + before;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t first = __builtin_amdgcn_readlane(at, k);
+        if ((bal[k] >> l) & 1u) {
+            const uint32_t i = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[k] >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal[k], first));
+            sb.list[i] = (uint16_t)(t * kSlotBytes);
+            sb.link[i] = (uint16_t)b.head;
+            b.head = i | (uint32_t)k << kLinkShift;
+        }
+    }
+    if (b.e.ok) b.slot = emit_slot(b.slot, b.e.f.x, b.e.f.y, b.e.c.w, tx, ty, tiles_x, tiles_y, w_lim, h_lim);
+    if (w == 0) {
+        // pad list l / 4 with dummies
+        const int k = (int)(l >> 2);
+        const uint32_t i = __shfl(n, k, 64) + (l & 3u), pk = __shfl(padded, k, 64), bk = __shfl(base, k, 64);
+        if (i < pk) sb.list[bk + i] = (uint16_t)(kBwdDummy * kSlotBytes);
+    }
+    const int sbk = (int)(4u * w + (l >> 4));
+    L.base = __shfl(base, sbk, 64);
+    L.len = __shfl(padded, sbk, 64);
+    const uint32_t most = max(max(__builtin_amdgcn_readlane(L.len, 0), __builtin_amdgcn_readlane(L.len, 16)),
+                              max(__builtin_amdgcn_readlane(L.len, 32), __builtin_amdgcn_readlane(L.len, 48)));
+    L.steps = total ? most : 0u;
     __syncthreads();
-    return (most + 3u) & ~3u;
+    return L;
 }
 
 // Reverse walk of one tile (logical index within the launch) by a 256-thread workgroup,
 // one lane per pixel, each 16-lane row owning a 4x4 sub-block (the forward pixel layout).
-// Record of an entry: its gradient sums (kGradTerms), at its emit position.
+// Record of an entry: its gradient sums (kGradTerms), at its emit position, marked in
+// has_rec; an entry that no pixel composited has neither.
 // With checkpoints (`ckpt` non-null) and a list of at least kChunkedMin entries, the
 // workgroup walks only chunk `chunk` of the list, positions [chunk * kCkptChunk,
 // (chunk + 1) * kCkptChunk); a pixel whose last entry lies beyond the chunk starts from the
@@ -127,11 +261,11 @@ __device__ __forceinline__ void composite_bwd_tile(
     const float2* __restrict__ conic, const uint32_t* __restrict__ pidx, const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ ranges,
     float bg_r, float bg_g, float bg_b, const float* __restrict__ image, const float* __restrict__ dL_dimage,
     const float* __restrict__ T_final, const uint32_t* __restrict__ n_last, const float4* __restrict__ ckpt,
-    float4* __restrict__ rec) {
+    float4* __restrict__ rec, uint8_t* __restrict__ has_rec) {
     int vi, tx, ty;
     locate_tile(pk, logical, vi, tx, ty);
     const ViewDesc& vd = pk.v[vi];
-    const uint32_t t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = lane_id();
     const uint32_t sbk = 4 * w + ((t >> 4) & 3u);   // this lane's sub-block
     const int x = tx * kTile + sub_x(t), y = ty * kTile + sub_y(t);
     const bool inside = x < vd.width && y < vd.height;
@@ -144,10 +278,14 @@ __device__ __forceinline__ void composite_bwd_tile(
     const bool chunked = ckpt && chunked_list(len);
     const uint32_t c_lo = chunked ? chunk * kCkptChunk : 0u;
     const uint32_t c_hi = chunked ? min(c_lo + kCkptChunk, len) : len;
-    if (c_lo > c_hi) return;   // no such chunk (uniform over the workgroup)
+    if (c_lo >= c_hi) return;   // no such chunk, or an empty list (uniform over the workgroup)
 
-    float T = 1.0f, dr = 0.0f, dg = 0.0f, db = 0.0f;
-    float Sr = 0.0f, Sg = 0.0f, Sb = 0.0f;
+    // the first round's entries are loaded beside the pixels
+    uint32_t hi = start + c_hi, nb = min((uint32_t)kBwdBatch, c_hi - c_lo);
+    BwdEntry b = load_bwd<AN>(record, conic, pidx, offsets, pk.n_particles, hi, nb);
+
+    // S: light from behind the current entry (per channel) dotted with dL/dcolour
+    float T = 1.0f, dr = 0.0f, dg = 0.0f, db = 0.0f, S = 0.0f;
     uint32_t last = 0;
     if (inside) {
         const size_t hw = (size_t)vd.width * vd.height;
@@ -162,144 +300,186 @@ __device__ __forceinline__ void composite_bwd_tile(
             const float4 s = ckpt[(size_t)ckpt_slot(start, c_hi / kCkptChunk) * 256 + t];
             const float* im = image + (size_t)3 * vd.pix_off;
             T = s.x;
-            Sr = im[pix] - s.y;
-            Sg = im[hw + pix] - s.z;
-            Sb = im[2 * hw + pix] - s.w;
+            S = dr * (im[pix] - s.y) + dg * (im[hw + pix] - s.z) + db * (im[2 * hw + pix] - s.w);
         } else {
             // light arriving from behind the last entry: T_final bg
             T = T_final[vd.pix_off + pix];
-            Sr = T * bg_r;
-            Sg = T * bg_g;
-            Sb = T * bg_b;
+            S = T * (dr * bg_r + dg * bg_g + db * bg_b);
         }
     }
 
     if (t < 16) sb.gmax[t] = 0u;
+    sb.dL[w][0][lane] = dr;
+    sb.dL[w][1][lane] = dg;
+    sb.dL[w][2][lane] = db;
     __syncthreads();
     if (last > c_lo) atomicMax(&sb.gmax[sbk], min(last, c_hi));
-    __syncthreads();
-    uint32_t max_last = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) max_last = max(max_last, sb.gmax[k]);
-    max_last = max(max_last, c_lo);   // 1-based end of the walk inside [c_lo, c_hi]
+    if (!__syncthreads_or(last > c_lo)) return;   // no pixel composited an entry from here on
 
-    // entries of the chunk no pixel reached carry zero gradient
-    for (uint32_t e = start + max_last + t; e < start + c_hi; e += 256) {
-        const uint32_t g = pidx[e];
-        if (g < pk.n_particles) {
-            const float4 f = record[2 * (size_t)g];
-            const float r = record[2 * (size_t)g + 1].w;
-            const uint32_t slot = emit_slot(offsets[g], f.x, f.y, r, tx, ty, vd.tiles_x, vd.tiles_y, w_lim, h_lim);
-            if (slot < pk.n_entries_cap) {
+    // B operands of the reduction, one register per K step m (K index lane / 16, pixel
+    // 4 (lane / 16) + m of a sub-block, i.e. X = m - 1.5, Y = lane / 16 - 1.5): column
+    // lane % 16 < 12 is channel column % 3 of dL/dcolour of the wave's sub-block column / 3;
+    // the moments take columns 12 - 15 (anisotropic: columns 0 - 5). k and w have an
+    // accumulator each, so that a non-finite k does not reach the colour sums through the
+    // zero columns
+    const uint32_t col = lane & 15u, row = lane >> 4, ch = col % 3u;
+    const float4 w4 = *reinterpret_cast<const float4*>(&sb.dL[w][ch][(16u * (col / 3u) + 4u * row) & 63u]);
+    const float b_w[4] = {col < 12u ? w4.x : 0.0f, col < 12u ? w4.y : 0.0f, col < 12u ? w4.z : 0.0f,
+                          col < 12u ? w4.w : 0.0f};
+    float b_k[4];
 #pragma unroll
-                for (int q = 0; q < kRecVec4<AN>; ++q)
-                    rec[kRecVec4<AN> * (size_t)slot + q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
-        }
+    for (uint32_t m = 0; m < 4; ++m) {
+        const float X = (float)m - 1.5f, Y = (float)row - 1.5f;
+        const uint32_t q = AN ? col : col - 12u;   // isotropic: wraps to a large value below column 12
+        b_k[m] = q == 0u ? 1.0f : q == 1u ? X : q == 2u ? Y : 0.0f;
+        if (!AN && q == 3u) b_k[m] = X * X + Y * Y;
+        if (AN) b_k[m] = q == 3u ? X * X : q == 4u ? X * Y : q == 5u ? Y * Y : b_k[m];
     }
+    // this lane's column of a result (row 4 g + e: entry e of sub-block g = lane / 16)
+    const bool w_writer = col < 12u && col / 3u == row;
+    const bool k_writer = AN ? col < 6u : col >= 12u;
+    const uint32_t w_term = kMoments<AN> + ch, k_term = (AN ? col : col - 12u) & 7u;
+    float* const t_write = &sb.trans[w][4u * row * kTransPitch + col];
+    const float* const t_read = &sb.trans[w][col * kTransPitch + 4u * row];
 
-    const uint32_t q8 = rev3(lane & 7u);
-    const bool writer = (lane & 15u) < 8u && q8 < (uint32_t)kGradTerms<AN>;
-    const bool writer9 = AN && (lane & 15u) == 8u;   // the ninth sum
-    for (uint32_t hi = start + max_last; hi > start + c_lo;) {
-        const uint32_t nb = min((uint32_t)kBwdBatch, hi - start - c_lo);
+    while (true) {
         const uint32_t pos_hi = hi - start;
-        uint32_t len;
-        const uint32_t steps = stage_bwd(sb, record, conic, pidx, offsets, pk.n_particles, hi, nb, pos_hi, tx, ty,
-                                         vd.tiles_x, vd.tiles_y, w_lim, h_lim, len);
-        for (uint32_t k = 0; k < steps; k += 4) {
-            constexpr uint64_t kD = (uint64_t)kBwdDummy;
+        const BwdLists L = stage_bwd(sb, b, nb, pos_hi, tx, ty, vd.tiles_x, vd.tiles_y, w_lim, h_lim);
+        // staged slot j holds list position pos_hi - j (1-based): composited by this pixel
+        // in the forward pass only from slot pos_hi - last on
+        const int off_min = ((int)pos_hi - (int)last) * (int)kSlotBytes;
+        for (uint32_t k = 0; k < L.steps; k += 4) {
+            constexpr uint64_t kD = (uint64_t)kBwdDummy * kSlotBytes;
             uint64_t q4 = kD | (kD << 16) | (kD << 32) | (kD << 48);   // four dummy slots
-            if (k < len) q4 = *reinterpret_cast<const uint64_t*>(&sb.list[sbk][k]);
+            const bool on = k < L.len;
+            if (on) q4 = *reinterpret_cast<const uint64_t*>(&sb.list[L.base + k]);
+            // colour . dL/dcolour of the four entries at this lane's pixel: lane e of a quad
+            // brings entry e's colour (4 x 4 x 1 blocks: row entry, column pixel)
+            const float4 c4 = staged_at(sb.col, (uint32_t)(q4 >> (16u * (lane & 3u))) & 0xFFFFu);
+            f32x4 cd = {0.0f, 0.0f, 0.0f, 0.0f};
+            cd = __builtin_amdgcn_mfma_f32_4x4x1f32(c4.x, dr, cd, 0, 0, 0);
+            cd = __builtin_amdgcn_mfma_f32_4x4x1f32(c4.y, dg, cd, 0, 0, 0);
+            cd = __builtin_amdgcn_mfma_f32_4x4x1f32(c4.z, db, cd, 0, 0, 0);
+            float kk[4], wg[4];
+            bool any = false;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const uint32_t j = (uint32_t)(q4 >> (16 * r)) & 0xFFFFu;
-                const uint32_t pos1 = pos_hi - j;            // 1-based list position
-                const float4 f = sb.fp[j];
-                const float4 c = sb.col[j];
-                const float2 kc = AN ? sb.cn[j] : make_float2(0.0f, 0.0f);
-                const float dx = px - f.x, dy = py - f.y;
+                const uint32_t off = (uint32_t)(q4 >> (16 * r)) & 0xFFFFu;
+                const float4 f = staged_at(sb.fp, off);
+                const float2 kc = AN ? sb.cn[off / kSlotBytes] : make_float2(0.0f, 0.0f);
                 float ga;
-                float a = staged_alpha<AN>(dx, dy, f, kc, ga);
+                float a = staged_alpha<AN>(px - f.x, py - f.y, f, kc, ga);
                 // an entry this pixel composited in the forward pass (same decision); the
                 // pad record has alpha 0
-                const bool use = (pos1 <= last) && (a >= kAlphaMin);
+                const bool use = (int)off >= off_min && a >= kAlphaMin;
+                any = any || use;
                 a = use ? a : 0.0f;
                 const float inv_om = __builtin_amdgcn_rcpf(1.0f - a);
                 T = T * inv_om;                              // transmittance before this entry
-                const float wgt = a * T;
-                const float dLda = dr * (c.x * T - Sr * inv_om) + dg * (c.y * T - Sg * inv_om) +
-                                   db * (c.z * T - Sb * inv_om);
-                Sr = fmaf(c.x, wgt, Sr);
-                Sg = fmaf(c.y, wgt, Sg);
-                Sb = fmaf(c.z, wgt, Sb);
+                wg[r] = a * T;
+                const float dLda = fmaf(-S, inv_om, cd[r] * T);
+                S = fmaf(cd[r], wg[r], S);
                 // alpha = o exp(-d^2 / s^2) below the clamp: d/du = 2 alpha dx / s^2,
                 // d/d(1/s^2) = -alpha d^2, d/do = alpha / o
-                const float kk = (use && ga < kAlphaMax) ? dLda * ga : 0.0f;
-                float gv[8], g9 = 0.0f;
-                if (!AN) {
-                    const float inv_s2 = f.z * (1.0f / kLog2e);
-                    gv[0] = 2.0f * kk * inv_s2 * dx;
-                    gv[1] = 2.0f * kk * inv_s2 * dy;
-                    gv[2] = -kk * fmaf(dx, dx, dy * dy);
-                    gv[3] = kk * c.w;
-                    gv[4] = dr * wgt;
-                    gv[5] = dg * wgt;
-                    gv[6] = db * wgt;
-                    gv[7] = 0.0f;
-                } else {
-                    // alpha = o exp(-Q) below the clamp: dL/du = k (2 A dx + 2 B dy),
-                    // dL/dA = -k dx^2, ...: the conic enters per particle
-                    const float kx = kk * dx, ky = kk * dy;
-                    gv[0] = kx;
-                    gv[1] = ky;
-                    gv[2] = kx * dx;
-                    gv[3] = kx * dy;
-                    gv[4] = ky * dy;
-                    gv[5] = kk * c.w;
-                    gv[6] = dr * wgt;
-                    gv[7] = dg * wgt;
-                    g9 = db * wgt;
-                }
-                const bool any = ballot64(use) != 0;
-                const float red = any ? row_sum8(gv, lane) : 0.0f;
-                if (writer && j != kBwdDummy) sb.part[sbk][q8][j] = red;
+                kk[r] = (use && ga < kAlphaMax) ? dLda * ga : 0.0f;
+            }
+            f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f}, sum_k = sum;
+            if (ballot64(any) != 0) {
+                // LDS operations of one wave complete in order: the buffer serves k, then w
+#pragma unroll
+                for (int r = 0; r < 4; ++r) t_write[r * kTransPitch] = kk[r];
+                __builtin_amdgcn_wave_barrier();
+                const float4 ak = *reinterpret_cast<const float4*>(t_read);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) t_write[r * kTransPitch] = wg[r];
+                __builtin_amdgcn_wave_barrier();
+                const float4 aw = *reinterpret_cast<const float4*>(t_read);
+                __builtin_amdgcn_wave_barrier();
+                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.x, b_k[0], sum_k, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.x, b_w[0], sum, 0, 0, 0);
+                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.y, b_k[1], sum_k, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.y, b_w[1], sum, 0, 0, 0);
+                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.z, b_k[2], sum_k, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.z, b_w[2], sum, 0, 0, 0);
+                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.w, b_k[3], sum_k, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.w, b_w[3], sum, 0, 0, 0);
+            }
+            // the sums of pads are written too (nothing reads them)
+            if (on) {
+                float(*pr)[kPartPitch<AN>] = &sb.part[L.base + k];
                 if (AN) {
-                    // the ninth sum over the row: butterfly (quad swaps, row rotations)
-                    float r9 = g9;
-                    if (any) {
-                        r9 += dpp<0xB1>(r9);
-                        r9 += dpp<0x4E>(r9);
-                        r9 += dpp<0x124>(r9);
-                        r9 += dpp<0x128>(r9);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (k_writer) pr[r][k_term] = sum_k[r];
+                        if (w_writer) pr[r][w_term] = sum[r];
                     }
-                    if (writer9 && j != kBwdDummy) sb.part[sbk][kGradTerms<AN> - 1][j] = r9;
+                } else if (k_writer || w_writer) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) pr[r][k_writer ? k_term : w_term] = k_writer ? sum_k[r] : sum[r];
                 }
             }
         }
         __syncthreads();
-        // combine: the sub-blocks that listed an entry, in fixed order; wave w writes
-        // float4 w of each record (sums 4w .. 4w + 3)
-        const uint32_t l = lane;
-        if (w < (uint32_t)kRecVec4<AN> && l < nb) {
-            const uint32_t m = (uint32_t)sb.mask[0][l] | ((uint32_t)sb.mask[1][l] << 4) |
-                               ((uint32_t)sb.mask[2][l] << 8) | ((uint32_t)sb.mask[3][l] << 12);
-            const int q0 = 4 * (int)w;
-            float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        // combine: each thread sums its entry's pairs (from the last sub-block), the moments moved
+        // from the sub-block's centre (X, Y) to the entry's: dx = X' + (X - u)
+        if (b.head != kLinkEnd && b.slot < pk.n_entries_cap) {
+            // the moments are moved in FP64 (anisotropic): along a thin kernel's minor axis the
+            // second moments cancel, and rounding each on its way would be amplified there
+            using M = typename std::conditional<AN, double, float>::type;
+            const M rel_x = (M)((float)(tx * kTile) + 2.0f) - (M)b.e.f.x;
+            const M rel_y = (M)((float)(ty * kTile) + 2.0f) - (M)b.e.f.y;
+            M s[AN ? 6 : 4];
+            float c[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                if ((m >> k) & 1u) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (q0 + e < kGradTerms<AN>) s4[e] += sb.part[k][q0 + e][l];
+            for (int q = 0; q < (AN ? 6 : 4); ++q) s[q] = (M)0;
+            uint32_t next = b.head;
+            while (next != kLinkEnd) {
+                const uint32_t i = next & ((1u << kLinkShift) - 1u), k = next >> kLinkShift;
+                next = sb.link[i];
+                const float4 p0 = *reinterpret_cast<const float4*>(&sb.part[i][0]);
+                const float4 p1 = *reinterpret_cast<const float4*>(&sb.part[i][4]);
+                const M ax = rel_x + (M)(float)(((k >> 2) & 1u) * 8u + (k & 1u) * 4u);
+                const M ay = rel_y + (M)(float)((k >> 3) * 8u + ((k & 3u) >> 1) * 4u);
+                const M m0 = p0.x, mx = p0.y, my = p0.z;
+                const M kx = fma(ax, m0, mx), ky = fma(ay, m0, my);   // k dx, k dy
+                s[0] += kx;
+                s[1] += ky;
+                if constexpr (!AN) {
+                    // k d^2 = k (X'^2 + Y'^2) + ax (k X' + k dx) + ay (k Y' + k dy)
+                    s[2] += p0.w + fma(ax, mx + kx, ay * (my + ky));
+                    s[3] += m0;
+                    c[0] += p1.x;
+                    c[1] += p1.y;
+                    c[2] += p1.z;
+                } else {
+                    s[2] += fma(ax, mx + kx, (M)p0.w);
+                    s[3] += fma(ax, my, fma(ay, kx, (M)p1.x));
+                    s[4] += fma(ay, my + ky, (M)p1.y);
+                    s[5] += m0;
+                    c[0] += p1.z;
+                    c[1] += p1.w;
+                    c[2] += sb.part[i][8];
                 }
             }
-            const uint32_t slot = sb.slot[l];
-            if (slot < pk.n_entries_cap)
-                rec[kRecVec4<AN> * (size_t)slot + w] = make_float4(s4[0], s4[1], s4[2], s4[3]);
+            const float inv_o = sb.col[t].w;
+            float4* r = rec + kRecVec4<AN> * (size_t)b.slot;
+            if constexpr (!AN) {
+                const float two_inv_s2 = 2.0f * (sb.fp[t].z * (1.0f / kLog2e));
+                r[0] = make_float4(two_inv_s2 * s[0], two_inv_s2 * s[1], -s[2], inv_o * s[3]);
+                r[1] = make_float4(c[0], c[1], c[2], 0.0f);
+            } else {
+                r[0] = make_float4((float)s[0], (float)s[1], (float)s[2], (float)s[3]);
+                r[1] = make_float4((float)s[4], inv_o * (float)s[5], c[0], c[1]);
+                r[2] = make_float4(c[2], 0.0f, 0.0f, 0.0f);
+            }
+            has_rec[b.slot] = 1;
         }
-        __syncthreads();
-        hi -= nb;
+        hi -= L.kept;
+        if (hi <= start + c_lo) break;
+        nb = min((uint32_t)kBwdBatch, hi - start - c_lo);
+        b = load_bwd<AN>(record, conic, pidx, offsets, pk.n_particles, hi, nb);
+        __syncthreads();   // the staged round has been read
     }
 }
 
@@ -307,44 +487,79 @@ __global__ void __launch_bounds__(64) fill_u32_kernel_b(uint32_t* __restrict__ p
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
 }
 
-// Work items of the tiles whose list is longer than one checkpoint chunk: one
-// (tile, chunk) pair per chunk, appended in any order, with one device-wide add per
-// workgroup (adds to one counter from many XCDs are serialised in memory).
-__global__ void __launch_bounds__(256) bwd_chunk_list_kernel(const uint32_t* __restrict__ ranges, uint32_t tile0,
-                                                             uint32_t n_tiles, uint32_t cap,
+__global__ void __launch_bounds__(256) clear_marks_kernel(uint8_t* __restrict__ marks,
+                                                          const uint32_t* __restrict__ count_p, uint64_t capacity) {
+    // (the marks are 256-byte aligned and padded to whole 16-byte vectors)
+    const uint64_t n = min((uint64_t)*count_p, capacity);
+    for (uint64_t i = ((uint64_t)blockIdx.x * 256u + threadIdx.x) * 16u; i < n; i += (uint64_t)gridDim.x * 4096u)
+        *reinterpret_cast<uint4*>(marks + i) = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Work items of the tiles whose list is longer than one checkpoint chunk: one (tile, chunk)
+// pair per chunk up to the last that a pixel of the tile composited from (occluded entries,
+// most of the long lists of dense scenes, then cost no workgroup), appended in any order,
+// with one device-wide add per workgroup (adds to one counter from many XCDs are serialised
+// in memory). A workgroup takes 64 tiles; 16 lanes read a tile's n_last, a row each.
+constexpr uint32_t kReachTiles = 64;
+
+__global__ void __launch_bounds__(256) bwd_chunk_list_kernel(const RenderPack pk, const uint32_t* __restrict__ ranges,
+                                                             uint32_t tile0, uint32_t n_tiles,
+                                                             const uint32_t* __restrict__ n_last,
                                                              const int32_t* __restrict__ status,
                                                              uint32_t* __restrict__ heavy,
                                                              uint32_t* __restrict__ heavy_count,
                                                              uint32_t heavy_max) {
-    __shared__ uint32_t s_wave[4];
-    __shared__ uint32_t s_base;
+    __shared__ uint32_t s_n[kReachTiles];
     if (*status != kStatusOk) return;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    uint32_t nch = 0;
-    if (i < n_tiles) {
-        const uint32_t s = ranges[2 * (tile0 + i)], e = min(ranges[2 * (tile0 + i) + 1], cap);
-        const uint32_t len = e > s ? e - s : 0u;
-        if (chunked_list(len)) nch = (len + kCkptChunk - 1) / kCkptChunk;
+    const uint32_t lane = lane_id(), w = threadIdx.x >> 6, r = lane & 15u;
+#pragma unroll
+    for (uint32_t q = 0; q < kReachTiles / 16; ++q) {
+        const uint32_t at = 16u * q + 4u * w + (lane >> 4);   // tile of this row of lanes
+        const uint32_t i = blockIdx.x * kReachTiles + at;
+        uint32_t most = 0, len = 0;
+        if (i < n_tiles) {
+            const uint32_t s = ranges[2 * (tile0 + i)], e = min(ranges[2 * (tile0 + i) + 1], pk.n_entries_cap);
+            len = e > s ? e - s : 0u;
+        }
+        if (chunked_list(len)) {
+            int v = 0;
+            for (int j = 1; j < pk.nv; ++j) v = i >= pk.block_begin[j] ? j : v;
+            const ViewDesc& vd = pk.v[v];
+            const uint32_t local = i - pk.block_begin[v];
+            const int x0 = (int)(local % (uint32_t)vd.tiles_x) * kTile;
+            const int y = (int)(local / (uint32_t)vd.tiles_x) * kTile + (int)r;
+            if (y < vd.height) {
+                const uint32_t* p = n_last + vd.pix_off + (size_t)y * vd.width + x0;
+                if (x0 + kTile <= vd.width && (reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint4 n = reinterpret_cast<const uint4*>(p)[c];
+                        most = max(most, max(max(n.x, n.y), max(n.z, n.w)));
+                    }
+                } else {
+                    for (int c = 0; c < min(kTile, vd.width - x0); ++c) most = max(most, p[c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, o, 16));
+        if (r == 0) s_n[at] = chunked_list(len) ? (min(most, len) + kCkptChunk - 1) / kCkptChunk : 0u;
     }
+    __syncthreads();
+    if (w != 0) return;
+    const uint32_t nch = s_n[lane];
     uint32_t incl = nch;
 #pragma unroll
     for (uint32_t o = 1; o < 64; o <<= 1) {
         const uint32_t y = __shfl_up(incl, o, 64);
         if (lane >= o) incl += y;
     }
-    if (lane == 63) s_wave[w] = incl;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-        const uint32_t c = s_wave[q];
-        before += q < w ? c : 0u;
-        total += c;
-    }
-    if (threadIdx.x == 0) s_base = total ? atomicAdd(heavy_count, total) : 0u;
-    __syncthreads();
-    const uint32_t base = s_base + before + incl - nch;
+    const uint32_t total = __shfl(incl, 63, 64);
+    uint32_t base = 0;
+    if (lane == 0 && total) base = atomicAdd(heavy_count, total);
+    base = __shfl(base, 0, 64) + incl - nch;
     if (!nch || base + nch > heavy_max) return;   // the bound holds for ranges that partition the entries
+    const uint32_t i = blockIdx.x * kReachTiles + lane;
     for (uint32_t c = 0; c < nch; ++c) {
         heavy[2 * (base + c)] = i;
         heavy[2 * (base + c) + 1] = c;
@@ -352,7 +567,7 @@ __global__ void __launch_bounds__(256) bwd_chunk_list_kernel(const uint32_t* __r
 }
 
 // One workgroup per work item, in dispatch order. With checkpoints: workgroups
-// [0, n_chunks) take the chunks of the long tiles (listed by bwd_chunk_list_kernel), the
+// [0, n_chunks) take the reached chunks of the long tiles (listed by bwd_chunk_list_kernel), the
 // next ones the other tiles in longest-list-first order (they follow the long ones in the
 // queue, whose length classes tell how many those are); a workgroup past the last item
 // leaves at once. Without: workgroup b walks the tile at queue position b whole.
@@ -370,6 +585,7 @@ struct BwdArgs {
     const uint32_t* n_last;
     const float4* ckpt;
     float4* rec;
+    uint8_t* has_rec;
     const uint32_t* order;
     const uint32_t* hist;
     uint32_t n_items;
@@ -405,16 +621,16 @@ __device__ __forceinline__ void bwd_ordered(StagedBwdT<AN>& sb, const RenderPack
         logical = order[b];
     }
     composite_bwd_tile(sb, pk, logical, chunk, A.record, A.conic, A.pidx, A.offsets, A.ranges, A.bg_r, A.bg_g, A.bg_b,
-                       A.image, A.dL_dimage, A.T_final, A.n_last, ckpt, A.rec);
+                       A.image, A.dL_dimage, A.T_final, A.n_last, ckpt, A.rec, A.has_rec);
 }
 
-__global__ void __launch_bounds__(256) composite_bwd_ordered_kernel(const RenderPack pk, const BwdArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) composite_bwd_ordered_kernel(const RenderPack pk, const BwdArgs a) {
     __shared__ StagedBwdT<false> sb;
     bwd_ordered(sb, pk, a);
 }
 
 // The anisotropic family (eq. 5 kernels).
-__global__ void __launch_bounds__(256) aniso_bwd_ordered_kernel(const RenderPack pk, const BwdArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) aniso_bwd_ordered_kernel(const RenderPack pk, const BwdArgs a) {
     __shared__ StagedBwdT<true> sb;
     bwd_ordered(sb, pk, a);
 }
@@ -528,17 +744,103 @@ struct GradPack {
     GradView v[kMaxViews];
 };
 
+// The records of a workgroup's 256 particles in one view are one run of the emit order
+// (offsets are a scan of the tile counts). The run is staged in LDS window by window with
+// coalesced loads (marked records only, zeros for the others) and each thread adds its own
+// particle's records from there, in emit order. Read by each thread from global memory, the
+// record loop of a wave lasted as long as its particle with the most tiles, a load latency
+// per turn: 6M particles x 8 views of 4K took 2329 us (2989 us with marks read first).
+constexpr uint32_t kRecWindow = 512;
+
+template <int NV>
+struct RecShared {
+    float4 v[NV][kRecWindow];
+    uint32_t run[2];
+};
+
+// Sums the NV float4s of records [e0, e0 + cnt) into S (zeroed here). Every thread of the
+// workgroup calls it, e0 non-decreasing over the threads; false: no record was marked.
+// Contains __syncthreads.
+template <int NV>
+__device__ __forceinline__ bool sum_records(RecShared<NV>& sh, const float4* __restrict__ rec,
+                                            const uint8_t* __restrict__ has_rec, uint32_t e0, uint32_t cnt,
+                                            float (&S)[4 * NV]) {
+    const uint32_t t = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 4 * NV; ++k) S[k] = 0.0f;
+    if (t == 0) sh.run[0] = e0;
+    if (t == 255) sh.run[1] = e0 + cnt;
+    __syncthreads();
+    const uint32_t lo = sh.run[0], hi = sh.run[1];
+    bool any = false;
+    for (uint32_t w0 = lo; w0 < hi; w0 += kRecWindow) {
+        bool has[kRecWindow / 256];
+#pragma unroll
+        for (uint32_t q = 0; q < kRecWindow / 256; ++q) {
+            const uint32_t e = w0 + q * 256u + t;
+            has[q] = e < hi && has_rec[e];
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < kRecWindow / 256; ++q) {
+            float4 r[NV];
+#pragma unroll
+            for (int k = 0; k < NV; ++k) r[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (has[q]) {
+#pragma unroll
+                for (int k = 0; k < NV; ++k) r[k] = rec[NV * (size_t)(w0 + q * 256u + t) + k];
+            }
+#pragma unroll
+            for (int k = 0; k < NV; ++k) sh.v[k][q * 256u + t] = r[k];
+        }
+        const bool window = __syncthreads_or(has[0] || has[1]);
+        if (window) {
+            any = true;
+            for (uint32_t e = max(e0, w0); e < min(e0 + cnt, w0 + kRecWindow); ++e) {
+#pragma unroll
+                for (int k = 0; k < NV; ++k) {
+                    const float4 r = sh.v[k][e - w0];
+                    S[4 * k] += r.x;
+                    S[4 * k + 1] += r.y;
+                    S[4 * k + 2] += r.z;
+                    S[4 * k + 3] += r.w;
+                }
+            }
+        }
+        __syncthreads();   // the window has been read (and, before the next view, the run)
+    }
+    static_assert(kRecWindow == 512, "two records per thread and window");
+    if (lo >= hi) __syncthreads();   // uniform: the run has been read
+    return any;
+}
+
+// The entries of a particle in one view, clipped to a valid run: [e0, e0 + cnt).
+struct RecRun {
+    uint32_t e0, cnt;
+};
+
+__device__ __forceinline__ RecRun record_run(const uint32_t* __restrict__ tile_count,
+                                             const uint32_t* __restrict__ offsets, uint32_t pi, bool in,
+                                             uint32_t n_entries) {
+    RecRun r{offsets[pi], tile_count[pi]};
+    if ((uint64_t)r.e0 + r.cnt > n_entries) r = {min(r.e0, n_entries), 0u};
+    if (!in) r = {r.e0 + r.cnt, 0u};   // behind the last particle's
+    return r;
+}
+
 // One thread per particle of one scene; DEG is the scene's SH degree.
 template <int DEG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) grad_project_kernel(const GradPack pk, const float4* __restrict__ rec,
+                                                           const uint8_t* __restrict__ has_rec,
                                                            const uint32_t* __restrict__ tile_count,
                                                            const uint32_t* __restrict__ offsets,
                                                            const uint32_t* __restrict__ count_p,
                                                            const int32_t* __restrict__ status) {
+    __shared__ RecShared<kRecVec4<false>> sh;
     if (*status != kStatusOk) return;
     const uint32_t n_entries = *count_p;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= pk.n) return;
+    // threads past the last particle stay for the shared record sums, on the last one's inputs
+    const bool in = blockIdx.x * 256u + threadIdx.x < pk.n;
+    const uint32_t i = min(blockIdx.x * 256u + threadIdx.x, pk.n - 1u);
     const uint32_t n = pk.n;
     constexpr int K = (DEG + 1) * (DEG + 1);
     const float mx = pk.pos[i], my = pk.pos[n + i], mz = pk.pos[2 * n + i];
@@ -553,25 +855,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) g
         coef[k] = pk.color[(size_t)k * n + i];
     }
 
+    RecRun next = record_run(tile_count, offsets, pk.v[0].p_off + i, in, n_entries);
     for (int vv = 0; vv < pk.nv; ++vv) {
         const GradView& gv = pk.v[vv];
-        const uint32_t pi = gv.p_off + i;
-        const uint32_t cnt = tile_count[pi];
-        if (cnt == 0) continue;
-        const uint32_t e0 = offsets[pi];
-        if ((uint64_t)e0 + cnt > n_entries) continue;
-        float du = 0.0f, dv = 0.0f, dis2 = 0.0f, dop = 0.0f, drgb[3] = {0.0f, 0.0f, 0.0f};
-        for (uint32_t e = e0; e < e0 + cnt; ++e) {
-            const float4 a = rec[2 * (size_t)e];
-            const float4 b = rec[2 * (size_t)e + 1];
-            du += a.x;
-            dv += a.y;
-            dis2 += a.z;
-            dop += a.w;
-            drgb[0] += b.x;
-            drgb[1] += b.y;
-            drgb[2] += b.z;
-        }
+        const RecRun cur = next;
+        if (vv + 1 < pk.nv) next = record_run(tile_count, offsets, pk.v[vv + 1].p_off + i, in, n_entries);
+        float S[8];
+        if (!sum_records<2>(sh, rec, has_rec, cur.e0, cur.cnt, S) || cur.cnt == 0) continue;
+        const float du = S[0], dv = S[1], dis2 = S[2], dop = S[3], drgb[3] = {S[4], S[5], S[6]};
         gop += dop;
         // projection: p = R mu + t, u = f p_x/z + cx, v = f p_y/z + cy, s = f sigma/z, 1/s^2
         const double pxd = (double)gv.R[0] * mx + (double)gv.R[1] * my + (double)gv.R[2] * mz + (double)gv.t[0];
@@ -591,6 +882,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) g
         gmz += gv.R[2] * gpx + gv.R[5] * gpy + gv.R[8] * gpz;
         color_backward<DEG>(CoefRef{coef}, drgb, gv.eye, mx, my, mz, gcol, gmx, gmy, gmz);
     }
+    if (!in) return;
     if (pk.accumulate) {
         pk.g_pos[i] += gmx;
         pk.g_pos[n + i] += gmy;
@@ -644,16 +936,19 @@ __device__ __forceinline__ void quat_rot(double w, double x, double y, double z,
 // (through its normalisation) and the three scales.
 template <int DEG>
 __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGradPack pk, const float4* __restrict__ rec,
+                                                                 const uint8_t* __restrict__ has_rec,
                                                                  const float4* __restrict__ record,
                                                                  const float2* __restrict__ conic,
                                                                  const uint32_t* __restrict__ tile_count,
                                                                  const uint32_t* __restrict__ offsets,
                                                                  const uint32_t* __restrict__ count_p,
                                                                  const int32_t* __restrict__ status) {
+    __shared__ RecShared<kRecVec4<true>> sh;
     if (*status != kStatusOk) return;
     const uint32_t n_entries = *count_p;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= pk.n) return;
+    // threads past the last particle stay for the shared record sums, on the last one's inputs
+    const bool in = blockIdx.x * 256u + threadIdx.x < pk.n;
+    const uint32_t i = min(blockIdx.x * 256u + threadIdx.x, pk.n - 1u);
     const uint32_t n = pk.n;
     constexpr int K = (DEG + 1) * (DEG + 1);
     const float mx = pk.pos[i], my = pk.pos[n + i], mz = pk.pos[2 * n + i];
@@ -689,27 +984,15 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
         coef[k] = pk.color[(size_t)k * n + i];
     }
 
+    RecRun next = record_run(tile_count, offsets, pk.v[0].p_off + i, in, n_entries);
     for (int vv = 0; vv < pk.nv; ++vv) {
         const GradView& gv = pk.v[vv];
         const uint32_t pi = gv.p_off + i;
-        const uint32_t cnt = tile_count[pi];
-        if (cnt == 0) continue;
-        const uint32_t e0 = offsets[pi];
-        if ((uint64_t)e0 + cnt > n_entries) continue;
-        any = true;
+        const RecRun cur = next;
+        if (vv + 1 < pk.nv) next = record_run(tile_count, offsets, pk.v[vv + 1].p_off + i, in, n_entries);
         float S[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) S[k] = 0.0f;
-        for (uint32_t e = e0; e < e0 + cnt; ++e) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const float4 r = rec[3 * (size_t)e + q];
-                S[4 * q] += r.x;
-                S[4 * q + 1] += r.y;
-                S[4 * q + 2] += r.z;
-                S[4 * q + 3] += r.w;
-            }
-        }
+        if (!sum_records<3>(sh, rec, has_rec, cur.e0, cur.cnt, S) || cur.cnt == 0) continue;
+        any = true;
         gop += S[5];
         const double A = (double)record[2 * (size_t)pi].z;
         const float2 bc = conic[pi];
@@ -816,6 +1099,7 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
         gmy += (float)gmu64[1];
         gmz += (float)gmu64[2];
     }
+    if (!in) return;
     if (pk.accumulate) {
         pk.g_pos[i] += gmx;
         pk.g_pos[n + i] += gmy;
@@ -844,7 +1128,7 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
 static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Workspace: gradient records (32 B per entry of capacity, 48 B for the anisotropic
-// family), the tile queue, the chunk item count and the chunk items (two words each; at
+// family) and their marks (1 B per entry), the tile queue, the chunk item count and the chunk items (two words each; at
 // most capacity / kCkptChunk + tiles).
 static size_t bwd_heavy_items(uint64_t capacity, uint32_t tiles) {
     return (size_t)(capacity / kCkptChunk) + tiles + 1;
@@ -854,13 +1138,19 @@ static size_t rec_bytes(bool an) { return an ? 48 : 32; }
 
 size_t render_bwd_ws(uint64_t capacity, const isogs_camera* cams, int32_t nv, bool an) {
     const uint32_t tiles = max_group_tiles(cams, nv);
-    return round256((size_t)capacity * rec_bytes(an)) + round256(tile_queue_words(tiles) * 4) + 256 +
-           bwd_heavy_items(capacity, tiles) * 8 + 256;
+    return round256((size_t)capacity * rec_bytes(an)) + round256((size_t)capacity) +
+           round256(tile_queue_words(tiles) * 4) + 256 + bwd_heavy_items(capacity, tiles) * 8 + 256;
 }
 
 // Reverse compositing of every view into the entry records (both families): chunks of
-// long tiles (with checkpoints), then tiles longest first. Returns the records.
-static float4* launch_composite_bwd(bool an, const int32_t* n_all, const isogs_camera* cams, int32_t nv,
+// long tiles (with checkpoints), then tiles longest first. Returns the records (rec NULL: a
+// launch failed).
+struct BwdRecords {
+    float4* rec;
+    uint8_t* has_rec;
+};
+
+static BwdRecords launch_composite_bwd(bool an, const int32_t* n_all, const isogs_camera* cams, int32_t nv,
                                     const isogs_projected* proj, const float* conic, const isogs_bins* bins,
                                     const float* bg, const float* image, const float* dL_dimage,
                                     const float* T_final, const uint32_t* n_last, const float* ckpt, void* ws,
@@ -869,6 +1159,8 @@ static float4* launch_composite_bwd(bool an, const int32_t* n_all, const isogs_c
     char* base = static_cast<char*>(ws);
     float4* rec = reinterpret_cast<float4*>(base);
     base += round256((size_t)bins->capacity * rec_bytes(an));
+    uint8_t* has_rec = reinterpret_cast<uint8_t*>(base);
+    base += round256((size_t)bins->capacity);
     uint32_t* q = reinterpret_cast<uint32_t*>(base);
     base += round256(tile_queue_words(max_tiles) * 4);
     uint32_t* heavy_count = reinterpret_cast<uint32_t*>(base);
@@ -878,6 +1170,9 @@ static float4* launch_composite_bwd(bool an, const int32_t* n_all, const isogs_c
     // more items than tiles; over ranges that partition the entries, at most
     // capacity / kCkptChunk more in all
     const uint32_t extra_items = ckpt ? (uint32_t)(bins->capacity / kCkptChunk) + 1u : 0u;
+    if (bins->capacity)
+        hipLaunchKernelGGL(clear_marks_kernel, dim3((unsigned)std::min<uint64_t>(2048, (bins->capacity + 4095) / 4096)),
+                           dim3(256), 0, stream, has_rec, bins->count, bins->capacity);
     uint32_t p_off = 0, tile_base = 0, pix_off = 0;
     for (int v0 = 0; v0 < nv; v0 += kMaxViews) {
         const int m = min(kMaxViews, nv - v0);
@@ -890,18 +1185,19 @@ static float4* launch_composite_bwd(bool an, const int32_t* n_all, const isogs_c
         uint32_t* order = launch_tile_queue(q, bins->ranges, tile0, blocks, pk.n_entries_cap, stream);
         if (ckpt) {
             hipLaunchKernelGGL(fill_u32_kernel_b, dim3(1), dim3(64), 0, stream, heavy_count, 1u);
-            hipLaunchKernelGGL(bwd_chunk_list_kernel, dim3((blocks + 255) / 256), dim3(256), 0, stream, bins->ranges,
-                               tile0, blocks, pk.n_entries_cap, bins->status, heavy, heavy_count, heavy_max);
+            hipLaunchKernelGGL(bwd_chunk_list_kernel, dim3((blocks + kReachTiles - 1) / kReachTiles), dim3(256), 0,
+                               stream, pk, bins->ranges, tile0, blocks, n_last, bins->status, heavy, heavy_count,
+                               heavy_max);
         }
         const BwdArgs a{reinterpret_cast<const float4*>(proj->record), reinterpret_cast<const float2*>(conic),
                         bins->pidx, bins->offsets, bins->ranges, bins->status, bg[0], bg[1], bg[2], image, dL_dimage,
-                        T_final, n_last, reinterpret_cast<const float4*>(ckpt), rec, order, q, blocks, heavy,
+                        T_final, n_last, reinterpret_cast<const float4*>(ckpt), rec, has_rec, order, q, blocks, heavy,
                         heavy_count, heavy_max};
         hipLaunchKernelGGL(an ? aniso_bwd_ordered_kernel : composite_bwd_ordered_kernel, dim3(blocks + extra_items),
                            dim3(256), 0, stream, pk, a);
-        if (hipPeekAtLastError() != hipSuccess) return nullptr;
+        if (hipPeekAtLastError() != hipSuccess) return {nullptr, nullptr};
     }
-    return rec;
+    return {rec, has_rec};
 }
 
 // Views grouped by scene (equal position buffers), in view order; calls fn(first view of
@@ -947,9 +1243,9 @@ int launch_render_bwd(const isogs_scene* scenes, const isogs_camera* cams, int32
         pos[v] = scenes[v].pos;
     }
     // 1. reverse compositing
-    const float4* rec = launch_composite_bwd(false, n_all, cams, nv, proj, nullptr, bins, bg, image, dL_dimage, T_final,
+    const BwdRecords br = launch_composite_bwd(false, n_all, cams, nv, proj, nullptr, bins, bg, image, dL_dimage, T_final,
                                              n_last, ckpt, ws, stream);
-    if (!rec) return -1;
+    if (!br.rec) return -1;
     // 2. per scene: reduce records over its views (in view order) and chain to parameters
     int rc = 0;
     for_each_scene(pos, nv, [&](int v, const int* pending, int np) {
@@ -973,10 +1269,10 @@ int launch_render_bwd(const isogs_scene* scenes, const isogs_camera* cams, int32
             if (sc.n > 0) {
                 const dim3 grid((sc.n + 255) / 256);
                 switch (sc.sh_degree) {
-                    case 0: hipLaunchKernelGGL(grad_project_kernel<0>, grid, dim3(256), 0, stream, gp, rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
-                    case 1: hipLaunchKernelGGL(grad_project_kernel<1>, grid, dim3(256), 0, stream, gp, rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
-                    case 2: hipLaunchKernelGGL(grad_project_kernel<2>, grid, dim3(256), 0, stream, gp, rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
-                    default: hipLaunchKernelGGL(grad_project_kernel<3>, grid, dim3(256), 0, stream, gp, rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
+                    case 0: hipLaunchKernelGGL(grad_project_kernel<0>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
+                    case 1: hipLaunchKernelGGL(grad_project_kernel<1>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
+                    case 2: hipLaunchKernelGGL(grad_project_kernel<2>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
+                    default: hipLaunchKernelGGL(grad_project_kernel<3>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, proj->tile_count, bins->offsets, bins->count, bins->status); break;
                 }
             }
             if (hipPeekAtLastError() != hipSuccess) rc = -1;
@@ -1001,9 +1297,9 @@ int launch_aniso_render_bwd(const isogs_aniso_scene* scenes, const isogs_camera*
         o += (uint32_t)scenes[v].n;
         pos[v] = scenes[v].pos;
     }
-    const float4* rec = launch_composite_bwd(true, n_all, cams, nv, &proj->fp, proj->conic, bins, bg, image, dL_dimage,
+    const BwdRecords br = launch_composite_bwd(true, n_all, cams, nv, &proj->fp, proj->conic, bins, bg, image, dL_dimage,
                                              T_final, n_last, ckpt, ws, stream);
-    if (!rec) return -1;
+    if (!br.rec) return -1;
     int rc = 0;
     for_each_scene(pos, nv, [&](int v, const int* pending, int np) {
         const isogs_aniso_scene& sc = scenes[v];
@@ -1031,10 +1327,10 @@ int launch_aniso_render_bwd(const isogs_aniso_scene* scenes, const isogs_camera*
                 const float2* k = reinterpret_cast<const float2*>(proj->conic);
                 const uint32_t* tc = proj->fp.tile_count;
                 switch (sc.sh_degree) {
-                    case 0: hipLaunchKernelGGL(aniso_grad_project_kernel<0>, grid, dim3(256), 0, stream, gp, rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                    case 1: hipLaunchKernelGGL(aniso_grad_project_kernel<1>, grid, dim3(256), 0, stream, gp, rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                    case 2: hipLaunchKernelGGL(aniso_grad_project_kernel<2>, grid, dim3(256), 0, stream, gp, rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                    default: hipLaunchKernelGGL(aniso_grad_project_kernel<3>, grid, dim3(256), 0, stream, gp, rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
+                    case 0: hipLaunchKernelGGL(aniso_grad_project_kernel<0>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
+                    case 1: hipLaunchKernelGGL(aniso_grad_project_kernel<1>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
+                    case 2: hipLaunchKernelGGL(aniso_grad_project_kernel<2>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
+                    default: hipLaunchKernelGGL(aniso_grad_project_kernel<3>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
                 }
             }
             if (hipPeekAtLastError() != hipSuccess) rc = -1;
