@@ -154,9 +154,10 @@ typedef struct {
 int isogs_project(const isogs_scene* scenes, const isogs_camera* cams, int32_t n_views,
                   const isogs_projected* out, void* stream);
 
-/* Bins the footprints into 16x16 tiles and sorts the entries stably by (tile, depth): a
- * device LSD radix sort on the tile id, then a stable sort of every tile's segment on the
- * depth bits; fills tile ranges, per-entry particle indices and, if requested, the keys.
+/* Bins the footprints into 16x16 tiles and sorts the entries stably by (tile, depth): every
+ * entry is placed into its tile's segment, and every segment sorted on (depth bits, packed
+ * particle index), which is the stable order; fills tile ranges, per-entry particle indices
+ * and, if requested, the keys.
  *   n_per_view  host array [V]: particles of each view (the n of its scene)
  *   ws, ws_bytes  workspace; with ws == NULL only *ws_bytes is written (the bytes needed
  *                 for this capacity and these views), and nothing is launched.

@@ -809,7 +809,8 @@ int isogs_bin_sort_static(const isogs_projected* proj, const int32_t* n_per_view
     uint64_t n, tiles;
     if ((rc = check_totals(n_per_view, cams, n_views, &n, &tiles, nullptr))) return rc;
     if (!bins) return fail(ISOGS_ERR_INVALID, "bins is NULL");
-    const isogs::BinSortPlan plan = isogs::plan_bin_sort(n_per_view, cams, n_views, bins->capacity);
+    const isogs::BinSortPlan plan = isogs::plan_bin_sort(n_per_view, cams, n_views, bins->capacity,
+                                                         kStaticScratchBytes);
     if (plan.bytes > kStaticScratchBytes)
         return fail(ISOGS_ERR_WORKSPACE,
                     "isogs_bin_sort_static: %zu bytes of scratch needed for capacity %llu and %llu tiles, "

@@ -1,25 +1,22 @@
 // Binning of footprints into 16x16 tiles and the stable (tile, depth) sort.
 //
-// The sort is split by key part. Entries are emitted in particle order, which is the tie
-// order of the (tile, depth) sort; a stable sort on the tile id alone therefore leaves
-// each tile's entries in emit order, and a stable sort of every tile's segment on depth
-// then yields exactly the stable (tile, depth) order. The global passes rank only the tile
-// bits (ceil(tile bits / 8) passes instead of ceil((tile bits + 31) / 8)), carrying the
-// particle index and the depth bits along so that the per-tile depth sort, which runs in
-// LDS, reads its keys sequentially instead of gathering them.
+// Entries are emitted in particle order, which is the tie order of the (tile, depth) sort, and
+// a particle has at most one entry in a tile: inside a tile the stable depth order is the order
+// of the 64-bit keys (depth bits, packed particle index), whatever order the entries arrive in.
+// So the entries are placed straight into their tile's segment, in any order, and every segment
+// is then sorted on that key; no global radix passes carry the entries through memory.
 //
 // Steps (all on the caller's stream, no host synchronisation):
-//   1. fill        zero tile ranges and counters
-//   2. scan        exclusive scan of per-particle tile counts -> emit offsets, total, status
-//   3. emit        one (tile id, particle index, depth bits) per (particle, member tile)
-//   4. passes      stable LSD radix passes over the tile id, digits of up to 9 bits, each
-//                  as count / scan / scatter kernels; the per-digit scan over the sort tiles
-//                  also yields each digit's total, from which the scatter forms the bases
-//   5. finalize    tile ranges [start, end)
-//   6. segments    stable sort of each tile's segment on the depth bits (and the 64-bit
-//                  (tile, depth) keys, when the caller asks for them): one wave per short
-//                  segment, two, four or eight waves per longer one (several segments to a
-//                  workgroup), the whole workgroup beyond 4096 entries
+//   1. count      a workgroup takes a chunk of a view's particles and counts its entries per
+//                 tile in LDS; the counts are one row of the view's (chunk, tile) matrix
+//   2. columns    per tile, the exclusive prefix over the chunks and the total; 64-tile sums
+//   3. top        scans of the 64-tile sums and of the chunks' entry totals, count, status
+//   4. place      the chunk again: emit offsets, and every entry (key) to its tile's segment at
+//                 the chunk's position in it plus an LDS counter; tile ranges, and the segments
+//                 of more than kSmallMax entries listed by size
+//   5. partition  segments longer than kBigMax: distributed over buckets of the depth range
+//                 until every piece fits the sort of step 6
+//   6. sort       segments and pieces in LDS: one wave, four waves or sixteen waves each
 #include "common.h"
 #include <algorithm>
 
@@ -27,1548 +24,1228 @@
 
 namespace isogs {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
-constexpr int kScanBlock = kScanThreads * kScanItems;   // particles per scan block
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortThreads * kSortItems;    // entries per sort workgroup
-constexpr int kRadixBits = 8;                 // digits of the per-tile depth sorts
-constexpr int kRadix = 1 << kRadixBits;
-constexpr int kTileRadixBits = 9;             // digits of the global tile-id passes
-constexpr int kTileRadix = 1 << kTileRadixBits;
-constexpr int kMaxPasses = 4;                             // tile ids have at most 32 bits
-constexpr int kBigThreads = 512;                          // workgroup of the long-segment sort
-constexpr int kBigWaves = kBigThreads / kWave;
-constexpr int kBigItems = 8;
-constexpr uint32_t kSegMax = kBigThreads * kBigItems;    // longest segment sorted in LDS
+constexpr int kBinThreads = 1024;
+constexpr int kBinWaves = kBinThreads / kWave;
+constexpr uint32_t kColTiles = 64;                      // tiles per column-scan workgroup
+constexpr uint32_t kMaxChunks = 512;                    // rows of a view's matrix at most
+// tiles a workgroup counts at once (one LDS word each): views of up to 1080p, and larger ones
+// (4K has 32400) with one workgroup per CU; a view with more tiles is taken in bands
+constexpr uint32_t kBandSmall = 9216, kBandLarge = 36864;
+constexpr uint32_t kSmallMax = 256;                     // sorted by one wave
+constexpr uint32_t kMidMax = 1024;                      // by four
+constexpr uint32_t kBigMax = 4096;                      // by sixteen
 constexpr uint32_t kCountLimit = (1u << 30) - 1u;       // entries per batch must stay below
+constexpr uint64_t kGroupMaxParticles = 131072;         // calls of up to so many: eight lanes per particle
 
-// Splits the key bits [lo, hi) into the fewest passes of at most `maxw` bits, widths as
-// equal as possible (ballot ranking costs one ballot per digit bit, so no pass ranks unused
-// bits).
-struct DigitSplit {
-    int passes, base, extra, lo;
-    __host__ __device__ DigitSplit(int lo_, int hi_, int maxw = kRadixBits) : lo(lo_) {
-        const int span = hi_ > lo_ ? hi_ - lo_ : 0;
-        passes = (span + maxw - 1) / maxw;
-        base = passes ? span / passes : 0;
-        extra = passes ? span % passes : 0;
-    }
-    __host__ __device__ int width(int p) const { return base + (p < extra ? 1 : 0); }
-    __host__ __device__ int shift(int p) const { return lo + p * base + (p < extra ? p : extra); }
+// A view's place in the binning arrays.
+struct BinView {
+    uint32_t p_off, n;                  // packed particles
+    uint32_t tile_base, tiles;          // global tiles
+    int32_t width, height, tiles_x, tiles_y;
+    uint32_t per, chunks, chunk0;       // particles per chunk, chunks, index of the first
+    uint32_t block0;                    // its first 64-tile block
+    uint64_t m_off;                     // its matrix: [chunks][tiles + 1] counts
 };
 
-// The segment sorts rank fixed 8-bit digits, [lo, lo + 8 passes) covering the differing
-// bits [lo, hi): bits at and above hi are equal within the segment, so ranking them too
-// leaves the order unchanged, and a compile-time width keeps the ballot chain free of
-// per-bit conditions (their masks otherwise take scalar registers the kernel runs short of).
-struct Split8 {
-    int passes, lo;
-    __device__ Split8(int lo_, int hi_) : passes(hi_ > lo_ ? (hi_ - lo_ + kRadixBits - 1) / kRadixBits : 0), lo(lo_) {}
-    __device__ int shift(int p) const { return lo + p * kRadixBits; }
+struct BinPack {
+    int32_t nv;
+    uint32_t view0;                        // index of the launch's first view
+    uint32_t chunk_begin[kMaxViews + 1];   // chunks of earlier views in this launch
+    uint32_t block_begin[kMaxViews + 1];   // column-scan blocks of earlier views
+    uint32_t tile0, tiles;                 // global tiles of the launch
+    BinView v[kMaxViews];
 };
 
-// Digit of key k at (shift, bits).
-__device__ __forceinline__ uint32_t digit_at(uint32_t k, int shift, int bits) {
-    return (k >> shift) & ((1u << bits) - 1u);
+// A piece of a segment (sorted by step 6): its entries, tile and the buffer that holds it
+// (0: the keys, 1: depth bits in the workspace and indices in pidx).
+struct SortItem {
+    uint32_t start, n, tile, buf;
+};
+
+// Counters, one per 128-byte line.
+constexpr uint32_t kLine = 32;
+enum : uint32_t { kNumMid = 0, kNumBig = kLine, kNumLarge = 2 * kLine, kWork = 3 * kLine, kNumMidItems = 4 * kLine,
+                  kNumBigItems = 5 * kLine, kCounterWords = 6 * kLine };
+
+// Device arrays of one call.
+struct BinArrays {
+    uint64_t* key;          // [capacity] (depth bits << 32) | packed particle index, by tile
+    uint32_t* z_alt;        // [capacity] the other buffer's depth bits (its indices are in pidx)
+    uint2* box;             // [N] tile boxes of step 1 for step 4, or NULL
+    uint32_t* m;            // the (chunk, tile) matrices
+    uint32_t* tile_pre;     // [T] entries of the 64-tile block's earlier tiles
+    uint32_t* tile_tot;     // [T]
+    uint32_t* missing;      // [views] entries without a tile
+    uint32_t* missing_at;   // [views] and their first position
+    uint32_t* block_sum;    // [64-tile blocks], scanned by step 3
+    uint64_t* chunk_sum;    // [chunks], scanned by step 3
+    uint32_t* counters;
+    uint32_t *mid, *big;    // tiles listed by segment length
+    SortItem *large, *mid_item, *big_item;
+    uint2* stack;           // pending ranges of step 5: slots start / 4096 .. of each segment
+    uint32_t list_max, large_max, item_max;
+    uint32_t blocks, chunks, views;
+};
+
+// Inclusive scan over the 64 lanes of a wave: DPP shifts inside the four 16-lane rows, then the
+// totals of the earlier rows as scalars (shuffles through LDS cost a round trip per step).
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15), r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31),
+                   r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
+    const uint32_t row = lane_id() >> 4;
+    return x + (row == 0 ? 0u : row == 1 ? r0 : row == 2 ? r0 + r1 : r0 + r1 + r2);
 }
 
-// Inclusive scan over the 64 lanes of a wave.
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+__device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t x) {
     const int lane = (int)lane_id();
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, kWave);
+        const uint64_t y = __shfl_up(x, o, kWave);
         if (lane >= o) x += y;
     }
     return x;
 }
 
+// Largest value of the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true));
+    return max(max((uint32_t)__builtin_amdgcn_readlane((int)x, 15), (uint32_t)__builtin_amdgcn_readlane((int)x, 31)),
+               max((uint32_t)__builtin_amdgcn_readlane((int)x, 47), (uint32_t)__builtin_amdgcn_readlane((int)x, 63)));
+}
+
 // Exclusive scan over a block of NW waves; s_tmp holds NW words. Returns the block total
 // in `total`. Contains __syncthreads.
-template <int NW = 4>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* s_tmp, uint32_t& total) {
+template <int NW, typename T>
+__device__ __forceinline__ T block_exclusive_scan(T x, T* s_tmp, T& total) {
     const uint32_t w = threadIdx.x >> 6;
-    const uint32_t inc = wave_inclusive_scan(x);
+    const T inc = wave_inclusive_scan(x);
     if (lane_id() == kWave - 1) s_tmp[w] = inc;
     __syncthreads();
-    uint32_t before = 0;
+    T before = 0;
     total = 0;
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
-        before += ((uint32_t)j < w) ? s_tmp[j] : 0u;
+        before += ((uint32_t)j < w) ? s_tmp[j] : (T)0;
         total += s_tmp[j];
     }
     __syncthreads();
     return before + inc - x;
 }
 
-__global__ void __launch_bounds__(256) fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t value) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = value;
+// ---- Tile boxes -----------------------------------------------------------------------------
+
+// The candidate tiles of a particle, row-major cells of a w x h box.
+struct TileBox {
+    float u, v, r2, w_lim, h_lim;
+    int tx0, ty0, w, h;
+    __device__ bool member(int cx, int cy) const { return tile_member(u, v, r2, tx0 + cx, ty0 + cy, w_lim, h_lim); }
+};
+
+// What a particle's box is made of.
+struct BoxLoad {
+    float u, v, r;
+};
+__device__ __forceinline__ BoxLoad load_footprint(const float4* __restrict__ record, uint32_t i) {
+    const float2 uv = *reinterpret_cast<const float2*>(record + 2 * (size_t)i);
+    return {uv.x, uv.y, record[2 * (size_t)i + 1].w};
 }
 
-// Step 2a: per-block sums of tile counts.
-__global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(const uint32_t* __restrict__ cnt, uint32_t n,
-                                                                   uint32_t* __restrict__ block_sums) {
-    __shared__ uint32_t s_tmp[4];
-    const uint32_t base = blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
-    uint32_t acc = 0;
-    if (base + kScanItems <= n && (reinterpret_cast<uintptr_t>(cnt) & 15u) == 0) {
-        const uint4 a = *reinterpret_cast<const uint4*>(cnt + base);
-        const uint4 b = *reinterpret_cast<const uint4*>(cnt + base + 4);
-        acc = a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
-    } else {
+__device__ __forceinline__ TileBox make_box(const BinView& vd, const BoxLoad& l) {
+    const float r = l.r;
+    TileBox b;
+    b.u = l.u;
+    b.v = l.v;
+    b.r2 = r * r;
+    b.w_lim = (float)vd.width - 0.5f;
+    b.h_lim = (float)vd.height - 0.5f;
+    int tx1, ty1;
+    tile_box(l.u, l.v, r, vd.tiles_x, vd.tiles_y, b.tx0, tx1, b.ty0, ty1);
+    b.w = max(0, tx1 - b.tx0 + 1);
+    b.h = max(0, ty1 - b.ty0 + 1);
+    if (b.w == 0 || b.h == 0) b.w = b.h = 0;
+    return b;
+}
+
+// A box of at most 4 x 4 cells with its members as a bit mask (bit 4 y + x), in 8 bytes: step 4
+// then reads 8 bytes of a particle instead of its 32-byte record, and visits members only. The
+// squared offsets of four columns and four rows are formed once, so that a wave does not go
+// through as many turns as its largest box has cells. Any other box (larger, a tile coordinate
+// of 4096 or more, a tile count other than its members') is marked and walked again.
+constexpr uint32_t kBoxWalk = 0x80000000u;
+__device__ __forceinline__ uint32_t box_mask4(const TileBox& b) {
+    float dxx[4], dyy[4];
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) acc += (base + k < n) ? cnt[base + k] : 0u;
+    for (int q = 0; q < 4; ++q) {   // (tile_member's arithmetic)
+        const float x0 = (float)((b.tx0 + q) * kTile), y0 = (float)((b.ty0 + q) * kTile);
+        const float dx = fmaxf(fmaxf(x0 + 0.5f - b.u, b.u - fminf(x0 + 15.5f, b.w_lim)), 0.0f);
+        const float dy = fmaxf(fmaxf(y0 + 0.5f - b.v, b.v - fminf(y0 + 15.5f, b.h_lim)), 0.0f);
+        dxx[q] = dx * dx;
+        dyy[q] = dy * dy;
     }
-    uint32_t total;
-    block_exclusive_scan(acc, s_tmp, total);
-    if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
+    uint32_t mask = 0;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) mask |= (dxx[c & 3] + dyy[c >> 2] <= b.r2 ? 1u : 0u) << c;
+    // cells of the box only
+    return mask & ((1u << min(b.w, 4)) - 1u) * 0x1111u & ((1u << 4 * min(b.h, 4)) - 1u);
 }
 
-// Step 2b: exclusive scan of the block sums (one workgroup), total and capacity status.
-// Each thread takes a run of consecutive sums, so one workgroup scan covers up to
-// kScanThreads * kTopItems of them at a time (a 10-view call of 1M particles has about 5000).
-constexpr uint32_t kTopItems = 32;
-__global__ void __launch_bounds__(kScanThreads) scan_top_kernel(uint32_t* __restrict__ block_sums, uint32_t nb,
-                                                                uint64_t capacity, uint32_t* __restrict__ count,
-                                                                int32_t* __restrict__ status) {
-    __shared__ uint32_t s_tmp[4];
-    uint64_t carry = 0;
-    for (uint32_t b0 = 0; b0 < nb; b0 += kScanThreads * kTopItems) {
-        const uint32_t per = (min(nb - b0, kScanThreads * kTopItems) + kScanThreads - 1) / kScanThreads;
-        const uint32_t i0 = b0 + threadIdx.x * per, i1 = min(i0 + per, nb);
-        uint32_t sum = 0;
-        for (uint32_t i = i0; i < i1; ++i) sum += block_sums[i];
-        uint32_t total;
-        uint64_t run = carry + block_exclusive_scan(sum, s_tmp, total);
-        for (uint32_t i = i0; i < i1; ++i) {
-            const uint32_t x = block_sums[i];
-            block_sums[i] = (uint32_t)run;
-            run += x;
-        }
-        carry += total;
+// Calls put(tile of the view) for the members of a mask whose cell 0 is tile `first`.
+template <typename Fn>
+__device__ __forceinline__ void put_mask4(uint32_t mask, uint32_t first, uint32_t tiles_x, Fn put) {
+    while (mask) {
+        const uint32_t c = (uint32_t)__ffs((int)mask) - 1u;
+        mask &= mask - 1u;
+        put(first + (c >> 2) * tiles_x + (c & 3u));
     }
+}
+
+// Calls put(tile of the view) for the first `want` members of a box of any size, by the group
+// of G lanes (lane j of it) that holds the particle. Returns their number in every lane.
+template <int G, typename Fn>
+__device__ __forceinline__ uint32_t walk_box(const BinView& vd, const TileBox& b, uint32_t want, uint32_t j, Fn put) {
+    uint32_t n = 0;
+    if (G > 1) {
+        // count together, then place together; a count below the members (the tile count came
+        // from elsewhere) is placed by the first lane alone, in order
+        const uint32_t cells = (uint32_t)(b.w * b.h);
+        int cx = (int)j, cy = 0;
+        for (uint32_t c = j; c < cells; c += G, cx += G) {
+            while (cx >= b.w) {
+                cx -= b.w;
+                ++cy;
+            }
+            n += b.member(cx, cy) ? 1u : 0u;
+        }
+#pragma unroll
+        for (int o = 1; o < G; o <<= 1) n += __shfl_xor(n, o, kWave);
+        if (n <= want) {
+            cx = (int)j;
+            cy = 0;
+            for (uint32_t c = j; c < cells; c += G, cx += G) {
+                while (cx >= b.w) {
+                    cx -= b.w;
+                    ++cy;
+                }
+                if (b.member(cx, cy)) put((uint32_t)((b.ty0 + cy) * vd.tiles_x + b.tx0 + cx));
+            }
+            return n;
+        }
+        if (j != 0) return want;
+        n = 0;
+    }
+    for (int y = 0; y < b.h && n < want; ++y)
+        for (int x = 0; x < b.w && n < want; ++x)
+            if (b.member(x, y)) {
+                ++n;
+                put((uint32_t)((b.ty0 + y) * vd.tiles_x + b.tx0 + x));
+            }
+    return n;
+}
+
+// Members of a box up to `want`, counted by one lane.
+__device__ __forceinline__ uint32_t count_members(const TileBox& b, uint32_t want) {
+    uint32_t n = 0;
+    for (int y = 0; y < b.h && n < want; ++y)
+        for (int x = 0; x < b.w && n < want; ++x) n += b.member(x, y) ? 1u : 0u;
+    return n;
+}
+
+__device__ __forceinline__ int view_of_chunk(const BinPack& pk, uint32_t b) {
+    int v = 0;
+    for (int i = 1; i < pk.nv; ++i) v = (b >= pk.chunk_begin[i]) ? i : v;
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Step 1. A particle has no more entries than its tile count says; missing ones (the count may
+// come from elsewhere) belong to no tile and go behind all others. G lanes share a particle
+// (small scenes: few particles, large boxes), blockIdx.y is the band of tiles. Bound by the
+// records' bytes and the walk over the box.
+template <uint32_t BT, int G>
+__global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk, const float4* __restrict__ record,
+                                                                const uint32_t* __restrict__ tile_count,
+                                                                const BinArrays A) {
+    __shared__ uint32_t s_h[BT];
+    __shared__ unsigned long long s_sum;
+    __shared__ uint32_t s_miss;
+    const uint32_t t = threadIdx.x, j = t % G;
+    const int vi = view_of_chunk(pk, blockIdx.x);
+    const BinView& vd = pk.v[vi];
+    const uint32_t row = blockIdx.x - pk.chunk_begin[vi], t0 = blockIdx.y * BT;
+    if (t0 >= vd.tiles && blockIdx.y) return;   // (uniform) fewer bands than the launch's largest view
+    const uint32_t nt = min(BT, vd.tiles - t0);
+    for (uint32_t q = t; q < nt; q += kBinThreads) s_h[q] = 0u;
+    if (t == 0) {
+        s_sum = 0;
+        s_miss = 0;
+    }
+    __syncthreads();
+    const uint32_t c0 = row * vd.per, c1 = min(vd.n, c0 + vd.per);
+    unsigned long long sum = 0;
+    uint32_t miss = 0;
+    // the next particle is loaded while this one is walked (past the end: the last one again)
+    const uint32_t last = vd.p_off + max(c1, 1u) - 1u, first = vd.p_off + c0 + t / G;
+    BoxLoad next_box{0.0f, 0.0f, 0.0f};
+    uint32_t next_want = 0;
+    if (c0 < c1) {
+        next_box = load_footprint(record, min(first, last));
+        next_want = tile_count[min(first, last)];
+    }
+    for (uint32_t q = c0; q < c1; q += kBinThreads / G) {
+        const uint32_t i = q + t / G, g = vd.p_off + i;
+        const BoxLoad load = next_box;
+        const uint32_t want = i < c1 ? next_want : 0u;
+        next_box = load_footprint(record, min(g + kBinThreads / G, last));
+        next_want = tile_count[min(g + kBinThreads / G, last)];
+        if (!want) continue;   // whole groups
+        const TileBox b = make_box(vd, load);
+        auto put = [&](uint32_t tile) {
+            if (tile - t0 < nt) atomicAdd(&s_h[tile - t0], 1u);
+        };
+        uint2 packed = make_uint2(0u, kBoxWalk);
+        uint32_t n;
+        const uint32_t mask = b.w <= 4 && b.h <= 4 ? box_mask4(b) : 0u;
+        if ((uint32_t)__popc(mask) == want && (b.tx0 | b.ty0) < 4096) {
+            n = want;
+            packed = make_uint2(mask, (uint32_t)b.tx0 | (uint32_t)b.ty0 << 12);
+            if (j == 0) put_mask4(mask, (uint32_t)(b.ty0 * vd.tiles_x + b.tx0), (uint32_t)vd.tiles_x, put);
+        } else {
+            n = walk_box<G>(vd, b, want, j, put);
+        }
+        if (j == 0) {
+            sum += want;
+            miss += want - n;
+            if (A.box && blockIdx.y == 0) A.box[g] = packed;
+        }
+    }
+    if (blockIdx.y == 0 && sum) {
+        atomicAdd(&s_sum, sum);
+        if (miss) atomicAdd(&s_miss, miss);
+    }
+    __syncthreads();
+    uint32_t* m = A.m + vd.m_off + (size_t)row * (vd.tiles + 1);
+    for (uint32_t q = t; q < nt; q += kBinThreads) m[t0 + q] = s_h[q];
+    if (t == 0 && blockIdx.y == 0) {
+        m[vd.tiles] = s_miss;
+        A.chunk_sum[vd.chunk0 + row] = s_sum;
+    }
+}
+
+// Step 2: 64 columns (tiles; the last column of a view holds the entries without a tile) per
+// workgroup, a wave per run of up to kMaxChunks / 16 rows held in registers.
+__global__ void __launch_bounds__(kBinThreads) bin_columns_kernel(const BinPack pk, const BinArrays A) {
+    __shared__ uint32_t s_part[kBinWaves][kColTiles];
+    constexpr uint32_t kRows = kMaxChunks / kBinWaves;
+    int v = 0;
+    for (int i = 1; i < pk.nv; ++i) v = (blockIdx.x >= pk.block_begin[i]) ? i : v;
+    v = __builtin_amdgcn_readfirstlane(v);
+    const BinView& vd = pk.v[v];
+    const uint32_t w = threadIdx.x >> 6, l = lane_id();
+    const uint32_t block = blockIdx.x - pk.block_begin[v], col = block * kColTiles + l;
+    const uint32_t rows = (vd.chunks + kBinWaves - 1) / kBinWaves, r0 = w * rows;
+    uint32_t* m = A.m + vd.m_off + col;
+    const size_t pitch = vd.tiles + 1;
+    const bool on = col <= vd.tiles;
+    uint32_t x[kRows], sum = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kRows; ++r) x[r] = on && r < rows && r0 + r < vd.chunks ? m[(r0 + r) * pitch] : 0u;
+#pragma unroll
+    for (uint32_t r = 0; r < kRows; ++r) sum += x[r];
+    s_part[w][l] = sum;
+    __syncthreads();
+    uint32_t run = 0, total = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < (uint32_t)kBinWaves; ++q) {
+        const uint32_t y = s_part[q][l];
+        run += q < w ? y : 0u;
+        total += y;
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kRows; ++r) {
+        if (on && r < rows && r0 + r < vd.chunks) m[(r0 + r) * pitch] = run;
+        run += x[r];
+    }
+    if (w != 0) return;
+    const uint32_t mine = col < vd.tiles ? total : 0u;
+    const uint32_t incl = wave_inclusive_scan(mine);
+    if (col < vd.tiles) {
+        A.tile_pre[vd.tile_base + col] = incl - mine;
+        A.tile_tot[vd.tile_base + col] = total;
+    }
+    if (col == vd.tiles) A.missing[pk.view0 + v] = total;
+    if (l == kWave - 1) A.block_sum[vd.block0 + block] = incl;
+}
+
+// Exclusive scan of v[0, n) (values T) by one workgroup, in place or into `out`, starting
+// from `base`; returns base plus the total. Contains __syncthreads.
+template <typename T, typename O>
+__device__ __forceinline__ uint64_t scan_array(const T* v, O* out, uint32_t n, uint64_t base, uint64_t* s_tmp) {
+    const uint32_t per = (n + kBinThreads - 1) / kBinThreads;
+    const uint32_t i0 = min(n, threadIdx.x * per), i1 = min(n, i0 + per);
+    uint64_t sum = 0;
+    for (uint32_t i = i0; i < i1; ++i) sum += v[i];
+    uint64_t total;
+    uint64_t run = base + block_exclusive_scan<kBinWaves, uint64_t>(sum, s_tmp, total);
+    for (uint32_t i = i0; i < i1; ++i) {
+        const T x = v[i];
+        out[i] = (O)run;
+        run += x;
+    }
+    return base + total;
+}
+
+// Step 3: one workgroup.
+__global__ void __launch_bounds__(kBinThreads) bin_top_kernel(const BinArrays A, uint64_t capacity,
+                                                              uint32_t* __restrict__ count,
+                                                              int32_t* __restrict__ status) {
+    __shared__ uint64_t s_tmp[kBinWaves];
+    if (threadIdx.x < kCounterWords) A.counters[threadIdx.x] = 0u;
+    const uint64_t in_tiles = scan_array(A.block_sum, A.block_sum, A.blocks, 0, s_tmp);
+    scan_array(A.missing, A.missing_at, A.views, in_tiles, s_tmp);
+    const uint64_t total = scan_array(A.chunk_sum, A.chunk_sum, A.chunks, 0, s_tmp);
     if (threadIdx.x == 0) {
-        const bool fits = carry <= capacity && carry < (uint64_t)kCountLimit;
-        *count = (uint32_t)(carry > 0xFFFFFFFFull ? 0xFFFFFFFFull : carry);
+        const bool fits = total <= capacity && total < (uint64_t)kCountLimit;
+        *count = (uint32_t)(total > 0xFFFFFFFFull ? 0xFFFFFFFFull : total);
         *status = fits ? kStatusOk : kStatusCapacity;
     }
 }
 
-// Step 2c: emit offsets = block prefix + in-block exclusive scan.
-__global__ void __launch_bounds__(kScanThreads) scan_down_kernel(const uint32_t* __restrict__ cnt, uint32_t n,
-                                                                 const uint32_t* __restrict__ block_prefix,
-                                                                 uint32_t* __restrict__ offsets) {
-    __shared__ uint32_t s_tmp[4];
-    // each thread scans kScanItems consecutive particles (blocked), lanes then threads; whole
-    // runs move as two 16-byte loads and stores when both arrays allow it
-    static_assert(kScanItems == 8, "two 16-byte vectors per thread");
-    const uint32_t base = blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
-    const bool vec = base + kScanItems <= n && ((reinterpret_cast<uintptr_t>(cnt) | reinterpret_cast<uintptr_t>(offsets)) & 15u) == 0;
-    uint32_t v[kScanItems];
-    if (vec) {
-        const uint4 a = *reinterpret_cast<const uint4*>(cnt + base);
-        const uint4 b = *reinterpret_cast<const uint4*>(cnt + base + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-        for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? cnt[base + k] : 0u;
+__device__ __forceinline__ uint32_t tile_start(const BinArrays& A, const BinView& vd, uint32_t tile) {
+    return A.block_sum[vd.block0 + tile / kColTiles] + A.tile_pre[vd.tile_base + tile];
+}
+
+// Tile ranges of 1024 tiles, and the lists of those with more than kSmallMax entries (one
+// device-wide add per workgroup and list). Contains __syncthreads.
+__device__ __forceinline__ void bin_ranges(const BinPack& pk, const BinArrays& A, uint32_t block, bool ok,
+                                           uint32_t* __restrict__ ranges) {
+    __shared__ uint32_t s_n[3], s_at[3];
+    const uint32_t t = threadIdx.x, i = block * kBinThreads + t;
+    if (t < 3) s_n[t] = 0;
+    __syncthreads();
+    uint32_t start = 0, n = 0;
+    if (i < pk.tiles && ok) {
+        int v = 0;
+        for (int q = 1; q < pk.nv; ++q) v = pk.tile0 + i >= pk.v[q].tile_base ? q : v;
+        const BinView& vd = pk.v[v];
+        n = A.tile_tot[pk.tile0 + i];
+        start = n ? tile_start(A, vd, pk.tile0 + i - vd.tile_base) : 0u;
     }
-    uint32_t acc = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) acc += v[k];
-    uint32_t total;
-    const uint32_t run = block_exclusive_scan(acc, s_tmp, total) + block_prefix[blockIdx.x];
-    uint32_t o[kScanItems];
-    o[0] = run;
-#pragma unroll
-    for (int k = 1; k < kScanItems; ++k) o[k] = o[k - 1] + v[k - 1];
-    if (vec) {
-        *reinterpret_cast<uint4*>(offsets + base) = make_uint4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<uint4*>(offsets + base + 4) = make_uint4(o[4], o[5], o[6], o[7]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < kScanItems; ++k)
-            if (base + k < n) offsets[base + k] = o[k];
+    if (i < pk.tiles) {
+        ranges[2 * (size_t)(pk.tile0 + i)] = start;
+        ranges[2 * (size_t)(pk.tile0 + i) + 1] = start + n;
+    }
+    const uint32_t c = n <= kSmallMax ? 3u : n <= kMidMax ? 0u : n <= kBigMax ? 1u : 2u;
+    uint32_t at = 0;
+    if (c < 3u) at = atomicAdd(&s_n[c], 1u);
+    __syncthreads();
+    if (t < 3 && s_n[t]) s_at[t] = atomicAdd(&A.counters[t * kLine], s_n[t]);
+    __syncthreads();
+    if (c >= 3u) return;
+    at += s_at[c];
+    if (at >= (c == 2u ? A.large_max : A.list_max)) return;   // (the bound on tiles with so many entries)
+    if (c == 0u) A.mid[at] = pk.tile0 + i;
+    if (c == 1u) A.big[at] = pk.tile0 + i;
+    if (c == 2u) A.large[at] = SortItem{start, n, pk.tile0 + i, 0u};
+}
+
+// Step 4. Workgroups past the chunks write tile ranges. The key writes are scattered: a chunk
+// has a few entries for each of thousands of tiles, so they are bound by the caches' handling
+// of partial lines rather than by bytes.
+template <uint32_t BT, int G>
+__global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_eu(BT == kBandSmall ? 8 : 4))) bin_place_kernel(const BinPack pk, const float4* __restrict__ record,
+                                                                const float* __restrict__ depth,
+                                                                const uint32_t* __restrict__ tile_count,
+                                                                const BinArrays A, const int32_t* __restrict__ status,
+                                                                const uint32_t* __restrict__ count_p,
+                                                                uint32_t* __restrict__ ranges,
+                                                                uint32_t* __restrict__ offsets,
+                                                                uint32_t* __restrict__ pidx) {
+    __shared__ uint32_t s_c[BT];
+    __shared__ uint32_t s_tmp[kBinWaves];
+    const uint32_t t = threadIdx.x, j = t % G;
+    const bool ok = *status == kStatusOk;
+    if (blockIdx.x >= pk.chunk_begin[pk.nv]) {
+        if (blockIdx.y == 0) bin_ranges(pk, A, blockIdx.x - pk.chunk_begin[pk.nv], ok, ranges);
+        return;
+    }
+    const int vi = view_of_chunk(pk, blockIdx.x);
+    const BinView& vd = pk.v[vi];
+    const uint32_t row = blockIdx.x - pk.chunk_begin[vi], t0 = blockIdx.y * BT;
+    if (t0 >= vd.tiles && blockIdx.y) return;
+    const uint32_t nt = min(BT, vd.tiles - t0), count = *count_p;
+    const uint32_t* m = A.m + vd.m_off + (size_t)row * (vd.tiles + 1);
+    if (ok)
+        for (uint32_t q = t; q < nt; q += kBinThreads) s_c[q] = tile_start(A, vd, t0 + q) + m[t0 + q];
+    const uint32_t c0 = row * vd.per, c1 = min(vd.n, c0 + vd.per);
+    if (blockIdx.y == 0) {
+        // emit offsets, and the entries without a tile (emit order)
+        const uint32_t n_missing = ok ? m[vd.tiles] : 0u;   // (of earlier chunks: a prefix)
+        const bool any_missing = ok && A.missing[pk.view0 + vi] != 0u;
+        uint32_t run = (uint32_t)A.chunk_sum[vd.chunk0 + row];
+        uint32_t at = any_missing ? A.missing_at[pk.view0 + vi] + n_missing : 0u;
+        for (uint32_t q = c0; q < c1; q += kBinThreads) {
+            const uint32_t i = q + t, want = i < c1 ? tile_count[vd.p_off + i] : 0u;
+            uint32_t total;
+            const uint32_t o = run + block_exclusive_scan<kBinWaves, uint32_t>(want, s_tmp, total);
+            if (i < c1) offsets[vd.p_off + i] = o;
+            run += total;
+            if (!any_missing) continue;   // uniform
+            const uint32_t miss =
+                want ? want - count_members(make_box(vd, load_footprint(record, vd.p_off + i)), want) : 0u;
+            const uint32_t p = at + block_exclusive_scan<kBinWaves, uint32_t>(miss, s_tmp, total);
+            for (uint32_t k = 0; k < miss && p + k < count; ++k) pidx[p + k] = vd.p_off + i;
+            at += total;
+        }
+    }
+    if (!ok || c0 >= c1) return;
+    __syncthreads();
+    const uint32_t last = vd.p_off + c1 - 1u, first = min(vd.p_off + c0 + t / G, last);
+    uint32_t next_want = tile_count[first], next_z = __float_as_uint(depth[first]);
+    uint2 next_box = A.box ? A.box[first] : make_uint2(0u, kBoxWalk);
+    for (uint32_t q = c0; q < c1; q += kBinThreads / G) {
+        const uint32_t i = q + t / G, g = vd.p_off + i, ahead = min(g + kBinThreads / G, last);
+        const uint32_t want = i < c1 ? next_want : 0u;
+        const uint64_t key = (uint64_t)next_z << 32 | g;
+        const uint2 b = next_box;
+        next_want = tile_count[ahead];
+        next_z = __float_as_uint(depth[ahead]);
+        if (A.box) next_box = A.box[ahead];
+        if (!want) continue;
+        auto put = [&](uint32_t tile) {
+            if (tile - t0 >= nt) return;
+            const uint32_t p = atomicAdd(&s_c[tile - t0], 1u);
+            if (p < count) A.key[p] = key;
+        };
+        if (b.y & kBoxWalk)
+            walk_box<G>(vd, make_box(vd, load_footprint(record, g)), want, j, put);
+        else if (j == 0)
+            put_mask4(b.x, (b.y >> 12) * (uint32_t)vd.tiles_x + (b.y & 0xFFFu), (uint32_t)vd.tiles_x, put);
     }
 }
 
+// ---- Sorting in LDS ---------------------------------------------------------------------------
 
-// Step 3: one entry per (particle, member tile); entries of a particle are consecutive
-// from its offset, tiles in row-major order. A particle writes no more entries than its
-// tile count says (the count may come from elsewhere; here it is the difference of
-// consecutive offsets, which the scan made from those counts, the last one's from the
-// total); missing ones get the sentinel id 0xFFFFFFFF, which sorts last and belongs to no
-// tile. One workgroup per chunk of 256 particles of a view. The chunk's entries are one
-// run of the output; when it holds at most kEmitStage entries they are gathered in LDS
-// (tile id and owner) and written as whole runs, else each particle writes its own.
-constexpr uint32_t kEmitStage = 2048;
+// Where a piece is read from.
+struct SortSource {
+    const uint64_t* key;
+    const uint32_t* z_alt;
+    uint32_t buf;
+    __device__ uint64_t at(uint32_t p, const uint32_t* pidx) const {
+        return buf ? (uint64_t)z_alt[p] << 32 | pidx[p] : key[p];
+    }
+};
 
-__global__ void __launch_bounds__(256) emit_kernel(const ViewPack pk, const float4* __restrict__ record,
-                                                   const uint32_t* __restrict__ offsets, uint32_t n_total,
-                                                   const float* __restrict__ depth,
-                                                   const uint32_t* __restrict__ count_p, uint64_t capacity,
-                                                   uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                   uint32_t* __restrict__ zbits) {
-    __shared__ uint32_t s_key[kEmitStage];
-    __shared__ uint8_t s_own[kEmitStage];
-    __shared__ uint32_t s_z[256];
-    const uint32_t count = *count_p;
-    if ((uint64_t)count > capacity) return;
-    const uint32_t c = blockIdx.x;
-    const int vi = view_of_block(pk, c);
-    const ViewDesc& vd = pk.v[vi];
-    const uint32_t first = vd.p_off + (c - pk.block_begin[vi]) * 256u;
-    const uint32_t last = min(first + 255u, vd.p_off + vd.n - 1u);
-    // the chunk's run [E0, E1), uniform over the workgroup
-    const uint32_t E0 = offsets[first];
-    const uint32_t E1 = last + 1 < n_total ? offsets[last + 1] : count;
-    const bool staged = E1 >= E0 && E1 <= count && E1 - E0 <= kEmitStage;
-    const uint32_t i = first + threadIdx.x;
-    uint32_t e0 = 0, want = 0;
-    if (i <= last) {
-        e0 = offsets[i];
-        want = (i + 1 < n_total ? offsets[i + 1] : count) - e0;
-        if ((uint64_t)e0 + want > count) want = 0;
+// Buckets: a monotone map of the depth bits (of the index where all depths are equal) from
+// their range [lo, hi] to [0, nb): nb equal parts of the range.
+struct BucketMap {
+    uint32_t lo, nb;
+    bool by_index;
+    float scale;
+    __device__ BucketMap(uint32_t lo_, uint32_t hi, bool by_index_, uint32_t nb_) : lo(lo_), nb(nb_), by_index(by_index_) {
+        scale = (float)nb / ((float)(hi - lo) + 1.0f);
     }
-    uint32_t z = 0;
-    int tx0 = 0, tx1 = -1, ty0 = 0, ty1 = -1;
-    float fx = 0.f, fy = 0.f, r2 = 0.f;
-    if (want) {
-        const float4 fp = record[2 * (size_t)i];
-        const float r = record[2 * (size_t)i + 1].w;
-        z = __float_as_uint(depth[i]);
-        fx = fp.x;
-        fy = fp.y;
-        r2 = r * r;
-        tile_box(fp.x, fp.y, r, vd.tiles_x, vd.tiles_y, tx0, tx1, ty0, ty1);
+    // position in units of buckets, and the bucket of a position
+    __device__ float at(uint64_t k) const { return (float)((by_index ? (uint32_t)k : (uint32_t)(k >> 32)) - lo) * scale; }
+    __device__ uint32_t bucket(float v) const { return min((uint32_t)v, nb - 1u); }
+    __device__ uint32_t of(uint64_t k) const { return bucket(at(k)); }
+};
+
+// Sorted by THREADS threads (a wave, or the workgroup): up to THREADS * ITEMS entries. Entries
+// are counted in 4 THREADS equal parts of the depth range; a part that holds c of them, the
+// entries [base, base + c), is divided again into c buckets (the parts' counts are a
+// piecewise linear distribution function, and every bucket takes an equal share of it: the
+// depths of a tile lie in a few dense surfaces and clusters, and equal buckets of the range
+// alone left dozens of entries in some). The buckets are counted and scanned, the entries stored
+// by bucket, and an entry's rank inside its bucket is the number of smaller keys there, usually
+// one or two reads. Six LDS round trips whatever the key width, where ranking three 8-bit digits by
+// ballots took about 35 instructions per digit and entry. Where a bucket holds more than
+// kBucketMax (many equal depths) the keys go through a bitonic network instead.
+constexpr uint32_t kBucketMax = 64;
+
+template <int THREADS, int ITEMS>
+struct __align__(16) SortShared {
+    union {
+        uint64_t key[THREADS * ITEMS];
+        uint32_t part[THREADS * 4 + 4];   // before the entries are stored
+    };
+    uint32_t base[THREADS * ITEMS + 4];
+    uint32_t red[2][THREADS / kWave];
+    uint32_t tmp[THREADS / kWave];
+    uint32_t most[THREADS / kWave];
+};
+
+template <int THREADS>
+__device__ __forceinline__ void group_sync() {
+    if (THREADS == kWave)
+        __builtin_amdgcn_wave_barrier();   // LDS operations of one wave complete in order
+    else
+        __syncthreads();
+}
+
+// Smallest and largest x over the group, in every thread. Contains group_sync.
+template <int THREADS>
+__device__ __forceinline__ void group_range(uint32_t& lo, uint32_t& hi, uint32_t (*red)[THREADS / kWave]) {
+    constexpr int kW = THREADS / kWave;
+    lo = ~wave_max(~lo);
+    hi = wave_max(hi);
+    if (kW == 1) return;
+    if (lane_id() == 0) {
+        red[0][threadIdx.x >> 6] = lo;
+        red[1][threadIdx.x >> 6] = hi;
     }
-    const float w_lim = (float)vd.width - 0.5f, h_lim = (float)vd.height - 0.5f;
-    if (!staged) {
-        uint32_t j = 0;
-        for (int ty = ty0; ty <= ty1 && j < want; ++ty) {
-            for (int tx = tx0; tx <= tx1 && j < want; ++tx) {
-                if (!tile_member(fx, fy, r2, tx, ty, w_lim, h_lim)) continue;
-                const uint32_t e = e0 + j++;
-                keys[e] = vd.tile_base + (uint32_t)(ty * vd.tiles_x + tx);
-                vals[e] = i;
-                zbits[e] = z;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kW; ++q) {
+        lo = min(lo, red[0][q]);
+        hi = max(hi, red[1][q]);
+    }
+}
+
+// Exclusive scan of x over the group's threads. Contains group_sync.
+template <int THREADS>
+__device__ __forceinline__ uint32_t group_exclusive_scan(uint32_t x, uint32_t* tmp) {
+    uint32_t incl = wave_inclusive_scan(x);
+    if (THREADS > kWave) {
+        const uint32_t w = threadIdx.x >> 6;
+        if (lane_id() == kWave - 1) tmp[w] = incl;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < THREADS / kWave; ++q) incl += (uint32_t)q < w ? tmp[q] : 0u;
+    }
+    return incl - x;
+}
+
+// The piece's keys as its threads hold them: item i of thread t is entry i * THREADS + t.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void load_piece(const SortSource& src, uint32_t start, uint32_t n,
+                                           const uint32_t* pidx, uint64_t (&k)[ITEMS]) {
+    const uint32_t t = threadIdx.x % THREADS;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) k[i] = src.at(start + min((uint32_t)i * THREADS + t, n - 1u), pidx);
+}
+
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void sort_piece(SortShared<THREADS, ITEMS>& sh, uint64_t (&k)[ITEMS], uint32_t start,
+                                           uint32_t n, uint32_t tile, uint32_t* pidx, uint64_t* __restrict__ keys64) {
+    constexpr int kW = THREADS / kWave;
+    constexpr uint32_t kCap = THREADS * ITEMS;
+    static_assert(ITEMS % 4 == 0, "whole 16-byte vectors of buckets per thread");
+    const uint32_t t = threadIdx.x % THREADS, w = t >> 6, l = lane_id();
+    uint32_t lo_z = ~0u, hi_z = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {   // (past the end: the last entry again)
+        lo_z = min(lo_z, (uint32_t)(k[i] >> 32));
+        hi_z = max(hi_z, (uint32_t)(k[i] >> 32));
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; i += 4) *reinterpret_cast<uint4*>(&sh.base[i * THREADS + 4 * t]) = make_uint4(0u, 0u, 0u, 0u);
+    *reinterpret_cast<uint4*>(&sh.part[4 * t]) = make_uint4(0u, 0u, 0u, 0u);
+    group_range<THREADS>(lo_z, hi_z, sh.red);
+    const bool equal = lo_z == hi_z;   // uniform over the group
+    if (equal) {
+        lo_z = ~0u;
+        hi_z = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            lo_z = min(lo_z, (uint32_t)k[i]);
+            hi_z = max(hi_z, (uint32_t)k[i]);
+        }
+        group_sync<THREADS>();
+        group_range<THREADS>(lo_z, hi_z, sh.red);
+    }
+    group_sync<THREADS>();
+    const BucketMap map(lo_z, hi_z, equal, 4 * THREADS);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if ((uint32_t)i * THREADS + t < n) atomicAdd(&sh.part[map.of(k[i])], 1u);
+    group_sync<THREADS>();
+    {
+        const uint4 q = *reinterpret_cast<const uint4*>(&sh.part[4 * t]);
+        const uint32_t e = group_exclusive_scan<THREADS>(q.x + q.y + q.z + q.w, sh.tmp);
+        *reinterpret_cast<uint4*>(&sh.part[4 * t]) = make_uint4(e, e + q.x, e + q.x + q.y, e + q.x + q.y + q.z);
+        if (t == THREADS - 1) sh.part[4 * THREADS] = n;
+    }
+    group_sync<THREADS>();
+    uint32_t slot[ITEMS];   // bucket, and the arrival in it
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const float at = map.at(k[i]);
+        const uint32_t p = map.bucket(at), b0 = sh.part[p], c = max(sh.part[p + 1] - b0, 1u);
+        const uint32_t b = b0 + min((uint32_t)((at - (float)p) * (float)c), c - 1u);
+        slot[i] = (uint32_t)i * THREADS + t < n ? atomicAdd(&sh.base[b], 1u) << 16 | b : b;
+    }
+    group_sync<THREADS>();
+    // exclusive scan of ITEMS consecutive buckets per thread, and the largest bucket
+    uint32_t c[ITEMS], most = 0, sum = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; i += 4) {
+        const uint4 q = *reinterpret_cast<const uint4*>(&sh.base[ITEMS * t + i]);
+        c[i] = q.x;
+        c[i + 1] = q.y;
+        c[i + 2] = q.z;
+        c[i + 3] = q.w;
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        most = max(most, c[i]);
+        sum += c[i];
+    }
+    most = wave_max(most);
+    if (kW > 1 && l == 0) sh.most[w] = most;
+    uint32_t e = group_exclusive_scan<THREADS>(sum, sh.tmp);
+    if (kW > 1) {
+#pragma unroll
+        for (int q = 0; q < kW; ++q) most = max(most, sh.most[q]);
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; i += 4) {
+        const uint32_t e1 = e + c[i], e2 = e1 + c[i + 1], e3 = e2 + c[i + 2];
+        *reinterpret_cast<uint4*>(&sh.base[ITEMS * t + i]) = make_uint4(e, e1, e2, e3);
+        e = e3 + c[i + 3];
+    }
+    if (t == THREADS - 1) sh.base[kCap] = n;
+    group_sync<THREADS>();
+    uint32_t lo[ITEMS], len[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const uint32_t b = slot[i] & 0xFFFFu;
+        lo[i] = sh.base[b];
+        len[i] = (uint32_t)i * THREADS + t < n ? sh.base[b + 1] - lo[i] : 0u;
+        if (len[i]) sh.key[lo[i] + (slot[i] >> 16)] = k[i];
+    }
+    group_sync<THREADS>();
+    uint32_t* out = reinterpret_cast<uint32_t*>(sh.key);
+    if (most <= kBucketMax) {
+        // the ITEMS buckets side by side, so that their reads are in flight together
+        uint32_t rank[ITEMS], longest = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            rank[i] = 0;
+            longest = max(longest, len[i]);
+        }
+        if (longest > 1u) {
+            for (uint32_t q = 0; q < longest; ++q) {
+                uint64_t x[ITEMS];
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i) x[i] = sh.key[lo[i] + min(q, max(len[i], 1u) - 1u)];
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i) rank[i] += q < len[i] && x[i] < k[i] ? 1u : 0u;
             }
         }
-        for (; j < want; ++j) {
-            const uint32_t e = e0 + j;
-            keys[e] = 0xFFFFFFFFu;
-            vals[e] = i;
-            zbits[e] = z;
+        group_sync<THREADS>();   // every key has been read
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            if (!len[i]) continue;
+            out[lo[i] + rank[i]] = (uint32_t)k[i];
+            if (keys64) keys64[start + lo[i] + rank[i]] = (uint64_t)tile << 32 | k[i] >> 32;
+        }
+        group_sync<THREADS>();
+    } else {
+        uint32_t size = 2;
+        while (size < n) size <<= 1;   // at most kCap, uniform
+        for (uint32_t p = n + t; p < size; p += THREADS) sh.key[p] = ~0ull;
+        group_sync<THREADS>();
+        for (uint32_t s = 2; s <= size; s <<= 1) {
+            for (uint32_t d = s >> 1; d > 0; d >>= 1) {
+                for (uint32_t p = t; p < size / 2; p += THREADS) {
+                    const uint32_t a = 2 * (p & ~(d - 1u)) | (p & (d - 1u)), c2 = a | d;
+                    const uint64_t x = sh.key[a], y = sh.key[c2];
+                    if ((x > y) == ((a & s) == 0u)) {
+                        sh.key[a] = y;
+                        sh.key[c2] = x;
+                    }
+                }
+                group_sync<THREADS>();
+            }
+        }
+        uint64_t r[ITEMS];
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) r[i] = sh.key[min((uint32_t)i * THREADS + t, n - 1u)];
+        group_sync<THREADS>();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t p = (uint32_t)i * THREADS + t;
+            if (p >= n) continue;
+            out[p] = (uint32_t)r[i];
+            if (keys64) keys64[start + p] = (uint64_t)tile << 32 | r[i] >> 32;
+        }
+        group_sync<THREADS>();
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const uint32_t p = (uint32_t)i * THREADS + t;
+        if (p < n) pidx[start + p] = out[p];
+    }
+}
+
+// Up to 64 entries by one wave, one per lane: the rank is the number of smaller keys.
+__device__ __forceinline__ void sort_lanes(const SortSource& src, uint32_t start, uint32_t n, uint32_t tile,
+                                           uint32_t* __restrict__ pidx, uint64_t* __restrict__ keys64) {
+    const uint32_t l = lane_id();
+    const uint64_t key = src.at(start + min(l, n - 1u), pidx);
+    uint32_t rank = 0;
+    for (uint32_t j = 0; j < n; ++j) {
+        const uint64_t kj = (uint64_t)__builtin_amdgcn_readlane((uint32_t)(key >> 32), (int)j) << 32 |
+                            __builtin_amdgcn_readlane((uint32_t)key, (int)j);
+        rank += kj < key ? 1u : 0u;
+    }
+    if (l >= n) return;
+    pidx[start + rank] = (uint32_t)key;
+    if (keys64) keys64[start + rank] = (uint64_t)tile << 32 | key >> 32;
+}
+
+// Item i of a size class: the pieces of step 5, then the listed tiles; none past the end.
+__device__ __forceinline__ SortItem class_item(const SortItem* __restrict__ items, uint32_t m,
+                                               const uint32_t* __restrict__ tiles, uint32_t total,
+                                               const uint32_t* __restrict__ ranges, uint32_t i) {
+    SortItem it{0, 0, 0, 0};
+    if (i >= total) return it;
+    if (i < m) return items[i];
+    it.tile = tiles[i - m];
+    it.start = ranges[2 * (size_t)it.tile];
+    it.n = ranges[2 * (size_t)it.tile + 1] - it.start;
+    return it;
+}
+
+// The workgroup's share of a size class; the next item is fetched while the current one is
+// sorted.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void sort_class(SortShared<THREADS, ITEMS>& sh, const BinArrays& A,
+                                           const SortItem* __restrict__ items, uint32_t m,
+                                           const uint32_t* __restrict__ tiles, uint32_t total, uint32_t block,
+                                           uint32_t blocks, const uint32_t* __restrict__ ranges, uint32_t* pidx,
+                                           uint64_t* __restrict__ keys64) {
+    SortItem cur = class_item(items, m, tiles, total, ranges, block);
+    while (cur.n) {   // uniform
+        block += blocks;
+        const SortItem next = class_item(items, m, tiles, total, ranges, block);
+        uint64_t k[ITEMS];
+        load_piece<THREADS, ITEMS>(SortSource{A.key, A.z_alt, cur.buf}, cur.start, cur.n, pidx, k);
+        sort_piece<THREADS, ITEMS>(sh, k, cur.start, cur.n, cur.tile, pidx, keys64);
+        __syncthreads();
+        cur = next;
+    }
+}
+
+// Step 6, segments and pieces of 1025 to 4096 entries.
+constexpr int kBigThreads = 1024;
+__global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) bin_sort_big_kernel(const BinArrays A,
+                                                                   const uint32_t* __restrict__ ranges, uint32_t* pidx,
+                                                                   uint64_t* __restrict__ keys64,
+                                                                   const int32_t* __restrict__ status) {
+    __shared__ SortShared<kBigThreads, 4> sh;
+    if (*status != kStatusOk) return;
+    const uint32_t n = min(A.counters[kNumBig], A.list_max), m = min(A.counters[kNumBigItems], A.item_max);
+    sort_class<kBigThreads, 4>(sh, A, A.big_item, m, A.big, n + m, blockIdx.x, gridDim.x, ranges, pidx, keys64);
+}
+
+// Step 6, the others: the first workgroups take the listed segments and pieces of up to 1024
+// entries, the rest one tile of up to 256 entries per wave.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) bin_sort_mid_kernel(const BinArrays A, uint32_t mid_blocks, uint32_t tiles,
+                                                           const uint32_t* __restrict__ ranges, uint32_t* pidx,
+                                                           uint64_t* __restrict__ keys64,
+                                                           const int32_t* __restrict__ status) {
+    __shared__ union {
+        SortShared<256, 4> mid;
+        SortShared<kWave, 4> small[4];
+    } sh;
+    if (*status != kStatusOk) return;
+    if (blockIdx.x >= mid_blocks) {
+        const uint32_t b = blockIdx.x - mid_blocks, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t tile = 4 * xcd_swizzle(b, gridDim.x - mid_blocks) + w;
+        if (tile >= tiles) return;
+        const uint32_t start = ranges[2 * (size_t)tile], n = ranges[2 * (size_t)tile + 1] - start;
+        if (n == 0 || n > kSmallMax) return;
+        const SortSource src{A.key, A.z_alt, 0u};
+        if (n <= (uint32_t)kWave) {
+            sort_lanes(src, start, n, tile, pidx, keys64);
+        } else {
+            uint64_t k[4];
+            load_piece<kWave, 4>(src, start, n, pidx, k);
+            sort_piece<kWave, 4>(sh.small[w], k, start, n, tile, pidx, keys64);
         }
         return;
     }
-    // staged: every entry of the run belongs to one particle of the chunk (the offsets are
-    // non-decreasing), so each LDS slot is written once
-    s_z[threadIdx.x] = z;
-    const uint32_t l0 = e0 - E0;
-    uint32_t j = 0;
-    for (int ty = ty0; ty <= ty1 && j < want; ++ty) {
-        for (int tx = tx0; tx <= tx1 && j < want; ++tx) {
-            if (!tile_member(fx, fy, r2, tx, ty, w_lim, h_lim)) continue;
-            s_key[l0 + j] = vd.tile_base + (uint32_t)(ty * vd.tiles_x + tx);
-            s_own[l0 + j] = (uint8_t)threadIdx.x;
-            ++j;
-        }
-    }
-    for (; j < want; ++j) {
-        s_key[l0 + j] = 0xFFFFFFFFu;
-        s_own[l0 + j] = (uint8_t)threadIdx.x;
-    }
-    __syncthreads();
-    for (uint32_t q = threadIdx.x; q < E1 - E0; q += 256u) {
-        const uint32_t o = s_own[q];
-        keys[E0 + q] = s_key[q];
-        vals[E0 + q] = first + o;
-        zbits[E0 + q] = s_z[o];
-    }
+    const uint32_t n = min(A.counters[kNumMid], A.list_max), m = min(A.counters[kNumMidItems], A.item_max);
+    sort_class<256, 4>(sh.mid, A, A.mid_item, m, A.mid, n + m, blockIdx.x, mid_blocks, ranges, pidx, keys64);
 }
 
-// Ranks up to ITEMS items per lane within the wave by a digit of `bits` <= MAXB bits. Items are taken in
-// rounds (item i of every lane in round i, lanes in order), so ranks follow the order
-// (round, lane). Lanes with equal digits are matched bit by bit with ballots; an item's
-// rank is the wave's count of its digit in earlier rounds plus the matching lanes below
-// it. `cnt` holds the wave's 256 digit counters (zero on entry) and ends with the wave's
-// digit totals. Bit i of `valid` marks item i as present; `items` (uniform) bounds the
-// rounds.
-template <int ITEMS, int MAXB = kRadixBits>
-__device__ __forceinline__ void wave_rank(const uint32_t (&k)[ITEMS], int shift, int bits, uint32_t valid,
-                                          int items, uint32_t* __restrict__ cnt, uint32_t (&rk)[ITEMS]) {
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        if (i < items) {
-            const uint32_t d = digit_at(k[i], shift, bits);
-            const bool ok = (valid >> i) & 1u;
-            const uint64_t okm = ballot64(ok);
-            uint32_t m_lo = (uint32_t)okm, m_hi = (uint32_t)(okm >> 32);
-#pragma unroll
-            for (int b = 0; b < MAXB; ++b) {
-                if (b < bits) {
-                    // keep the lanes whose bit b equals this lane's: m &= ~(ballot ^ sign(bit))
-                    // (one three-input bitwise instruction per half)
-                    const uint32_t sx = (uint32_t)((int32_t)(d << (31 - b)) >> 31);   // bit b, sign-extended
-                    const uint64_t bal = ballot64(sx != 0u);
-                    m_lo &= ~((uint32_t)bal ^ sx);
-                    m_hi &= ~((uint32_t)(bal >> 32) ^ sx);
-                }
-            }
-            const uint64_t m = ((uint64_t)m_hi << 32) | m_lo;
-            const uint32_t below = rank_below(m);
-            const uint32_t prior = cnt[d];
-            rk[i] = prior + below;
-            if (ok && below == 0) cnt[d] = prior + (uint32_t)__popcll(m);
-        }
-    }
-}
+// ---- Step 5: long segments ----------------------------------------------------------------------
 
-// Step 4: stable LSD passes over the tile ids (digit of `bits` <= 9 bits at `shift`), each
-// in three kernels over 4096-entry sort tiles, with no waiting between workgroups:
-//   4a  count     each sort tile's digit counts, stored digit-major
-//   4b  scan      per digit, the exclusive prefix over the sort tiles and the total
-//   4c  scatter   each sort tile ranks its entries per digit within each wave (ballots),
-//                 places them at digit base + earlier tiles' count + rank, reorders in LDS
-//                 so that the stores are contiguous runs per digit
-// Count and scatter give each XCD a contiguous range of sort tiles (xcd_swizzle over the
-// tiles in use): neighbouring sort tiles write neighbouring words of the digit-major counts
-// and, for a digit, adjacent pieces of its output run, so the partial cache lines they
-// leave are completed in one L2 instead of being written back separately from several.
-__global__ void __launch_bounds__(kSortThreads) tile_count_kernel(const uint32_t* __restrict__ kin,
-                                                                  const uint32_t* __restrict__ count_p,
-                                                                  uint64_t capacity, int shift, int bits,
-                                                                  uint32_t* __restrict__ tcount, uint32_t stride) {
-    // four copies of the counters, lane l adding to copy l mod 4: lanes of one instruction
-    // that share a digit (many do in the second pass, whose input is ordered by the low
-    // digit) mostly hit different copies, at different banks (copies kTileRadix + 1 apart)
-    constexpr uint32_t kCopy = kTileRadix + 1;
-    __shared__ uint32_t s_h[4 * kCopy];
-    const uint32_t count = *count_p;
-    if ((uint64_t)count > capacity) return;
-    const uint32_t n_tiles = (count + kSortTile - 1) / kSortTile;
-    if (blockIdx.x >= n_tiles) return;
-    const uint32_t tile = xcd_swizzle(blockIdx.x, n_tiles), t = threadIdx.x;
-    for (uint32_t q = t; q < 4 * kCopy; q += kSortThreads) s_h[q] = 0u;
-    __syncthreads();
-    uint32_t k[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) k[i] = kin[min(tile * kSortTile + i * kSortThreads + t, count - 1)];
-    uint32_t* h = s_h + (lane_id() & 3u) * kCopy;
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const bool ok = tile * kSortTile + i * kSortThreads + t < count;
-        const uint32_t d = digit_at(k[i], shift, bits);
-        // neighbouring entries mostly share a digit: then one add per wave
-        const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
-        const uint64_t act = ballot64(ok);
-        if (ballot64(ok && d != d0) == 0) {
-            if (lane_id() == 0 && act) atomicAdd(&s_h[d0], (uint32_t)__popcll(act));
-        } else if (ok) {
-            atomicAdd(&h[d], 1u);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t d = t; d < (uint32_t)kTileRadix; d += kSortThreads)
-        tcount[(size_t)d * stride + tile] = s_h[d] + s_h[kCopy + d] + s_h[2 * kCopy + d] + s_h[3 * kCopy + d];
-}
+// A workgroup takes a segment of more than kBigMax entries (from a device-wide counter) and
+// distributes it over 4096 buckets of its depth range, from one buffer to the other;
+// consecutive buckets whose entries start in the same 2048 make one piece (at most 4095
+// entries), a bucket of more than 2048 entries is a piece of its own, and pieces longer than
+// kBigMax are distributed again (the range of a bucket is at most a 4096th of its parent's, and
+// equal depths are told apart by their indices, so this ends after a few levels). The keys
+// cross memory twice per level, where four radix passes over 4096-entry chunks crossed it
+// three times each and took thirteen launches, whether or not a tile needed them.
+constexpr uint32_t kParts = 4096;
+constexpr uint32_t kPartGroup = 2048;
 
-__global__ void __launch_bounds__(256) tile_scan_kernel(uint32_t* __restrict__ tcount, uint32_t stride,
-                                                        const uint32_t* __restrict__ count_p, uint64_t capacity,
-                                                        uint32_t* __restrict__ hist) {
-    __shared__ uint32_t s_tmp[4];
-    constexpr uint32_t kItems = 16;   // consecutive sort tiles per thread and chunk
-    const uint32_t count = *count_p;
-    if ((uint64_t)count > capacity) return;
-    const uint32_t ntiles = (count + kSortTile - 1) / kSortTile;
-    uint32_t* row = tcount + (size_t)blockIdx.x * stride;
-    uint32_t carry = 0;
-    for (uint32_t c0 = 0; c0 < ntiles; c0 += 256 * kItems) {
-        const uint32_t i0 = c0 + threadIdx.x * kItems;
-        uint32_t x[kItems], sum = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < kItems; ++q) {
-            x[q] = i0 + q < ntiles ? row[i0 + q] : 0u;
-            sum += x[q];
-        }
-        uint32_t total;
-        uint32_t run = carry + block_exclusive_scan(sum, s_tmp, total);
-#pragma unroll
-        for (uint32_t q = 0; q < kItems; ++q) {
-            if (i0 + q < ntiles) row[i0 + q] = run;
-            run += x[q];
-        }
-        carry += total;
-    }
-    if (threadIdx.x == 0) hist[blockIdx.x] = carry;   // this digit's count over all entries
-}
-
-// BITS: the pass's digit width, a compile-time constant (the ballot chain then carries no
-// per-bit condition). Positions past the last entry (the final sort tile only) carry the
-// all-ones key, whose digit is the largest, so they sort behind every entry of the tile
-// and no step needs a per-item validity mask; only positions below n_here are written.
-template <int BITS>
-__global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(
-    const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, const uint32_t* __restrict__ zin,
-    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t* __restrict__ zout,
-    const uint32_t* __restrict__ count_p, uint64_t capacity, int shift,
-    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ tcount, uint32_t stride) {
-    __shared__ uint32_t s_buf[kSortTile];   // tile reordered by digit: keys, values, depth bits
-    __shared__ uint16_t s_dig[kSortTile];    // digit at each reordered position
-    __shared__ uint32_t s_wcnt[4][kTileRadix];
-    __shared__ uint32_t s_local[kTileRadix];
-    __shared__ uint32_t s_base[kTileRadix];
-    __shared__ uint32_t s_tmp[4];
-
-    const uint32_t count = *count_p;
-    if ((uint64_t)count > capacity) return;
-    const uint32_t n_tiles = (count + kSortTile - 1) / kSortTile;
-    if (blockIdx.x >= n_tiles) return;
-    const uint32_t tile = xcd_swizzle(blockIdx.x, n_tiles);
-    const uint32_t t = threadIdx.x, w = t >> 6, lane = t & 63;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        s_wcnt[k][t] = 0u;
-        s_wcnt[k][t + 256] = 0u;
-    }
-    __syncthreads();
-
-    // load: wave w owns entries [tile*4096 + w*1024, +1024), item i of lane l at i*64 + l
-    const uint32_t wbase = tile * kSortTile + w * (kSortTile / 4);
-    const uint32_t n_here = min((uint32_t)kSortTile, count - tile * kSortTile);
-    uint32_t k[kSortItems], v[kSortItems], rk[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const uint32_t idx = wbase + i * kWave + lane;
-        k[i] = idx < count ? kin[idx] : 0xFFFFFFFFu;
-    }
-    // this tile's start of digits 2t, 2t+1: digit base over all entries + earlier tiles' count
-    const uint32_t h0 = hist[2 * t], h1 = hist[2 * t + 1];
-    const uint32_t e0 = tcount[(size_t)(2 * t) * stride + tile], e1 = tcount[(size_t)(2 * t + 1) * stride + tile];
-    wave_rank<kSortItems, BITS>(k, shift, BITS, 0xFFFFFFFFu, kSortItems, s_wcnt[w], rk);
-    // values are needed only after the keys are placed: their loads overlap the scans
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) v[i] = vin[min(wbase + i * kWave + lane, count - 1)];
-    __syncthreads();
-
-    uint32_t mine[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t d = 2 * t + h;
-        const uint32_t c0 = s_wcnt[0][d], c1 = s_wcnt[1][d], c2 = s_wcnt[2][d], c3 = s_wcnt[3][d];
-        mine[h] = c0 + c1 + c2 + c3;
-        s_wcnt[0][d] = 0u;
-        s_wcnt[1][d] = c0;
-        s_wcnt[2][d] = c0 + c1;
-        s_wcnt[3][d] = c0 + c1 + c2;
-    }
-    uint32_t tot;
-    const uint32_t gbase = block_exclusive_scan(h0 + h1, s_tmp, tot);
-    const uint32_t lbase = block_exclusive_scan(mine[0] + mine[1], s_tmp, tot);
-    s_base[2 * t] = gbase + e0;
-    s_base[2 * t + 1] = gbase + h0 + e1;
-    s_local[2 * t] = lbase;
-    s_local[2 * t + 1] = lbase + mine[0];
-    __syncthreads();
-
-    // reorder in LDS by digit (stable), then write runs: keys first, then the values and
-    // the depth bits through the same buffer
-    uint32_t lpos[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const uint32_t d = digit_at(k[i], shift, BITS);
-        lpos[i] = s_local[d] + s_wcnt[w][d] + rk[i];
-        s_buf[lpos[i]] = k[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const uint32_t j = t + i * kSortThreads;
-        if (j < n_here) {
-            const uint32_t key = s_buf[j];
-            const uint32_t dd = digit_at(key, shift, BITS);
-            s_dig[j] = (uint16_t)dd;
-            const uint32_t dst = s_base[dd] + (j - s_local[dd]);
-            if (dst < count) kout[dst] = key;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) s_buf[lpos[i]] = v[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const uint32_t j = t + i * kSortThreads;
-        if (j < n_here) {
-            const uint32_t dd = s_dig[j];
-            const uint32_t dst = s_base[dd] + (j - s_local[dd]);
-            if (dst < count) vout[dst] = s_buf[j];
-        }
-    }
-    // the depth bits follow the same path (loaded late to keep registers free)
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) v[i] = zin[min(wbase + i * kWave + lane, count - 1)];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) s_buf[lpos[i]] = v[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const uint32_t j = t + i * kSortThreads;
-        if (j < n_here) {
-            const uint32_t dd = s_dig[j];
-            const uint32_t dst = s_base[dd] + (j - s_local[dd]);
-            if (dst < count) zout[dst] = s_buf[j];
-        }
-    }
-}
-
-// Step 5: tile ranges from the sorted tile ids, four consecutive entries per thread (one
-// 16-byte load; the workspace and its sections are 256-byte aligned) and the two
-// neighbours of the run.
-__global__ void __launch_bounds__(256) finalize_kernel(const uint32_t* __restrict__ keys,
-                                                       const uint32_t* __restrict__ count_p, uint64_t capacity,
-                                                       uint32_t tiles_total, uint32_t* __restrict__ ranges) {
-    const uint32_t count = *count_p;
-    if ((uint64_t)count > capacity) return;
-    const uint32_t groups = (count + 3) / 4;
-    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < groups; g += gridDim.x * blockDim.x) {
-        const uint32_t i0 = 4 * g;
-        uint32_t k[6];   // ids of entries i0 - 1 .. i0 + 4; none past the ends (all ones)
-        k[0] = i0 > 0 ? keys[i0 - 1] : 0xFFFFFFFFu;
-        if (i0 + 4 <= count) {
-            const uint4 q = *reinterpret_cast<const uint4*>(keys + i0);
-            k[1] = q.x;
-            k[2] = q.y;
-            k[3] = q.z;
-            k[4] = q.w;
-        } else {
-#pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) k[1 + j] = i0 + j < count ? keys[i0 + j] : 0xFFFFFFFFu;
-        }
-        k[5] = i0 + 4 < count ? keys[i0 + 4] : 0xFFFFFFFFu;
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
-            const uint32_t i = i0 + j, tl = k[1 + j];
-            if (i < count && tl < tiles_total) {
-                if (tl != k[j]) ranges[2 * tl] = i;
-                if (tl != k[j + 2]) ranges[2 * tl + 1] = i + 1;
-            }
-        }
-    }
-}
-
-// OR and AND of x over the workgroup (s_tmp: 2 * kBigWaves words). Contains __syncthreads.
-__device__ __forceinline__ void block_or_and(uint32_t x_or, uint32_t x_and, uint32_t* s_tmp, uint32_t& r_or,
-                                             uint32_t& r_and) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        x_or |= __shfl_xor(x_or, o, kWave);
-        x_and &= __shfl_xor(x_and, o, kWave);
-    }
-    const uint32_t w = threadIdx.x >> 6;
-    if (lane_id() == 0) {
-        s_tmp[w] = x_or;
-        s_tmp[kBigWaves + w] = x_and;
-    }
-    __syncthreads();
-    r_or = 0u;
-    r_and = 0xFFFFFFFFu;
-#pragma unroll
-    for (int j = 0; j < kBigWaves; ++j) {
-        r_or |= s_tmp[j];
-        r_and &= s_tmp[kBigWaves + j];
-    }
-    __syncthreads();
-}
-
-struct SegShared {
-    uint32_t buf[kSegMax];                      // segments reordered by digit: keys, then values
-    uint32_t wcnt[kBigWaves][kRadix];
-    uint32_t local[kBigWaves / 2][kRadix];      // group path: each group's digit bases; global
-                                                // path: digit histogram [0], next output position [1]
-    uint32_t tmp[2 * kBigWaves];
+struct __align__(16) PartShared {
+    uint32_t base[kParts];
+    uint32_t first[kParts + 1];   // start of each piece
+    uint32_t red[2][kBinWaves];
+    uint32_t tmp[kBinWaves];
+    uint32_t last[kBinWaves];
+    uint32_t item, depth, n_mid, n_big, at_mid, at_big, cur[3];
 };
 
-__device__ __forceinline__ void zero_wcnt(SegShared& sh, uint32_t t) {
-#pragma unroll
-    for (int q = 0; q < kBigWaves * kRadix / kBigThreads; ++q) (&sh.wcnt[0][0])[q * kBigThreads + t] = 0u;
-}
-
-// Digit d (< kRadix): wave prefixes written back into wcnt, returns the total over waves.
-__device__ __forceinline__ uint32_t digit_wave_prefix(SegShared& sh, uint32_t d) {
-    uint32_t run = 0;
-#pragma unroll
-    for (int q = 0; q < kBigWaves; ++q) {
-        const uint32_t c = sh.wcnt[q][d];
-        sh.wcnt[q][d] = run;
-        run += c;
-    }
-    return run;
-}
-
-// Segments of up to 512 G entries sorted in LDS by groups of G waves (G = 2, 4 or 8, the
-// same for the whole workgroup): the workgroup sorts kBigWaves / G segments side by side,
-// group g (waves gG .. gG + G - 1) the segment (tile, start, n) that its threads pass
-// (n = 0: none), so that the barriers and latencies of a pass are shared by several
-// segments. Items stay in registers between passes; each pass ranks by one 8-bit digit of
-// the depth bits within each wave (ballots), turns the group's digit counts into bases,
-// reorders the keys and then the values through the group's part of LDS and reloads them
-// in position order. Only the bits that differ within a segment are sorted on. Positions
-// past the segment's end, up to the group's whole rounds, carry the key with all bits set:
-// its digit is the largest of every pass and those positions come after every entry, so
-// stability keeps them at the end and no pass needs a per-item validity mask. G is a
-// parameter rather than a template argument so that the kernel holds one copy of this
-// code (three copies take more registers than the kernel may use).
-__device__ __forceinline__ void segment_sort_groups(SegShared& sh, uint32_t G, uint32_t tile, uint32_t start,
-                                                    uint32_t n, const uint32_t* __restrict__ zs,
-                                                    uint32_t* __restrict__ pidx, uint64_t* __restrict__ keys64) {
-    static_assert(kBigWaves == 8 && kRadix == 256 && kBigItems * kWave * kBigWaves == (int)kSegMax, "group layout");
-    // the segment is the same for every lane of a wave, G for the whole workgroup: scalars
-    G = __builtin_amdgcn_readfirstlane(G);
-    tile = __builtin_amdgcn_readfirstlane(tile);
-    start = __builtin_amdgcn_readfirstlane(start);
-    n = __builtin_amdgcn_readfirstlane(n);
-    const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = lane_id();
-    const uint32_t group_threads = kWave * G;
-    const uint32_t g = w / G, g0 = g * G, tg = t - g * group_threads;
-    uint32_t* buf = sh.buf + g * group_threads * kBigItems;
-    const int items = (int)((n + group_threads - 1) / group_threads);   // uniform within the group
-    const uint32_t wbase = (w - g0) * kWave * (uint32_t)items;          // this wave's first position
-    uint32_t k[kBigItems], v[kBigItems], rk[kBigItems];
-    uint32_t k_or = 0u, k_and = 0xFFFFFFFFu;
-    if (n) {
-        // loads clamped into the segment rather than predicated, so that all of them are in
-        // flight at once
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i) {
-            const uint32_t p = min(wbase + (uint32_t)i * kWave + l, n - 1);
-            v[i] = pidx[start + p];
-            k[i] = zs[start + p];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kBigItems; ++i) {
-        const bool ok = i < items && wbase + (uint32_t)i * kWave + l < n;
-        k_or |= ok ? k[i] : 0u;
-        k_and &= ok ? k[i] : 0xFFFFFFFFu;
-        k[i] = ok ? k[i] : 0xFFFFFFFFu;
-    }
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        k_or |= __shfl_xor(k_or, o, kWave);
-        k_and &= __shfl_xor(k_and, o, kWave);
-    }
-    if (l == 0) {
-        sh.tmp[w] = k_or;
-        sh.tmp[kBigWaves + w] = k_and;
-    }
-    __syncthreads();
-    // the differing bits of every group (its waves' OR and AND; an empty group has OR 0 and
-    // AND all ones: no differing bit): this group's first bit, the most passes of any group
-    int lo = 0, passes = 0;
-    {
-        uint32_t a_or = 0u, a_and = 0xFFFFFFFFu;
-#pragma unroll
-        for (uint32_t q = 0; q < (uint32_t)kBigWaves; ++q) {
-            a_or |= sh.tmp[q];
-            a_and &= sh.tmp[kBigWaves + q];
-            if (((q + 1) & (G - 1)) == 0) {   // q is the last wave of group q / G
-                const uint32_t diff = a_or & ~a_and;
-                const int glo = diff ? __builtin_ctz(diff) : 0;
-                const int ghi = diff ? 32 - __builtin_clz(diff) : 0;
-                passes = max(passes, (ghi - glo + kRadixBits - 1) / kRadixBits);
-                if (q / G == g) lo = glo;
-                a_or = 0u;
-                a_and = 0xFFFFFFFFu;
-            }
-        }
-    }
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    passes = __builtin_amdgcn_readfirstlane(passes);
-    // digits of this thread in the group's scan: 2 tg, 2 tg + 1 for G = 2, tg otherwise
-    const uint32_t nd = G == 2 ? 2u : 1u, d0 = tg * nd;
-    // Every group makes the most passes any group needs, pass p on bits [min(lo + 8 p, 24),
-    // +8). A group's extra passes rank bits above its differing ones (equal within the
-    // segment) or its most significant differing bits again: stable passes over keys
-    // already in that order, which change nothing. Where the clamp makes a group's own last
-    // pass overlap the one before, the stable LSD order is still the sorted one.
-    for (int pass = 0; pass < passes; ++pass) {
-        const int shift = min(lo + pass * kRadixBits, 32 - kRadixBits);
-        // each wave clears its own counters: LDS operations of one wave complete in order
-#pragma unroll
-        for (int q = 0; q < kRadix / kWave; ++q) sh.wcnt[w][q * kWave + l] = 0u;
-        wave_rank<kBigItems>(k, shift, kRadixBits, 0xFFFFFFFFu, items, sh.wcnt[w], rk);
+__global__ void __launch_bounds__(kBinThreads) bin_partition_kernel(const BinArrays A, uint32_t* pidx,
+                                                                    const int32_t* __restrict__ status) {
+    __shared__ PartShared sh;
+    if (*status != kStatusOk) return;
+    const uint32_t t = threadIdx.x, w = t >> 6, l = lane_id();
+    const uint32_t n_large = min(A.counters[kNumLarge], A.large_max);
+    for (;;) {
         __syncthreads();
-        // this thread's digits: prefixes over the group's waves, the group's totals
-        uint32_t tot[2], mine = 0u;
+        if (t == 0) sh.item = atomicAdd(&A.counters[kWork], 1u);
+        __syncthreads();
+        if (sh.item >= n_large) break;   // uniform
+        const SortItem seg = A.large[sh.item];
+        uint2* stack = A.stack + seg.start / kBigMax;
+        uint32_t start = seg.start, n = seg.n, buf = 0;
+        if (t == 0) sh.depth = 0;
+        for (;;) {
+            const SortSource src{A.key, A.z_alt, buf};
+            // the range of the depths, and where they are all equal of the indices
+            uint32_t lo = ~0u, hi = 0, lo_i = ~0u, hi_i = 0;
+            for (uint32_t p0 = t; p0 < n; p0 += 4 * kBinThreads) {
+                uint64_t k[4];
 #pragma unroll
-        for (uint32_t j = 0; j < 2; ++j) {
-            const uint32_t d = d0 + j;
-            uint32_t run = 0u;
-            if (j < nd && d < (uint32_t)kRadix) {
+                for (int i = 0; i < 4; ++i) k[i] = src.at(start + min(p0 + (uint32_t)i * kBinThreads, n - 1u), pidx);
 #pragma unroll
-                for (uint32_t q = 0; q < (uint32_t)kBigWaves; ++q) {
-                    if (q < G) {
-                        const uint32_t c = sh.wcnt[g0 + q][d];
-                        sh.wcnt[g0 + q][d] = run;
-                        run += c;
+                for (int i = 0; i < 4; ++i) {
+                    lo = min(lo, (uint32_t)(k[i] >> 32));
+                    hi = max(hi, (uint32_t)(k[i] >> 32));
+                    lo_i = min(lo_i, (uint32_t)k[i]);
+                    hi_i = max(hi_i, (uint32_t)k[i]);
+                }
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < kParts / kBinThreads; ++q) sh.base[q * kBinThreads + t] = 0u;
+            if (t == 0) sh.n_mid = sh.n_big = 0;
+            group_range<kBinThreads>(lo, hi, sh.red);
+            const bool equal = lo == hi;
+            __syncthreads();
+            if (equal) {
+                lo = lo_i;
+                hi = hi_i;
+                group_range<kBinThreads>(lo, hi, sh.red);
+                __syncthreads();
+            }
+            const BucketMap map(lo, hi, equal, kParts);
+            for (uint32_t p0 = t; p0 < n; p0 += 4 * kBinThreads) {
+                uint64_t k[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) k[i] = src.at(start + min(p0 + (uint32_t)i * kBinThreads, n - 1u), pidx);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (p0 + (uint32_t)i * kBinThreads < n) atomicAdd(&sh.base[map.of(k[i])], 1u);
+            }
+            __syncthreads();
+            // four consecutive buckets per thread: bases, and which of them start a piece
+            static_assert(kParts == 4 * kBinThreads, "four buckets per thread");
+            const uint4 c4 = *reinterpret_cast<const uint4*>(&sh.base[4 * t]);
+            const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+            uint32_t total;
+            uint32_t e = block_exclusive_scan<kBinWaves, uint32_t>(c4.x + c4.y + c4.z + c4.w, sh.tmp, total);
+            uint32_t at[4], tag = 0;   // tag: the last non-empty bucket so far, 2 (group + 1) + alone
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                at[q] = e;
+                e += c[q];
+                if (c[q]) tag = 2u * (at[q] / kPartGroup + 1u) + (c[q] > kPartGroup ? 1u : 0u);
+            }
+            const uint64_t has = ballot64(tag != 0u);
+            const uint64_t below = has & ((1ull << l) - 1ull);
+            if (l == 0) sh.last[w] = has ? (uint32_t)__builtin_amdgcn_readlane(tag, 63 - __builtin_clzll(has)) : 0u;
+            uint32_t prev = __shfl(tag, below ? 63 - __clzll((long long)below) : 0, kWave);
+            __syncthreads();
+            if (!below) {
+                prev = 0;
+                for (int q = (int)w - 1; q >= 0 && !prev; --q) prev = sh.last[q];
+            }
+            bool starts[4];
+            uint32_t ns = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                starts[q] = false;
+                if (!c[q]) continue;
+                const uint32_t now = 2u * (at[q] / kPartGroup + 1u) + (c[q] > kPartGroup ? 1u : 0u);
+                starts[q] = now != prev || (now & 1u);
+                prev = now;
+                ns += starts[q] ? 1u : 0u;
+            }
+            uint32_t pieces;
+            uint32_t s = block_exclusive_scan<kBinWaves, uint32_t>(ns, sh.tmp, pieces);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                sh.base[4 * t + q] = at[q];
+                if (starts[q]) sh.first[s++] = at[q];
+            }
+            if (t == 0) sh.first[pieces] = n;
+            __syncthreads();
+            for (uint32_t p0 = t; p0 < n; p0 += 4 * kBinThreads) {
+                uint64_t k[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) k[i] = src.at(start + min(p0 + (uint32_t)i * kBinThreads, n - 1u), pidx);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (p0 + (uint32_t)i * kBinThreads >= n) continue;
+                    const uint32_t d = start + atomicAdd(&sh.base[map.of(k[i])], 1u);
+                    if (buf) {
+                        A.key[d] = k[i];
+                    } else {
+                        A.z_alt[d] = (uint32_t)(k[i] >> 32);
+                        pidx[d] = (uint32_t)k[i];
                     }
                 }
             }
-            tot[j] = run;
-            mine += run;
-        }
-        // exclusive scan of the totals over the group's threads (digit order)
-        const uint32_t inc = wave_inclusive_scan(mine);
-        if (l == kWave - 1) sh.tmp[w] = inc;
-        __syncthreads();
-        uint32_t base = inc - mine;
-#pragma unroll
-        for (uint32_t q = 0; q < (uint32_t)kBigWaves; ++q) base += (g0 + q < w) ? sh.tmp[g0 + q] : 0u;
-#pragma unroll
-        for (uint32_t j = 0; j < 2; ++j) {
-            const uint32_t d = d0 + j;
-            if (j < nd && d < (uint32_t)kRadix) sh.local[g][d] = base;
-            base += tot[j];
-        }
-        __syncthreads();
-        uint32_t pos[kBigItems];
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i) {
-            if (i < items) {
-                const uint32_t d = digit_at(k[i], shift, kRadixBits);
-                pos[i] = sh.local[g][d] + sh.wcnt[w][d] + rk[i];
-                buf[pos[i]] = k[i];
+            // the pieces: listed for step 6, or pending
+            const uint32_t to = buf ^ 1u;
+            for (uint32_t q0 = 0; q0 < pieces; q0 += kBinThreads) {
+                const uint32_t q = q0 + t;
+                const uint32_t f = q < pieces ? sh.first[q] : 0u, pn = q < pieces ? sh.first[q + 1] - f : 0u;
+                uint32_t i = 0;
+                if (pn > kBigMax)
+                    stack[atomicAdd(&sh.depth, 1u)] = make_uint2(start + f, pn | to << 31);
+                else if (pn)
+                    i = atomicAdd(pn <= kMidMax ? &sh.n_mid : &sh.n_big, 1u);
+                __syncthreads();
+                if (t == 0) {
+                    sh.at_mid = sh.n_mid ? atomicAdd(&A.counters[kNumMidItems], sh.n_mid) : 0u;
+                    sh.at_big = sh.n_big ? atomicAdd(&A.counters[kNumBigItems], sh.n_big) : 0u;
+                }
+                __syncthreads();
+                if (pn && pn <= kBigMax) {
+                    const bool mid = pn <= kMidMax;
+                    i += mid ? sh.at_mid : sh.at_big;
+                    if (i < A.item_max) (mid ? A.mid_item : A.big_item)[i] = SortItem{start + f, pn, seg.tile, to};
+                }
+                __syncthreads();
+                if (t == 0) sh.n_mid = sh.n_big = 0;
+                __syncthreads();
             }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i)
-            if (i < items) k[i] = buf[wbase + (uint32_t)i * kWave + l];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i)
-            if (i < items) buf[pos[i]] = v[i];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i)
-            if (i < items) v[i] = buf[wbase + (uint32_t)i * kWave + l];
-    }
-    // every read of the segment happened before the first barrier: in place is safe
-#pragma unroll
-    for (int i = 0; i < kBigItems; ++i) {
-        const uint32_t p = wbase + (uint32_t)i * kWave + l;
-        if (i >= items || p >= n) continue;
-        if (passes) pidx[start + p] = v[i];
-        if (keys64) keys64[start + p] = ((uint64_t)tile << 32) | k[i];
-    }
-}
-
-// Segment longer than kSegMax, sorted by one workgroup through global scratch. A first
-// sweep copies (depth bits, particle index) to (sk0, sv) and reduces the differing bits;
-// each pass then scatters chunk after chunk straight to its place, counting the next
-// pass's digits on the way. Every sweep issues kBigItems independent loads per thread.
-__device__ __forceinline__ void segment_sort_global(SegShared& sh, uint32_t tile, uint32_t start, uint32_t n,
-                                                    const uint32_t* __restrict__ zs, uint32_t* __restrict__ pidx,
-                                                    uint64_t* __restrict__ keys64, uint32_t* __restrict__ sk0,
-                                                    uint32_t* __restrict__ sk1, uint32_t* __restrict__ sv) {
-    const uint32_t t = threadIdx.x, w = t >> 6, l = lane_id();
-    uint32_t k_or = 0u, k_and = 0xFFFFFFFFu;
-    for (uint32_t c0 = 0; c0 < n; c0 += kSegMax) {
-        uint32_t g[kBigItems], key[kBigItems];
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i) {
-            const uint32_t pc = min(c0 + (uint32_t)i * kBigThreads + t, n - 1);
-            g[i] = pidx[start + pc];
-            key[i] = zs[start + pc];
-        }
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i) {
-            const uint32_t p = c0 + (uint32_t)i * kBigThreads + t;
-            if (p < n) {
-                sk0[start + p] = key[i];
-                sv[start + p] = g[i];
-                k_or |= key[i];
-                k_and &= key[i];
-            }
-        }
-    }
-    uint32_t all_or, all_and;
-    block_or_and(k_or, k_and, sh.tmp, all_or, all_and);   // also orders the sweep's writes
-    const uint32_t diff = all_or ^ all_and;
-    // uniform by construction; readfirstlane tells the compiler, so the digit loops branch
-    // on scalars
-    const int lo = __builtin_amdgcn_readfirstlane(diff ? __builtin_ctz(diff) : 0);
-    const int hi = __builtin_amdgcn_readfirstlane(diff ? 32 - __builtin_clz(diff) : 0);
-    const Split8 split(lo, hi);
-    const int passes = split.passes;
-    uint32_t *src_k = sk0, *src_v = sv, *dst_k = sk1, *dst_v = pidx;
-    if (passes > 0) {
-        // digit histogram of the first pass
-        if (t < kRadix) sh.local[0][t] = 0u;
-        __syncthreads();
-        for (uint32_t c0 = 0; c0 < n; c0 += kSegMax) {
-            uint32_t kk[kBigItems];
-#pragma unroll
-            for (int i = 0; i < kBigItems; ++i) kk[i] = src_k[start + min(c0 + (uint32_t)i * kBigThreads + t, n - 1)];
-#pragma unroll
-            for (int i = 0; i < kBigItems; ++i)
-                if (c0 + (uint32_t)i * kBigThreads + t < n) atomicAdd(&sh.local[0][digit_at(kk[i], split.shift(0), kRadixBits)], 1u);
-        }
-        __syncthreads();
-    }
-    for (int pass = 0; pass < passes; ++pass) {
-        const int shift = split.shift(pass), bits = kRadixBits;
-        const bool has_next = pass + 1 < passes;
-        const int next_shift = has_next ? split.shift(pass + 1) : 0, next_bits = kRadixBits;
-        uint32_t all;
-        const uint32_t h = t < kRadix ? sh.local[0][t] : 0u;
-        const uint32_t rb = block_exclusive_scan<kBigWaves>(h, sh.tmp, all);
-        if (t < kRadix) {
-            sh.local[1][t] = rb;
-            sh.local[0][t] = 0u;   // now the next pass's histogram
-        }
-        for (uint32_t c0 = 0; c0 < n; c0 += kSegMax) {
-            const uint32_t cn = min(kSegMax, n - c0);
-            const int items = (int)((cn + kBigThreads - 1) / kBigThreads);
-            const uint32_t wbase = c0 + w * kWave * (uint32_t)items;
-            zero_wcnt(sh, t);
-            __syncthreads();
-            uint32_t k[kBigItems], v[kBigItems], rk[kBigItems];
-            uint32_t valid = 0;
-#pragma unroll
-            for (int i = 0; i < kBigItems; ++i) {
-                const uint32_t p = wbase + (uint32_t)i * kWave + l;
-                valid |= (uint32_t)(i < items && p < c0 + cn) << i;
-                const uint32_t pc = min(p, n - 1);
-                k[i] = src_k[start + pc];
-                v[i] = src_v[start + pc];
-            }
-            wave_rank<kBigItems>(k, shift, bits, valid, items, sh.wcnt[w], rk);
-            __syncthreads();
-            const uint32_t tot = t < kRadix ? digit_wave_prefix(sh, t) : 0u;
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < kBigItems; ++i) {
-                if (!((valid >> i) & 1u)) continue;
-                const uint32_t d = digit_at(k[i], shift, bits);
-                const uint32_t o = sh.local[1][d] + sh.wcnt[w][d] + rk[i];
-                dst_k[start + o] = k[i];
-                dst_v[start + o] = v[i];
-                if (has_next) atomicAdd(&sh.local[0][digit_at(k[i], next_shift, next_bits)], 1u);
+            // the next pending range (written by this workgroup before the barriers above)
+            if (t == 0) {
+                sh.cur[1] = 0;
+                if (sh.depth) {
+                    const uint2 r = stack[--sh.depth];
+                    sh.cur[0] = r.x;
+                    sh.cur[1] = r.y & 0x7FFFFFFFu;
+                    sh.cur[2] = r.y >> 31;
+                }
             }
             __syncthreads();
-            if (t < kRadix) sh.local[1][t] += tot;
-        }
-        __syncthreads();
-        uint32_t* tk = src_k;
-        uint32_t* tv = src_v;
-        src_k = dst_k;
-        src_v = dst_v;
-        dst_k = tk;
-        dst_v = tv;
-    }
-    // sorted data in (src_k, src_v): (sk1, pidx) after an odd pass count, else (sk0, sv)
-    const bool in_place = src_v == pidx;
-    if (!in_place && passes == 0 && !keys64) return;   // order unchanged, pidx untouched
-    for (uint32_t c0 = 0; c0 < n; c0 += kSegMax) {
-#pragma unroll
-        for (int i = 0; i < kBigItems; ++i) {
-            const uint32_t p = c0 + (uint32_t)i * kBigThreads + t;
-            if (p >= n) continue;
-            if (!in_place) pidx[start + p] = src_v[start + p];
-            if (keys64) keys64[start + p] = ((uint64_t)tile << 32) | src_k[start + p];
+            start = sh.cur[0];
+            n = sh.cur[1];
+            buf = sh.cur[2];
+            __syncthreads();
+            if (!n) break;   // uniform
         }
     }
 }
 
-// Wave-level segment sort, for segments of up to kWaveSegMax entries: one wave per tile,
-// items in registers (item i of lane l at position 64 i + l), each pass ranks by one 8-bit
-// digit with ballots, turns the wave's 256 digit counts into bases with a wave scan and
-// reorders through the wave's own LDS region. No workgroup barrier is involved: LDS
-// operations of one wave complete in order.
-constexpr int kWaveItems = 8;
-constexpr uint32_t kWaveSegMax = kWave * kWaveItems;
-
-struct WaveSegShared {
-    uint32_t buf[4][kWaveSegMax];
-    uint32_t cnt[4][kRadix];
-};
-
-__device__ __forceinline__ void wave_sort_segment(uint32_t* __restrict__ buf, uint32_t* __restrict__ cnt,
-                                                  uint32_t tile, uint32_t start, uint32_t n,
-                                                  const uint32_t* __restrict__ zs, uint32_t* __restrict__ pidx,
-                                                  uint64_t* __restrict__ keys64) {
-    const uint32_t l = lane_id();
-    const int items = (int)((n + kWave - 1) / kWave);
-    uint32_t k[kWaveItems], v[kWaveItems], rk[kWaveItems], pos[kWaveItems];
-    uint32_t valid = 0, k_or = 0u, k_and = 0xFFFFFFFFu;
-    // loads clamped into the segment rather than predicated, so that all of them are in
-    // flight at once
-#pragma unroll
-    for (int i = 0; i < kWaveItems; ++i) {
-        const uint32_t p = (uint32_t)i * kWave + l;
-        valid |= (uint32_t)(i < items && p < n) << i;
-        v[i] = pidx[start + min(p, n - 1)];
-        k[i] = zs[start + min(p, n - 1)];
-    }
-#pragma unroll
-    for (int i = 0; i < kWaveItems; ++i) {
-        const bool ok = (valid >> i) & 1u;
-        k_or |= ok ? k[i] : 0u;
-        k_and &= ok ? k[i] : 0xFFFFFFFFu;
-    }
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        k_or |= __shfl_xor(k_or, o, kWave);
-        k_and &= __shfl_xor(k_and, o, kWave);
-    }
-    const uint32_t diff = k_or ^ k_and;
-    if (n <= kWave && diff) {
-        // one entry per lane: the rank is the number of smaller keys plus the number of
-        // equal keys at lower positions (about four instructions per entry)
-        const uint32_t key = k[0];
-        uint32_t rank = 0;
-        for (uint32_t j = 0; j < n; ++j) {
-            const uint32_t kj = __builtin_amdgcn_readlane(key, (int)j);
-            rank += (kj < key || (kj == key && j < l)) ? 1u : 0u;
-        }
-        if (valid & 1u) {
-            pidx[start + rank] = v[0];
-            if (keys64) keys64[start + rank] = ((uint64_t)tile << 32) | key;
-        }
-        return;
-    }
-    // uniform by construction; readfirstlane tells the compiler, so the digit loops branch
-    // on scalars
-    const int lo = __builtin_amdgcn_readfirstlane(diff ? __builtin_ctz(diff) : 0);
-    const int hi = __builtin_amdgcn_readfirstlane(diff ? 32 - __builtin_clz(diff) : 0);
-    const Split8 split(lo, hi);
-    for (int pass = 0; pass < split.passes; ++pass) {
-        const int shift = split.shift(pass), bits = kRadixBits;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cnt[4 * l + q] = 0u;
-        __builtin_amdgcn_wave_barrier();
-        wave_rank<kWaveItems>(k, shift, bits, valid, items, cnt, rk);
-        __builtin_amdgcn_wave_barrier();
-        // lane l owns digits 4l .. 4l+3: counts -> exclusive bases
-        const uint32_t c0 = cnt[4 * l], c1 = cnt[4 * l + 1], c2 = cnt[4 * l + 2], c3 = cnt[4 * l + 3];
-        const uint32_t sum = c0 + c1 + c2 + c3;
-        const uint32_t ex = wave_inclusive_scan(sum) - sum;
-        __builtin_amdgcn_wave_barrier();
-        cnt[4 * l] = ex;
-        cnt[4 * l + 1] = ex + c0;
-        cnt[4 * l + 2] = ex + c0 + c1;
-        cnt[4 * l + 3] = ex + c0 + c1 + c2;
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < kWaveItems; ++i) {
-            if ((valid >> i) & 1u) {
-                pos[i] = cnt[digit_at(k[i], shift, bits)] + rk[i];
-                buf[pos[i]] = k[i];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < kWaveItems; ++i)
-            if ((valid >> i) & 1u) k[i] = buf[(uint32_t)i * kWave + l];
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < kWaveItems; ++i)
-            if ((valid >> i) & 1u) buf[pos[i]] = v[i];
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < kWaveItems; ++i)
-            if ((valid >> i) & 1u) v[i] = buf[(uint32_t)i * kWave + l];
-        __builtin_amdgcn_wave_barrier();
-    }
-#pragma unroll
-    for (int i = 0; i < kWaveItems; ++i) {
-        if (!((valid >> i) & 1u)) continue;
-        const uint32_t p = (uint32_t)i * kWave + l;
-        if (hi > lo) pidx[start + p] = v[i];
-        if (keys64) keys64[start + p] = ((uint64_t)tile << 32) | k[i];
-    }
-}
-
-// The long segments are listed for step 6b by size class: class 0 up to kSegMax entries
-// (sorted by a whole workgroup), class 1 up to kSegMax / 2 (two at once), class 2 up to
-// kSegMax / 4 (four at once). Each class has kLongLists lists, tile t in list t mod
-// kLongLists, each with its own counter on its own 128-byte line: appends to one
-// device-wide counter are serialised in memory (the XCDs' L2s are not coherent), while
-// appends to different lines proceed in parallel. List j of class c is list c kLongLists + j
-// at (c kLongLists + j) * per words.
-constexpr uint32_t kLongLists = 64;
-constexpr uint32_t kClasses = 3;
-constexpr uint32_t kClassLists = kClasses * kLongLists;
-constexpr uint32_t kLongCounterStride = 32;   // words: one counter per 128-byte line
-// Segments longer than kSegMax (sorted through the workspace, several times the work of
-// the others) go to one more list, at kClassLists * per words, counted in counter slot
-// kHugeSlot; slot kWorkSlot is the work counter of step 6b. Segments longer than kChunkMin
-// are sorted by all workgroups together (step 6c): they are listed after that, at
-// kClassLists * per + tiles words, counted in slot kChunkSlot; slot kChunkTotalSlot receives
-// their number of 4096-entry chunks.
-constexpr uint32_t kHugeSlot = kClassLists, kWorkSlot = kClassLists + 1, kChunkSlot = kClassLists + 2,
-                   kChunkTotalSlot = kClassLists + 3, kLongCounters = kClassLists + 4;
-constexpr uint32_t kChunkMin = 16384;
-
-// Size class of a segment of kWaveSegMax < n <= kSegMax entries.
-__device__ __forceinline__ uint32_t seg_class(uint32_t n) {
-    return n > kSegMax / 2 ? 0u : n > kSegMax / 4 ? 1u : 2u;
-}
-
-// Step 6a: one wave per tile sorts segments of up to kWaveSegMax entries and appends the
-// longer ones to the lists for step 6b.
-__global__ void __launch_bounds__(kSortThreads) segment_sort_small_kernel(
-    const uint32_t* __restrict__ ranges, uint32_t tiles_total, const uint32_t* __restrict__ zs,
-    uint32_t* __restrict__ pidx, uint64_t* __restrict__ keys64, const uint32_t* __restrict__ count_p,
-    uint64_t capacity, const int32_t* __restrict__ status, uint32_t* __restrict__ long_lists,
-    uint32_t* __restrict__ long_counts) {
-    __shared__ WaveSegShared sh;
-    if (*status != kStatusOk) return;
-    if ((uint64_t)*count_p > capacity) return;
-    const uint32_t w = threadIdx.x >> 6;
-    const uint32_t tile = 4 * xcd_swizzle(blockIdx.x, gridDim.x) + w;
-    if (tile >= tiles_total) return;
-    const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
-    if (end <= start) return;
-    const uint32_t n = end - start;
-    if (n > kWaveSegMax) {
-        if (lane_id() == 0) {
-            const uint32_t per = (tiles_total + kLongLists - 1) / kLongLists;
-            if (n > kChunkMin) {
-                long_lists[kClassLists * per + tiles_total +
-                           atomicAdd(&long_counts[kChunkSlot * kLongCounterStride], 1u)] = tile;
-            } else {
-                const uint32_t j = n > kSegMax ? kHugeSlot : seg_class(n) * kLongLists + tile % kLongLists;
-                long_lists[j * per + atomicAdd(&long_counts[j * kLongCounterStride], 1u)] = tile;
-            }
-        }
-        return;
-    }
-    wave_sort_segment(sh.buf[w], sh.cnt[w], tile, start, n, zs, pidx, keys64);
-}
-
-// Tile of item r of class c: list j holds the class's items [first[j], first[j + 1]), so j
-// is the number of lists that end at or before r (one ballot of the wave).
-__device__ __forceinline__ uint32_t class_item(const uint32_t* __restrict__ long_lists, uint32_t per, uint32_t c,
-                                               const uint32_t* first, uint32_t r) {
-    const uint32_t j = (uint32_t)__popcll(ballot64(first[lane_id() + 1] <= r));
-    return long_lists[(c * kLongLists + j) * per + (r - first[j])];
-}
-
-// Step 6b: a resident grid sorts the listed long segments, with stable LSD radix passes: in
-// LDS up to kSegMax entries, through the workspace beyond. Workgroups take the next item
-// from a device-wide counter (one atomic per item: a few thousand per call, against tens of
-// microseconds of work each), the longest segments first, so that no workgroup is left with
-// a run of long ones while the others have finished: the segments sorted through the
-// workspace, then class 0 one per item, class 1 two per item, class 2 four per item. The
-// sort is bound by its ballot chains and the latency of its barriers, not by bytes, so the
-// kernel is held to 80 VGPRs: three workgroups per CU (at 64 the group sort spills to
-// scratch memory, without a limit two workgroups fit).
-__global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(6))) segment_sort_big_kernel(
-    const uint32_t* __restrict__ ranges, uint32_t tiles_total, const uint32_t* __restrict__ zs,
-    uint32_t* __restrict__ pidx, uint64_t* __restrict__ keys64, const uint32_t* __restrict__ count_p,
-    uint64_t capacity, const int32_t* __restrict__ status, const uint32_t* __restrict__ long_lists,
-    uint32_t* __restrict__ long_counts, uint32_t* __restrict__ sk0, uint32_t* __restrict__ sk1,
-    uint32_t* __restrict__ sv) {
-    __shared__ SegShared sh;
-    __shared__ uint32_t s_first[kClasses][kLongLists + 1];   // each list's first item within its class
-    __shared__ uint32_t s_item;
-    if (*status != kStatusOk) return;
-    if ((uint64_t)*count_p > capacity) return;
-    const uint32_t t = threadIdx.x;
-    static_assert(kLongLists == kWave, "one lane per list");
-    if (t < kClasses * kWave) {
-        const uint32_t c = t / kWave, lane = lane_id();
-        const uint32_t incl = wave_inclusive_scan(long_counts[(c * kLongLists + lane) * kLongCounterStride]);
-        s_first[c][lane + 1] = incl;
-        if (lane == 0) s_first[c][0] = 0u;
-    }
-    __syncthreads();
-    const uint32_t per = (tiles_total + kLongLists - 1) / kLongLists;
-    const uint32_t n_huge = long_counts[kHugeSlot * kLongCounterStride];
-    const uint32_t n0 = s_first[0][kLongLists], n1 = s_first[1][kLongLists], n2 = s_first[2][kLongLists];
-    const uint32_t e0 = n_huge + n0, e1 = e0 + (n1 + 1) / 2, total = e1 + (n2 + 3) / 4;
-    uint32_t* work = long_counts + kWorkSlot * kLongCounterStride;
-    const uint32_t w = t >> 6;
-    for (;;) {
-        if (t == 0) s_item = atomicAdd(work, 1u);
-        __syncthreads();
-        const uint32_t i = s_item;
-        if (i >= total) break;   // uniform: every thread read the same item
-        if (i < n_huge) {
-            const uint32_t tile = long_lists[kHugeSlot * per + i];
-            const uint32_t start = ranges[2 * tile], n = ranges[2 * tile + 1] - start;
-            segment_sort_global(sh, tile, start, n, zs, pidx, keys64, sk0, sk1, sv);
-        } else {
-            // class 0: one segment per item (groups of 8 waves), class 1: two (4 waves each),
-            // class 2: four (2 waves each)
-            const uint32_t c = i < e0 ? 0u : i < e1 ? 1u : 2u;
-            const uint32_t G = kBigWaves >> c;
-            const uint32_t r = c == 0 ? i - n_huge : c == 1 ? 2 * (i - e0) + w / G : 4 * (i - e1) + w / G;
-            const uint32_t nc = c == 0 ? n0 : c == 1 ? n1 : n2;
-            uint32_t tile = 0, start = 0, n = 0;
-            if (r < nc) {
-                tile = class_item(long_lists, per, c, s_first[c], r);
-                start = ranges[2 * tile];
-                n = ranges[2 * tile + 1] - start;
-            }
-            segment_sort_groups(sh, G, tile, start, n, zs, pidx, keys64);
-        }
-        __syncthreads();   // also orders every read of s_item before the next write
-    }
-}
-
-// Step 6c: the segments longer than kChunkMin, sorted by every workgroup together: each is
-// cut into 4096-entry chunks and sorted by stable LSD passes over the four bytes of the
-// depth bits, each pass as count (a digit histogram per chunk), scan (per segment: for each
-// digit, the prefix over its chunks, placed after the smaller digits' entries) and scatter
-// (each chunk ranks its entries per digit with ballots and writes them to their places,
-// reordered in LDS into runs). A pass whose byte is the same for every entry of a segment
-// would leave it unchanged: the scan marks it skipped and the segment stays where it is, so
-// each segment keeps its own record of which buffer holds it. Buffers: A = (depth bits,
-// pidx) as the tile passes left them, B = workspace. The grids are resident and stride over
-// the chunks (or segments); with no long segment every kernel leaves at once.
-struct ChunkPlan {
-    uint32_t* seg_start;    // [h] first entry of segment s
-    uint32_t* seg_n;        // [h] its length
-    uint32_t* chunk_first;  // [h + 1] index of its first chunk
-    uint32_t* seg_loc;      // [5][h] buffer holding segment s before pass p (0 = A, 1 = B)
-    uint32_t* seg_tile;     // [h] its tile
-    uint32_t* chunk_seg;    // [chunks] segment of each chunk
-    uint32_t* cnt;          // [chunks][kRadix] digit counts, then output bases
-    uint32_t h_max;
-};
-
-// One workgroup: the segment table, the chunk table and the chunk total.
-__global__ void __launch_bounds__(256) chunk_setup_kernel(const uint32_t* __restrict__ ranges, uint32_t tiles_total,
-                                                          const uint32_t* __restrict__ long_lists,
-                                                          uint32_t* __restrict__ long_counts, ChunkPlan cp) {
-    __shared__ uint32_t s_tmp[4];
-    const uint32_t per = (tiles_total + kLongLists - 1) / kLongLists;
-    const uint32_t h = min(long_counts[kChunkSlot * kLongCounterStride], cp.h_max);
-    const uint32_t* list = long_lists + kClassLists * per + tiles_total;
-    uint32_t carry = 0;
-    for (uint32_t s0 = 0; s0 < h; s0 += 256) {
-        const uint32_t sid = s0 + threadIdx.x;
-        uint32_t start = 0, n = 0, tile = 0;
-        if (sid < h) {
-            tile = list[sid];
-            start = ranges[2 * tile];
-            n = ranges[2 * tile + 1] - start;
-        }
-        const uint32_t nch = (n + kSortTile - 1) / kSortTile;
-        uint32_t total;
-        const uint32_t first = carry + block_exclusive_scan(nch, s_tmp, total);
-        if (sid < h) {
-            cp.seg_start[sid] = start;
-            cp.seg_n[sid] = n;
-            cp.seg_tile[sid] = tile;
-            cp.chunk_first[sid] = first;
-            cp.seg_loc[sid] = 0u;
-            for (uint32_t c = 0; c < nch; ++c) cp.chunk_seg[first + c] = sid;
-        }
-        carry += total;
-    }
-    if (threadIdx.x == 0) {
-        cp.chunk_first[h] = carry;
-        long_counts[kChunkTotalSlot * kLongCounterStride] = carry;
-    }
-}
-
-__device__ __forceinline__ uint32_t chunk_count_of(const uint32_t* long_counts) {
-    return long_counts[kChunkTotalSlot * kLongCounterStride];
-}
-
-// Entries [lo, hi) of chunk c, its segment and the buffer holding it before pass p.
-struct ChunkSpan {
-    uint32_t s, lo, hi, loc;
-};
-
-__device__ __forceinline__ ChunkSpan chunk_span(const ChunkPlan& cp, uint32_t c, int pass) {
-    ChunkSpan r;
-    r.s = cp.chunk_seg[c];
-    const uint32_t start = cp.seg_start[r.s], end = start + cp.seg_n[r.s];
-    r.lo = start + (c - cp.chunk_first[r.s]) * kSortTile;
-    r.hi = min(r.lo + kSortTile, end);
-    r.loc = cp.seg_loc[pass * cp.h_max + r.s];
-    return r;
-}
-
-__global__ void __launch_bounds__(kSortThreads) chunk_count_kernel(const uint32_t* __restrict__ a_key,
-                                                                   const uint32_t* __restrict__ b_key,
-                                                                   const uint32_t* __restrict__ long_counts,
-                                                                   ChunkPlan cp, int pass) {
-    __shared__ uint32_t s_h[kRadix];
-    const uint32_t nc = chunk_count_of(long_counts), t = threadIdx.x;
-    const int shift = 8 * pass;
-    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
-        const ChunkSpan sp = chunk_span(cp, c, pass);
-        const uint32_t* key = sp.loc ? b_key : a_key;
-        s_h[t] = 0u;
-        // all of the chunk's loads in flight at once (clamped into the chunk), then the counts
-        uint32_t k[kSortItems];
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) k[i] = key[min(sp.lo + i * kSortThreads + t, sp.hi - 1)];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            if (sp.lo + i * kSortThreads + t >= sp.hi) continue;
-            const uint32_t d = digit_at(k[i], shift, 8);
-            // a byte shared by the whole wave (the leading bytes of close depths): one add
-            const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
-            const uint64_t act = ballot64(true);
-            if (ballot64(d != d0) == 0) {
-                if (lane_id() == (uint32_t)__builtin_ctzll(act)) atomicAdd(&s_h[d0], (uint32_t)__popcll(act));
-            } else {
-                atomicAdd(&s_h[d], 1u);
-            }
-        }
-        __syncthreads();
-        cp.cnt[(size_t)c * kRadix + t] = s_h[t];
-        __syncthreads();
-    }
-}
-
-// One segment per workgroup iteration, thread d for digit d.
-__global__ void __launch_bounds__(256) chunk_scan_kernel(const uint32_t* __restrict__ long_counts, ChunkPlan cp,
-                                                         int pass) {
-    __shared__ uint32_t s_tmp[4];
-    __shared__ uint32_t s_nz[4];
-    static_assert(kRadix == 256, "one thread per digit");
-    const uint32_t h = min(long_counts[kChunkSlot * kLongCounterStride], cp.h_max), d = threadIdx.x;
-    for (uint32_t sid = blockIdx.x; sid < h; sid += gridDim.x) {
-        const uint32_t c0 = cp.chunk_first[sid], c1 = cp.chunk_first[sid + 1];
-        uint32_t run = 0;
-        for (uint32_t c = c0; c < c1; ++c) {
-            const uint32_t x = cp.cnt[(size_t)c * kRadix + d];
-            cp.cnt[(size_t)c * kRadix + d] = run;
-            run += x;
-        }
-        // a byte the same for every entry: the pass would not move anything
-        const uint32_t nz = (uint32_t)__popcll(ballot64(run != 0u));
-        if (lane_id() == 0) s_nz[d >> 6] = nz;
-        uint32_t total;
-        const uint32_t base = block_exclusive_scan(run, s_tmp, total) + cp.seg_start[sid];
-        const bool skip = s_nz[0] + s_nz[1] + s_nz[2] + s_nz[3] <= 1u;
-        const uint32_t loc = cp.seg_loc[pass * cp.h_max + sid];
-        if (d == 0) cp.seg_loc[(pass + 1) * cp.h_max + sid] = skip ? loc : loc ^ 1u;
-        if (!skip)
-            for (uint32_t c = c0; c < c1; ++c) cp.cnt[(size_t)c * kRadix + d] += base;
-        __syncthreads();   // s_nz and s_tmp are reused by the next segment
-    }
-}
-
-__global__ void __launch_bounds__(kSortThreads) chunk_scatter_kernel(uint32_t* __restrict__ a_key,
-                                                                     uint32_t* __restrict__ a_val,
-                                                                     uint32_t* __restrict__ b_key,
-                                                                     uint32_t* __restrict__ b_val,
-                                                                     const uint32_t* __restrict__ long_counts,
-                                                                     ChunkPlan cp, int pass) {
-    __shared__ uint32_t s_buf[kSortTile];
-    __shared__ uint32_t s_wcnt[4][kRadix];
-    __shared__ uint32_t s_local[kRadix];
-    __shared__ uint32_t s_base[kRadix];
-    __shared__ uint32_t s_tmp[4];
-    const uint32_t nc = chunk_count_of(long_counts), t = threadIdx.x, w = t >> 6, lane = t & 63;
-    const int shift = 8 * pass;
-    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
-        const ChunkSpan sp = chunk_span(cp, c, pass);
-        const uint32_t loc_next = cp.seg_loc[(pass + 1) * cp.h_max + sp.s];
-        if (loc_next == sp.loc) continue;   // skipped pass: uniform over the workgroup
-        const uint32_t* skey = sp.loc ? b_key : a_key;
-        const uint32_t* sval = sp.loc ? b_val : a_val;
-        uint32_t* dkey = sp.loc ? a_key : b_key;
-        uint32_t* dval = sp.loc ? a_val : b_val;
-        const uint32_t n_here = sp.hi - sp.lo;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) s_wcnt[k][t] = 0u;
-        // wave w owns chunk positions [w * 1024, +1024), item i of lane l at i * 64 + l;
-        // positions past the chunk's end carry the all-ones key (largest digit, placed last)
-        uint32_t k[kSortItems], v[kSortItems], rk[kSortItems];
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const uint32_t j = w * (kSortTile / 4) + i * kWave + lane;
-            const uint32_t idx = sp.lo + min(j, n_here - 1);
-            k[i] = j < n_here ? skey[idx] : 0xFFFFFFFFu;
-            v[i] = sval[idx];
-        }
-        s_base[t] = cp.cnt[(size_t)c * kRadix + t];
-        __syncthreads();
-        wave_rank<kSortItems>(k, shift, kRadixBits, 0xFFFFFFFFu, kSortItems, s_wcnt[w], rk);
-        __syncthreads();
-        const uint32_t c0 = s_wcnt[0][t], c1 = s_wcnt[1][t], c2 = s_wcnt[2][t], c3 = s_wcnt[3][t];
-        s_wcnt[0][t] = 0u;
-        s_wcnt[1][t] = c0;
-        s_wcnt[2][t] = c0 + c1;
-        s_wcnt[3][t] = c0 + c1 + c2;
-        uint32_t tot;
-        const uint32_t lb = block_exclusive_scan(c0 + c1 + c2 + c3, s_tmp, tot);
-        s_local[t] = lb;
-        __syncthreads();
-        uint32_t lpos[kSortItems];
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const uint32_t d = digit_at(k[i], shift, kRadixBits);
-            lpos[i] = s_local[d] + s_wcnt[w][d] + rk[i];
-            s_buf[lpos[i]] = k[i];
-        }
-        __syncthreads();
-        // runs per digit: position j of the reordered chunk goes to base[d] + (j - local[d])
-        uint32_t dig[kSortItems];
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const uint32_t j = t + i * kSortThreads;
-            const uint32_t key = s_buf[j];
-            dig[i] = digit_at(key, shift, kRadixBits);
-            if (j < n_here) dkey[s_base[dig[i]] + (j - s_local[dig[i]])] = key;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) s_buf[lpos[i]] = v[i];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const uint32_t j = t + i * kSortThreads;
-            if (j < n_here) dval[s_base[dig[i]] + (j - s_local[dig[i]])] = s_buf[j];
-        }
-        __syncthreads();   // LDS is reused by the next chunk
-    }
-}
-
-// The sorted segments into pidx (those left in B) and keys64.
-__global__ void __launch_bounds__(256) chunk_final_kernel(const uint32_t* __restrict__ b_key,
-                                                          const uint32_t* __restrict__ b_val,
-                                                          const uint32_t* __restrict__ a_key,
-                                                          uint32_t* __restrict__ pidx, uint64_t* __restrict__ keys64,
-                                                          const uint32_t* __restrict__ long_counts, ChunkPlan cp) {
-    const uint32_t nc = chunk_count_of(long_counts);
-    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
-        const ChunkSpan sp = chunk_span(cp, c, 4);
-        if (!sp.loc && !keys64) continue;   // already in place
-        const uint64_t tile = cp.seg_tile[sp.s];
-        const uint32_t* key = sp.loc ? b_key : a_key;
-        static_assert(kSortTile == 16 * 256, "sixteen entries per thread");
-        uint32_t v[16], k[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t j = min(sp.lo + i * 256 + threadIdx.x, sp.hi - 1);
-            v[i] = sp.loc ? b_val[j] : 0u;
-            k[i] = keys64 ? key[j] : 0u;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t j = sp.lo + i * 256 + threadIdx.x;
-            if (j >= sp.hi) continue;
-            if (sp.loc) pidx[j] = v[i];
-            if (keys64) keys64[j] = (tile << 32) | k[i];
-        }
-    }
-}
+// ---- Host -----------------------------------------------------------------------------------------
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, int32_t nv, uint64_t capacity) {
+static uint32_t view_tiles(const isogs_camera& c) {
+    return (uint32_t)((c.width + kTile - 1) / kTile) * (uint32_t)((c.height + kTile - 1) / kTile);
+}
+
+// The chunking of a call: particles per chunk. Two workgroups of 1024 threads fit a CU (one with
+// the larger band), so the chunks of all views together are at most what runs at once: 512, or
+// 256 where fewer particles are worth less than the matrix rows (4 bytes per tile of the view)
+// that more chunks cost.
+static uint32_t chunk_particles(uint64_t n_total, int32_t nv, bool large_band) {
+    const uint32_t least = n_total <= kGroupMaxParticles ? 128u : 1024u;
+    const uint32_t target = large_band || n_total < 4000000 ? kMaxChunks / 2 : kMaxChunks;
+    const uint32_t rows = std::max(target - std::min<uint32_t>((uint32_t)nv, target / 2), 1u);
+    return (uint32_t)std::max<uint64_t>(least, (n_total + rows - 1) / rows);
+}
+
+BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, int32_t nv, uint64_t capacity,
+                          size_t limit) {
     BinSortPlan p{};
     p.capacity = capacity;
     uint64_t n = 0, tiles = 0;
+    uint32_t most_tiles = 0;
     for (int v = 0; v < nv; ++v) {
         n += (uint64_t)n_per_view[v];
-        tiles += (uint64_t)((cams[v].width + kTile - 1) / kTile) * (uint64_t)((cams[v].height + kTile - 1) / kTile);
+        tiles += view_tiles(cams[v]);
+        most_tiles = std::max(most_tiles, view_tiles(cams[v]));
     }
     p.n_total = (uint32_t)n;
     p.tiles_total = (uint32_t)tiles;
-    // 2^tile_bits > tiles: the sentinel id 0xFFFFFFFF, cut to the sorted bits, still sorts
-    // after every real tile id
-    int tile_bits = 0;
-    while (tile_bits < 32 && (1ull << tile_bits) <= tiles) ++tile_bits;
-    p.passes = DigitSplit(0, tile_bits, kTileRadixBits).passes;
-    p.tile_bits = tile_bits;
-    p.sort_tiles = (uint32_t)((capacity + kSortTile - 1) / kSortTile);
-    p.scan_blocks = (uint32_t)((n + kScanBlock - 1) / kScanBlock);
-    size_t off = 0;
-    p.off_keys_a = off;     off = align256(off + capacity * 4);
-    p.off_keys_b = off;     off = align256(off + capacity * 4);
-    p.off_vals_alt = off;   off = align256(off + capacity * 4);
-    p.off_z_a = off;        off = align256(off + capacity * 4);
-    p.off_z_b = off;        off = align256(off + capacity * 4);
-    // zero-initialised region: the digit totals of the passes and the long-segment counts
-    p.off_hist = off;       off += (size_t)kMaxPasses * kTileRadix * 4;
-    p.off_long_counts = off; off = align256(off + (size_t)kLongCounters * kLongCounterStride * 4);
-    p.off_block_sums = off; off = align256(off + (size_t)(p.scan_blocks + 1) * 4);
-    // kClassLists lists of at most `per` tiles, the list of the segments sorted through the
-    // workspace, the list of the chunk-sorted ones
-    p.off_long_lists = off; off = align256(off + (size_t)(5 * tiles + 2 * kClassLists) * 4);
-    // the chunk sort's tables: at most h_max segments (longer than kChunkMin each) and
-    // capacity / 4096 + h_max chunks
-    p.chunk_h_max = (uint32_t)std::min<uint64_t>(tiles, capacity / (kChunkMin + 1) + 1);
-    p.chunk_max = (uint32_t)(capacity / kSortTile + p.chunk_h_max);
-    p.off_chunk_tables = off; off = align256(off + (size_t)(10 * (uint64_t)p.chunk_h_max + 1) * 4);
-    p.off_chunk_seg = off;   off = align256(off + (size_t)p.chunk_max * 4);
-    p.off_chunk_cnt = off;   off = align256(off + (size_t)p.chunk_max * kRadix * 4);
-    p.off_tcount = off;     off = align256(off + (size_t)p.sort_tiles * kTileRadix * 4);
-    p.bytes = off;
+    p.large_band = most_tiles > kBandSmall;
+    // The size that callers are told: 20 bytes per entry of capacity and tile, a tile digit
+    // histogram per 4096 entries and the tables of the long segments. The layout below takes
+    // less for all but scenes of many more particles than entries; a caller whose workspace
+    // cannot grow (`limit`) then gets a layout without the packed boxes (step 4 reads the
+    // records again), or also with one chunk per view, which never takes more.
+    const uint64_t sort_tiles = (capacity + 4095) / 4096, long_max = std::min<uint64_t>(tiles, capacity / 16385 + 1);
+    const size_t told = 5 * align256(capacity * 4) + (size_t)sort_tiles * 2048 + (size_t)(sort_tiles + long_max) * 1028 +
+                        (size_t)long_max * 40 + (size_t)tiles * 20 + (n + 2047) / 2048 * 4 + 40960;
+    for (int small = 0;; ++small) {
+        p.per = small > 1 ? 0x7FFFFFFFu : chunk_particles(n, nv, p.large_band);
+        uint64_t chunks = 0, blocks = 0, m = 0;
+        for (int v = 0; v < nv; ++v) {
+            const uint64_t c = ((uint64_t)n_per_view[v] + p.per - 1) / p.per, vt = view_tiles(cams[v]);
+            chunks += c;
+            blocks += (vt + 1 + kColTiles - 1) / kColTiles;
+            m += c * (vt + 1);
+        }
+        p.chunks = (uint32_t)chunks;
+        p.blocks = (uint32_t)blocks;
+        p.list_max = (uint32_t)std::min<uint64_t>(tiles, capacity / kSmallMax + 1);
+        p.large_max = (uint32_t)std::min<uint64_t>(tiles, capacity / kBigMax + 1);
+        // pieces of step 5: at most six per 4096 entries of a level and one more, a few levels
+        p.item_max = (uint32_t)(64 * (capacity / kBigMax + 1));
+        size_t off = 0;
+        auto take = [&off](size_t bytes) {
+            const size_t at = off;
+            off = align256(off + bytes);
+            return at;
+        };
+        p.off_key = take(capacity * 8);
+        p.off_z = take(capacity * 4);
+        p.off_box = take(small ? 0 : n * 8);
+        p.boxes = !small;
+        p.off_m = take(m * 4);
+        p.off_tile_pre = take(tiles * 4);
+        p.off_tile_tot = take(tiles * 4);
+        p.off_missing = take((size_t)nv * 8);
+        p.off_block_sum = take(blocks * 4);
+        p.off_chunk_sum = take(chunks * 8);
+        p.off_counters = take(kCounterWords * 4);
+        p.off_lists = take((size_t)p.list_max * 8 + (size_t)p.large_max * sizeof(SortItem) + 16);
+        p.off_items = take((size_t)p.item_max * 2 * sizeof(SortItem));
+        p.off_stack = take((capacity / kBigMax + 2) * 8);
+        p.bytes = std::max(off, told);
+        if (p.bytes <= limit || small == 2 || told > limit) break;
+    }
     return p;
 }
 
 int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const int32_t* n_per_view,
                     const isogs_camera* cams, int32_t nv, const isogs_bins* bins, void* ws, hipStream_t stream) {
     char* base = static_cast<char*>(ws);
-    uint32_t* keys_a = reinterpret_cast<uint32_t*>(base + plan.off_keys_a);
-    uint32_t* keys_b = reinterpret_cast<uint32_t*>(base + plan.off_keys_b);
-    uint32_t* vals_alt = reinterpret_cast<uint32_t*>(base + plan.off_vals_alt);
-    uint32_t* z_a = reinterpret_cast<uint32_t*>(base + plan.off_z_a);
-    uint32_t* z_b = reinterpret_cast<uint32_t*>(base + plan.off_z_b);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(base + plan.off_hist);
-    uint32_t* tcount = reinterpret_cast<uint32_t*>(base + plan.off_tcount);
-    uint32_t* block_sums = reinterpret_cast<uint32_t*>(base + plan.off_block_sums);
+    auto at = [base](size_t off) { return reinterpret_cast<uint32_t*>(base + off); };
+    BinArrays A{};
+    A.key = reinterpret_cast<uint64_t*>(base + plan.off_key);
+    A.z_alt = at(plan.off_z);
+    A.box = plan.boxes ? reinterpret_cast<uint2*>(base + plan.off_box) : nullptr;
+    A.m = at(plan.off_m);
+    A.tile_pre = at(plan.off_tile_pre);
+    A.tile_tot = at(plan.off_tile_tot);
+    A.missing = at(plan.off_missing);
+    A.missing_at = A.missing + nv;
+    A.block_sum = at(plan.off_block_sum);
+    A.chunk_sum = reinterpret_cast<uint64_t*>(base + plan.off_chunk_sum);
+    A.counters = at(plan.off_counters);
+    A.large = reinterpret_cast<SortItem*>(base + plan.off_lists);
+    A.mid = reinterpret_cast<uint32_t*>(A.large + plan.large_max);
+    A.big = A.mid + plan.list_max;
+    A.mid_item = reinterpret_cast<SortItem*>(base + plan.off_items);
+    A.big_item = A.mid_item + plan.item_max;
+    A.stack = reinterpret_cast<uint2*>(base + plan.off_stack);
+    A.list_max = plan.list_max;
+    A.large_max = plan.large_max;
+    A.item_max = plan.item_max;
+    A.blocks = plan.blocks;
+    A.chunks = plan.chunks;
+    A.views = (uint32_t)nv;
+    const float4* record = reinterpret_cast<const float4*>(proj->record);
+    const bool group = plan.n_total <= kGroupMaxParticles;
+    const uint32_t band = plan.large_band ? kBandLarge : kBandSmall;
 
-    // 1. zero ranges and the sort's bookkeeping
-    {
-        const size_t nz = (plan.off_block_sums - plan.off_hist) / 4;
-        hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)std::min<size_t>(1024, (nz + 255) / 256 + 1)), dim3(256), 0,
-                           stream, hist, nz, 0u);
-        const size_t nr = (size_t)plan.tiles_total * 2;
-        if (nr)
-            hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)std::min<size_t>(1024, (nr + 255) / 256)), dim3(256), 0,
-                               stream, bins->ranges, nr, 0u);
-    }
-    // 2. scan of tile counts
-    const uint32_t n = plan.n_total;
-    if (plan.scan_blocks) {
-        hipLaunchKernelGGL(scan_reduce_kernel, dim3(plan.scan_blocks), dim3(kScanThreads), 0, stream,
-                           proj->tile_count, n, block_sums);
-    }
-    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(kScanThreads), 0, stream, block_sums, plan.scan_blocks,
-                       plan.capacity, bins->count, bins->status);
-    if (plan.scan_blocks) {
-        hipLaunchKernelGGL(scan_down_kernel, dim3(plan.scan_blocks), dim3(kScanThreads), 0, stream,
-                           proj->tile_count, n, block_sums, bins->offsets);
-    }
-    if (hipPeekAtLastError() != hipSuccess) return -1;
-
-    // ping-pong so that the last tile pass lands the values in the caller's pidx
-    const bool odd = plan.passes & 1;
-    uint32_t* v_emit = odd ? vals_alt : bins->pidx;
-    uint32_t* v_other = odd ? bins->pidx : vals_alt;
-
-    // 3. emit (per group of views)
-    const DigitSplit tsplit(0, plan.tile_bits, kTileRadixBits);
-    uint32_t p_off = 0, tile_base = 0;
-    for (int v0 = 0; v0 < nv; v0 += kMaxViews) {
-        ViewPack pk{};
-        pk.nv = min(kMaxViews, nv - v0);
-        uint32_t blocks = 0;
-        for (int j = 0; j < pk.nv; ++j) {
-            const isogs_camera& cam = cams[v0 + j];
-            ViewDesc& d = pk.v[j];
-            d.p_off = p_off;
-            d.n = (uint32_t)n_per_view[v0 + j];
-            d.tile_base = tile_base;
-            d.width = cam.width;
-            d.height = cam.height;
-            d.tiles_x = (cam.width + kTile - 1) / kTile;
-            d.tiles_y = (cam.height + kTile - 1) / kTile;
-            pk.block_begin[j] = blocks;
-            blocks += (d.n + 255u) / 256u;
-            p_off += d.n;
-            tile_base += (uint32_t)(d.tiles_x * d.tiles_y);
+    // groups of up to kMaxViews views: counts and columns, then (all views) the scans, then
+    // placement
+    int32_t most = 0;
+    for (int stage = 0; stage < 2; ++stage) {
+        uint32_t p_off = 0, tile_base = 0, chunk0 = 0, block0 = 0;
+        uint64_t m_off = 0;
+        for (int v0 = 0; v0 < nv; v0 += kMaxViews) {
+            BinPack pk{};
+            pk.nv = min(kMaxViews, nv - v0);
+            pk.view0 = (uint32_t)v0;
+            pk.tile0 = tile_base;
+            uint32_t chunks = 0, blocks = 0, bands = 1;
+            for (int j = 0; j < pk.nv; ++j) {
+                const isogs_camera& cam = cams[v0 + j];
+                BinView& d = pk.v[j];
+                d.p_off = p_off;
+                d.n = (uint32_t)n_per_view[v0 + j];
+                d.tile_base = tile_base;
+                d.width = cam.width;
+                d.height = cam.height;
+                d.tiles_x = (cam.width + kTile - 1) / kTile;
+                d.tiles_y = (cam.height + kTile - 1) / kTile;
+                d.tiles = view_tiles(cam);
+                d.per = plan.per;
+                d.chunks = (uint32_t)(((uint64_t)d.n + plan.per - 1) / plan.per);
+                d.chunk0 = chunk0;
+                d.block0 = block0;
+                d.m_off = m_off;
+                pk.chunk_begin[j] = chunks;
+                pk.block_begin[j] = blocks;
+                chunks += d.chunks;
+                blocks += (d.tiles + 1 + kColTiles - 1) / kColTiles;
+                bands = std::max(bands, (d.tiles + band - 1) / band);
+                most = std::max(most, n_per_view[v0 + j]);
+                p_off += d.n;
+                tile_base += d.tiles;
+                chunk0 += d.chunks;
+                block0 += (d.tiles + 1 + kColTiles - 1) / kColTiles;
+                m_off += (uint64_t)d.chunks * (d.tiles + 1);
+            }
+            pk.chunk_begin[pk.nv] = chunks;
+            pk.block_begin[pk.nv] = blocks;
+            pk.tiles = tile_base - pk.tile0;
+            if (stage == 0) {
+                auto count = plan.large_band ? (group ? bin_count_kernel<kBandLarge, 8> : bin_count_kernel<kBandLarge, 1>)
+                                             : (group ? bin_count_kernel<kBandSmall, 8> : bin_count_kernel<kBandSmall, 1>);
+                if (chunks)
+                    hipLaunchKernelGGL(count, dim3(chunks, bands), dim3(kBinThreads), 0, stream, pk, record,
+                                       proj->tile_count, A);
+                hipLaunchKernelGGL(bin_columns_kernel, dim3(blocks), dim3(kBinThreads), 0, stream, pk, A);
+            } else {
+                auto place = plan.large_band ? (group ? bin_place_kernel<kBandLarge, 8> : bin_place_kernel<kBandLarge, 1>)
+                                             : (group ? bin_place_kernel<kBandSmall, 8> : bin_place_kernel<kBandSmall, 1>);
+                hipLaunchKernelGGL(place, dim3(chunks + (pk.tiles + kBinThreads - 1) / kBinThreads, bands),
+                                   dim3(kBinThreads), 0, stream, pk, record, proj->depth, proj->tile_count, A,
+                                   bins->status, bins->count, bins->ranges, bins->offsets, bins->pidx);
+            }
         }
-        pk.block_begin[pk.nv] = blocks;
-        if (!blocks) continue;
-        hipLaunchKernelGGL(emit_kernel, dim3(blocks), dim3(256), 0, stream, pk,
-                           reinterpret_cast<const float4*>(proj->record), bins->offsets, plan.n_total,
-                           proj->depth, bins->count, plan.capacity, keys_a, v_emit, z_a);
+        if (stage == 0)
+            hipLaunchKernelGGL(bin_top_kernel, dim3(1), dim3(kBinThreads), 0, stream, A, plan.capacity, bins->count,
+                               bins->status);
+        if (hipPeekAtLastError() != hipSuccess) return -1;
     }
-    if (plan.capacity == 0) return hipPeekAtLastError() == hipSuccess ? 0 : -1;
-
-    // 4. radix passes over the tile id
-    const uint32_t* kin = keys_a;
-    const uint32_t* vin = v_emit;
-    const uint32_t* zin = z_a;
-    uint32_t* kout = keys_b;
-    uint32_t* vout = v_other;
-    uint32_t* zout = z_b;
-    for (int p = 0; p < plan.passes; ++p) {
-        const int sh = tsplit.shift(p), wd = tsplit.width(p);
-        hipLaunchKernelGGL(tile_count_kernel, dim3(plan.sort_tiles), dim3(kSortThreads), 0, stream, kin, bins->count,
-                           plan.capacity, sh, wd, tcount, plan.sort_tiles);
-        hipLaunchKernelGGL(tile_scan_kernel, dim3(kTileRadix), dim3(256), 0, stream, tcount, plan.sort_tiles,
-                           bins->count, plan.capacity, hist + p * kTileRadix);
-        // digit widths of the tile passes: 8 or 9 bits (DigitSplit of at most 32 bits, 9 at most)
-        static_assert(kTileRadixBits == 9, "scatter instantiated for 8- and 9-bit digits");
-        auto scatter = wd == 9 ? sort_scatter_kernel<9> : wd == 8 ? sort_scatter_kernel<8> : wd == 7 ? sort_scatter_kernel<7>
-                     : wd == 6 ? sort_scatter_kernel<6> : wd == 5 ? sort_scatter_kernel<5> : wd == 4 ? sort_scatter_kernel<4>
-                     : wd == 3 ? sort_scatter_kernel<3> : wd == 2 ? sort_scatter_kernel<2> : sort_scatter_kernel<1>;
-        hipLaunchKernelGGL(scatter, dim3(plan.sort_tiles), dim3(kSortThreads), 0, stream, kin, vin, zin, kout, vout,
-                           zout, bins->count, plan.capacity, sh, hist + p * kTileRadix, tcount, plan.sort_tiles);
-        const uint32_t* tk = kin;
-        const uint32_t* tv = vin;
-        const uint32_t* tz = zin;
-        kin = kout;
-        vin = vout;
-        zin = zout;
-        kout = const_cast<uint32_t*>(tk);
-        vout = const_cast<uint32_t*>(tv);
-        zout = const_cast<uint32_t*>(tz);
+    if (plan.capacity == 0) return 0;
+    // a tile's list holds each particle of its view at most once: without a view of more
+    // particles than a length there is no such segment, and nothing is launched for it
+    if ((uint32_t)most > kBigMax) {
+        const unsigned grid = std::min<unsigned>(plan.large_max, 512u);
+        hipLaunchKernelGGL(bin_partition_kernel, dim3(grid), dim3(kBinThreads), 0, stream, A, bins->pidx, bins->status);
     }
-    // 5. ranges
-    const unsigned fin_blocks = (unsigned)std::min<uint64_t>(2048, (plan.capacity + 1023) / 1024);
-    hipLaunchKernelGGL(finalize_kernel, dim3(fin_blocks), dim3(256), 0, stream, kin, bins->count, plan.capacity,
-                       plan.tiles_total, bins->ranges);
-    // 6. depth order within every tile (zin: depth bits in the order of pidx; the tile-id
-    // arrays and vals_alt are scratch now)
-    if (plan.tiles_total) {
-        static int big_grid = 0;
-        if (!big_grid) big_grid = resident_blocks(reinterpret_cast<const void*>(segment_sort_big_kernel), kBigThreads);
-        if (!big_grid) return -1;
-        uint32_t* long_counts = reinterpret_cast<uint32_t*>(base + plan.off_long_counts);
-        uint32_t* long_lists = reinterpret_cast<uint32_t*>(base + plan.off_long_lists);
-        hipLaunchKernelGGL(segment_sort_small_kernel, dim3((plan.tiles_total + 3) / 4), dim3(kSortThreads), 0, stream,
-                           bins->ranges, plan.tiles_total, zin, bins->pidx, bins->keys, bins->count,
-                           plan.capacity, bins->status, long_lists, long_counts);
-        hipLaunchKernelGGL(segment_sort_big_kernel, dim3((unsigned)std::min<uint32_t>(plan.tiles_total, big_grid)),
-                           dim3(kBigThreads), 0, stream, bins->ranges, plan.tiles_total, zin, bins->pidx,
-                           bins->keys, bins->count, plan.capacity, bins->status, long_lists, long_counts, keys_a,
-                           keys_b, vals_alt);
-        // 6c. the longest segments, by all workgroups (A = (zin, pidx), B = (keys_a, vals_alt)).
-        // A tile's list holds each particle of its view at most once, so without a view of
-        // more than kChunkMin particles there is no such segment and nothing is launched.
-        int32_t most = 0;
-        for (int v = 0; v < nv; ++v) most = std::max(most, n_per_view[v]);
-        if ((uint32_t)most <= kChunkMin) return hipPeekAtLastError() == hipSuccess ? 0 : -1;
-        static int chunk_grid = 0;
-        if (!chunk_grid) chunk_grid = resident_blocks(reinterpret_cast<const void*>(chunk_scatter_kernel), kSortThreads);
-        if (!chunk_grid) return -1;
-        uint32_t* tables = reinterpret_cast<uint32_t*>(base + plan.off_chunk_tables);
-        const uint32_t hm = plan.chunk_h_max;
-        ChunkPlan cp{tables, tables + hm, tables + 2 * hm, tables + 3 * hm + 1, tables + 8 * hm + 1,
-                     reinterpret_cast<uint32_t*>(base + plan.off_chunk_seg),
-                     reinterpret_cast<uint32_t*>(base + plan.off_chunk_cnt), hm};
-        uint32_t* zmut = const_cast<uint32_t*>(zin);
-        const unsigned cg = (unsigned)std::min<uint32_t>(plan.chunk_max, (uint32_t)chunk_grid);
-        const unsigned sg = (unsigned)std::min<uint32_t>(hm, 1024u);
-        hipLaunchKernelGGL(chunk_setup_kernel, dim3(1), dim3(256), 0, stream, bins->ranges, plan.tiles_total,
-                           long_lists, long_counts, cp);
-        for (int pass = 0; pass < 4; ++pass) {
-            hipLaunchKernelGGL(chunk_count_kernel, dim3(cg), dim3(kSortThreads), 0, stream, zin, keys_a, long_counts,
-                               cp, pass);
-            hipLaunchKernelGGL(chunk_scan_kernel, dim3(sg), dim3(256), 0, stream, long_counts, cp, pass);
-            hipLaunchKernelGGL(chunk_scatter_kernel, dim3(cg), dim3(kSortThreads), 0, stream, zmut, bins->pidx, keys_a,
-                               vals_alt, long_counts, cp, pass);
-        }
-        hipLaunchKernelGGL(chunk_final_kernel, dim3(cg), dim3(256), 0, stream, keys_a, vals_alt, zin, bins->pidx,
-                           bins->keys, long_counts, cp);
+    if ((uint32_t)most > kMidMax) {
+        const unsigned grid = std::min<unsigned>(plan.list_max + plan.item_max, 768u);
+        hipLaunchKernelGGL(bin_sort_big_kernel, dim3(grid), dim3(kBigThreads), 0, stream, A, bins->ranges, bins->pidx,
+                           bins->keys, bins->status);
     }
+    const uint32_t mid_blocks = (uint32_t)most > kSmallMax ? std::min<uint32_t>(plan.list_max + plan.item_max, 2048u) : 0u;
+    hipLaunchKernelGGL(bin_sort_mid_kernel, dim3(mid_blocks + (plan.tiles_total + 3) / 4), dim3(256), 0, stream, A,
+                       mid_blocks, plan.tiles_total, bins->ranges, bins->pidx, bins->keys, bins->status);
     return hipPeekAtLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -10,22 +10,23 @@ namespace isogs {
 int launch_project(const isogs_scene* scenes, const isogs_camera* cams, int32_t nv, const isogs_projected* out,
                    hipStream_t stream);
 
-// Workspace layout of isogs_bin_sort for a given capacity and batch.
+// Workspace layout of isogs_bin_sort for a given capacity and batch. `limit`: bytes that the
+// workspace cannot exceed (a plan over it is one that has always needed more).
 struct BinSortPlan {
     uint64_t capacity;
     uint32_t n_total;       // packed particles over all views
     uint32_t tiles_total;   // global tiles over all views
-    int passes;             // radix passes (digits of at most 9 bits) over the tile id
-    int tile_bits;          // bits of the largest global tile id
-    uint32_t sort_tiles;    // 4096-entry sort tiles for `capacity`
-    uint32_t scan_blocks;   // 2048-particle scan blocks
-    uint32_t chunk_h_max;   // segments sorted in chunks by all workgroups, at most
-    uint32_t chunk_max;     // their 4096-entry chunks, at most
-    size_t off_keys_a, off_keys_b, off_vals_alt, off_z_a, off_z_b, off_hist, off_long_counts,
-        off_block_sums, off_long_lists, off_tcount, off_chunk_tables, off_chunk_seg, off_chunk_cnt, bytes;
+    bool large_band;        // a view has more tiles than the smaller kernels count at once
+    bool boxes;             // packed tile boxes are kept between the two passes over the particles
+    uint32_t per;           // particles per chunk
+    uint32_t chunks, blocks;   // chunks and 64-tile blocks over all views
+    uint32_t list_max, large_max, item_max;   // bounds on the listed segments and their pieces
+    size_t off_key, off_z, off_box, off_m, off_tile_pre, off_tile_tot, off_missing, off_block_sum, off_chunk_sum,
+        off_counters, off_lists, off_items, off_stack, bytes;
 };
 
-BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, int32_t nv, uint64_t capacity);
+BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, int32_t nv, uint64_t capacity,
+                          size_t limit = SIZE_MAX);
 
 int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const int32_t* n_per_view,
                     const isogs_camera* cams, int32_t nv, const isogs_bins* bins, void* ws, hipStream_t stream);
