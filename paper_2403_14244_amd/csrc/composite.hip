@@ -565,6 +565,60 @@ __global__ void __launch_bounds__(256) tile_class_scatter_kernel(const uint32_t*
     if (i < n_items) order[start[b] + base[b] + local] = i;
 }
 
+// The whole queue by one workgroup, for launches of few tiles: the class counts and cursors stay
+// in LDS (a wave adds once per class it holds). At 256 tiles one launch of 4 us where clearing,
+// counting and placing took three of 6 us together; at 8160 tiles the one workgroup takes
+// 19 us against 9 us, so the line lies between.
+constexpr uint32_t kOneQueueTiles = 2048;
+constexpr int kOneQueueThreads = 1024;
+
+__global__ void __launch_bounds__(kOneQueueThreads) tile_queue_kernel(const uint32_t* __restrict__ ranges,
+                                                                      uint32_t tile0, uint32_t n_items, uint32_t cap,
+                                                                      uint32_t* __restrict__ hist,
+                                                                      uint32_t* __restrict__ order) {
+    constexpr uint32_t kPer = kOneQueueTiles / kOneQueueThreads;
+    __shared__ uint32_t cnt[kBuckets], at[kBuckets];
+    const uint32_t t = threadIdx.x, l = lane_id();
+    if (t < (uint32_t)kBuckets) cnt[t] = 0u;
+    __syncthreads();
+    // (class << 16 | place among the workgroup's tiles of the class) of tiles t, t + 1024, ...
+    uint32_t mine[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t i = q * kOneQueueThreads + t;
+        mine[q] = i < n_items ? length_bucket(ranges, tile0 + i, cap) : 0xFFFFu;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t b = mine[q];
+        uint64_t left = ballot64(b != 0xFFFFu);
+        uint32_t place = 0;
+        while (left) {   // (uniform) the classes of the wave
+            const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)b, __builtin_ctzll(left));
+            const uint64_t same = ballot64(b == c);
+            uint32_t first = 0;
+            if (l == 0) first = atomicAdd(&cnt[c], (uint32_t)__popcll(same));
+            first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+            if (b == c) place = first + rank_below(same);
+            left &= ~same;
+        }
+        mine[q] = b << 16 | place;
+    }
+    __syncthreads();
+    if (t < (uint32_t)kBuckets) {
+        uint32_t s = 0;
+        for (int b = kBuckets - 1; b > (int)t; --b) s += cnt[b];
+        at[t] = s;
+        hist[t] = cnt[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t i = q * kOneQueueThreads + t;
+        if (i < n_items) order[at[mine[q] >> 16] + (mine[q] & 0xFFFFu)] = i;
+    }
+}
+
 int launch_render_fwd(const isogs_projected* proj, const int32_t* n_per_view, const isogs_bins* bins,
                       const isogs_camera* cams, int32_t nv, const float* bg, float* image, float* T_final,
                       uint32_t* n_last, float* ckpt, hipStream_t stream) {
@@ -630,6 +684,11 @@ uint32_t* launch_tile_queue(uint32_t* q, const uint32_t* ranges, uint32_t tile0,
     uint32_t* hist = q;
     uint32_t* cursor = q + kBuckets;
     uint32_t* order = q + kQueueHead;
+    if (n_tiles <= kOneQueueTiles) {
+        hipLaunchKernelGGL(tile_queue_kernel, dim3(1), dim3(kOneQueueThreads), 0, stream, ranges, tile0, n_tiles, cap,
+                           hist, order);
+        return order;
+    }
     hipLaunchKernelGGL(fill_u32_kernel_c, dim3(1), dim3(128), 0, stream, q, (uint32_t)kQueueHead);
     const unsigned hb = std::min<unsigned>(256u, (n_tiles + 255u) / 256u);
     hipLaunchKernelGGL(tile_class_hist_kernel, dim3(hb), dim3(256), 0, stream, ranges, tile0, n_tiles, cap, hist);
