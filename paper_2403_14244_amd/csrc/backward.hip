@@ -137,10 +137,9 @@ __device__ __forceinline__ uint64_t lanes_from(uint32_t first, uint32_t w) {
 }
 
 // Stages a round's entries and builds the 16 sub-block lists. An entry joins a sub-block's
-// list when its binning disk touches the sub-block (sub_block_touched, with the squared
-// offsets of the four columns and rows formed once) and its position (pos_hi - t, 1-based) is
-// at most the sub-block's largest n_last (no later entry was composited there). Contains
-// __syncthreads.
+// list when its binning disk reaches the sub-block (run_distances) and its position
+// (pos_hi - t, 1-based) is at most the sub-block's largest n_last (no later entry was
+// composited there). Contains __syncthreads.
 template <bool AN>
 __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, uint32_t nb, uint32_t pos_hi, int tx,
                                               int ty, int tiles_x, int tiles_y, float w_lim, float h_lim) {
@@ -155,16 +154,8 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
             r2 = c.w * c.w;
         }
         // (a sub-block without pixels has gmax 0 and keeps no entry)
-        const float xb = (float)(tx * kTile) + 0.5f, yb = (float)(ty * kTile) + 0.5f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float x_lo = xb + (float)(4 * q), y_lo = yb + (float)(4 * q);
-            const float x_hi = fminf(x_lo + 3.0f, w_lim), y_hi = fminf(y_lo + 3.0f, h_lim);
-            const float dx = fmaxf(fmaxf(x_lo - f.x, f.x - x_hi), 0.0f);
-            const float dy = fmaxf(fmaxf(y_lo - f.y, f.y - y_hi), 0.0f);
-            dxx[q] = dx * dx;
-            dyy[q] = dy * dy;
-        }
+        run_distances(f.x, tx * kTile, w_lim, dxx);
+        run_distances(f.y, ty * kTile, h_lim, dyy);
     }
     if (t == 0) {
         sb.fp[kBwdDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());
@@ -221,8 +212,7 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
     for (int k = 0; k < 16; ++k) {
         const uint32_t first = __builtin_amdgcn_readlane(at, k);
         if ((bal[k] >> l) & 1u) {
-            const uint32_t i = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[k] >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal[k], first));
+            const uint32_t i = rank_from(bal[k], first);
             sb.list[i] = (uint16_t)(t * kSlotBytes);
             sb.link[i] = (uint16_t)b.head;
             b.head = i | (uint32_t)k << kLinkShift;

@@ -122,17 +122,17 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
         if (ckpt && chunked_list(p.len) && b0 > p.start && (b0 - p.start) % kCkptChunk == 0)
             ckpt[(size_t)ckpt_slot(p.start, (b0 - p.start) / kCkptChunk) * 256 + t] =
                 make_float4(s.T, s.cr, s.cg, s.cb);
-        uint32_t steps;
+        SubLists lists;
         if (PIPE) {
             nxt = load_entry<AN>(record, g_next, pk.n_particles, conic);
             g_next = batch_pidx(pidx, b0 + 2 * kBatch, batch_len(b0 + 2 * kBatch));
-            steps = stage_loaded(sb, cur, p.tx * kTile, p.ty * kTile, p.w_lim, p.h_lim);
+            lists = stage_loaded(sb, cur, p.tx * kTile, p.ty * kTile, p.w_lim, p.h_lim);
         } else {
-            steps = stage_batch_sub(sb, record, conic, pidx, pk.n_particles, b0, batch_len(b0), p.tx * kTile,
+            lists = stage_batch_sub(sb, record, conic, pidx, pk.n_particles, b0, batch_len(b0), p.tx * kTile,
                                     p.ty * kTile, p.w_lim, p.h_lim);
         }
         const uint32_t pos0 = b0 - p.start + 1;   // 1-based list position of staged slot 0
-        const uint32_t len = sb.len[p.sbk];
+        const uint32_t steps = lists.steps, len = lists.len;
         uint32_t lastj = 0xFFFFFFFFu;
         auto composite_step = [&](const Step4& st) {
 #pragma unroll
@@ -259,8 +259,7 @@ struct StagedQuadT {
     float4 col[kBatch + 1];        // {r, g, b, slot bits}
     float2 cn[AN ? kBatch + 1 : 1];
     uint32_t list[4][kBatch + 4];  // byte offsets, per sub-block of the quadrant
-    uint32_t cnt[4][4];            // [loader wave][sub-block]
-    uint32_t len[4];
+    __align__(16) uint32_t cnt[4][4];   // [loader wave][sub-block]
 };
 
 // Stages a batch for quadrant `quad` of the tile: records of all entries, lists of the
@@ -269,49 +268,55 @@ struct StagedQuadT {
 template <bool AN>
 __device__ __forceinline__ uint32_t stage_quad(StagedQuadT<AN>& sq, const EntryLoad& e, int quad, int tile_x0,
                                                int tile_y0, float w_lim, float h_lim) {
-    const uint32_t t = threadIdx.x, w = t >> 6;
-    uint32_t mask = 0;
+    const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = lane_id();
+    float dxx[2], dyy[2], r2 = __builtin_nanf("");   // no entry: no comparison holds
     if (e.ok) {
-        const float4 f = e.f, c = e.c;
-        sq.fp[t] = staged_kernel<AN>(f);
+        sq.fp[t] = staged_kernel<AN>(e.f);
         if (AN) sq.cn[t] = staged_conic(e.k);
-        sq.col[t] = make_float4(c.x, c.y, c.z, __uint_as_float(t));
-        const float r2 = c.w * c.w;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (sub_block_touched(f.x, f.y, r2, 4 * quad + r, tile_x0, tile_y0, w_lim, h_lim)) mask |= 1u << r;
+        sq.col[t] = make_float4(e.c.x, e.c.y, e.c.z, __uint_as_float(t));
+        r2 = e.c.w * e.c.w;
     }
     if (t == 0) {
         sq.fp[kDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());
-        if (AN) sq.cn[kDummy] = make_float2(0.0f, 0.0f);
+        if (AN) sq.cn[AN ? kDummy : 0] = make_float2(0.0f, 0.0f);
         sq.col[kDummy] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)kDummy));
     }
+    const int qx0 = tile_x0 + (quad & 1) * 8, qy0 = tile_y0 + (quad >> 1) * 8;
+    run_distances(e.f.x, qx0, w_lim, dxx);
+    run_distances(e.f.y, qy0, h_lim, dyy);
+    const int cols = __builtin_amdgcn_readfirstlane((int)(w_lim + 0.5f)) - qx0;
+    const int rows = __builtin_amdgcn_readfirstlane((int)(h_lim + 0.5f)) - qy0;
+    bool hit[4];
     uint64_t bal[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) bal[r] = ballot64((mask >> r) & 1u);
-    if (lane_id() < 4) {
-        const uint32_t r = lane_id();
-        sq.cnt[w][r] = (uint32_t)__popcll(r == 0 ? bal[0] : r == 1 ? bal[1] : r == 2 ? bal[2] : bal[3]);
+    for (int r = 0; r < 4; ++r) {
+        hit[r] = dxx[r & 1] + dyy[r >> 1] <= r2 && 4 * (r & 1) < cols && 4 * (r >> 1) < rows;
+        bal[r] = ballot64(hit[r]);
+    }
+    if (l == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sq.cnt[w][r] = (uint32_t)__popcll(bal[r]);
     }
     __syncthreads();
+    // lane r (mod 4): list r's length, and the entries of earlier waves in it
+    const uint32_t c0 = sq.cnt[0][l & 3u], c1 = sq.cnt[1][l & 3u], c2 = sq.cnt[2][l & 3u], c3 = sq.cnt[3][l & 3u];
+    const uint32_t n = c0 + c1 + c2 + c3, padded = (n + 3u) & ~3u;
+    const uint32_t before = w == 0 ? 0u : w == 1 ? c0 : w == 2 ? c0 + c1 : c0 + c1 + c2;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        if ((mask >> r) & 1u) {
-            uint32_t pos = rank_below(bal[r]);
-            pos += (w > 0 ? sq.cnt[0][r] : 0u) + (w > 1 ? sq.cnt[1][r] : 0u) + (w > 2 ? sq.cnt[2][r] : 0u);
-            sq.list[r][pos] = t * kSlotBytes;
+        const uint32_t first = __builtin_amdgcn_readlane(before, r);
+        if (hit[r]) sq.list[r][rank_from(bal[r], first)] = t * kSlotBytes;
+    }
+    if (w == 0) {
+        const uint32_t r = l >> 2, nr = __shfl(n, (int)r, kWave), pr = (nr + 3u) & ~3u, j = l & 3u;
+        if (l < 16) {
+            if (nr + j < pr) sq.list[r][nr + j] = kDummy * kSlotBytes;
+            sq.list[r][pr + j] = kDummy * kSlotBytes;
         }
     }
-    if (t < 16) {
-        const uint32_t r = t >> 2;
-        const uint32_t n = sq.cnt[0][r] + sq.cnt[1][r] + sq.cnt[2][r] + sq.cnt[3][r];
-        const uint32_t padded = (n + 3u) & ~3u;
-        if (n + (t & 3u) < padded) sq.list[r][n + (t & 3u)] = kDummy * kSlotBytes;
-        sq.list[r][padded + (t & 3u)] = kDummy * kSlotBytes;
-        if ((t & 3u) == 0) sq.len[r] = padded;
-    }
+    const uint32_t steps = __builtin_amdgcn_readlane(padded, (int)w);
     __syncthreads();
-    return __builtin_amdgcn_readfirstlane(sq.len[w]);
+    return steps;
 }
 
 // Composites quadrant `quad` of one tile with the wide walk. Contains __syncthreads.

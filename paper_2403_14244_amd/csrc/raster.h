@@ -59,21 +59,6 @@ __device__ __forceinline__ int sub_y(uint32_t t) {
     return (int)(((t >> 6) >> 1) * 8u + (((t >> 4) & 3u) >> 1) * 4u + ((t >> 2) & 3u));
 }
 
-// Whether the binning disk (centre u, v, radius^2 r2) reaches a pixel centre of sub-block
-// k = 4 * quadrant + row of the tile at (tile_x0, tile_y0); quadrant q sits at
-// (8 (q % 2), 8 (q / 2)), row g of it at (4 (g % 2), 4 (g / 2)). A sub-block starting
-// beyond the image has no pixels. The forward and backward passes share this test, so
-// they cull the same entries.
-__device__ __forceinline__ bool sub_block_touched(float u, float v, float r2, int k, int tile_x0, int tile_y0,
-                                                  float w_lim, float h_lim) {
-    const int qx = ((k >> 2) & 1) * 8 + (k & 1) * 4, qy = ((k >> 2) >> 1) * 8 + ((k & 3) >> 1) * 4;
-    const float x_lo = (float)(tile_x0 + qx) + 0.5f, y_lo = (float)(tile_y0 + qy) + 0.5f;
-    const float x_hi = fminf(x_lo + 3.0f, w_lim), y_hi = fminf(y_lo + 3.0f, h_lim);
-    const float dx = fmaxf(fmaxf(x_lo - u, u - x_hi), 0.0f);
-    const float dy = fmaxf(fmaxf(y_lo - v, v - y_hi), 0.0f);
-    return x_lo <= w_lim && y_lo <= h_lim && dx * dx + dy * dy <= r2;
-}
-
 constexpr uint32_t kSlotBytes = 16;   // one staged float4
 
 // The walks serve two kernel families, chosen by the template flag AN: the isotropic
@@ -89,10 +74,40 @@ struct StagedSubT {
     float4 col[kBatch + 1];
     float2 cn[AN ? kBatch + 1 : 1];
     uint32_t list[16][kBatch + 4];   // byte offsets (16 x staged slot) into fp and col
-    uint32_t cnt[4][16];        // [loader wave][sub-block]
-    uint32_t len[16];           // padded list lengths (multiples of 4)
+    __align__(16) uint32_t cnt[4][16];   // [loader wave][sub-block]
 };
 using StagedSub = StagedSubT<false>;
+
+// A wave's view of the staged lists: its list steps (the longest of its four rows' padded
+// lists) and the padded length of this lane's row.
+struct SubLists {
+    uint32_t steps, len;
+};
+
+// Which sub-blocks an entry's binning disk (centre u, v, radius r) reaches: sub-block
+// k = 4 * quadrant + row, quadrant q at (8 (q % 2), 8 (q / 2)) of the tile and row g of it at
+// (4 (g % 2), 4 (g / 2)), holds a pixel centre within r of the centre, where the squared
+// distance is a column part plus a row part; a sub-block starting beyond the image has no
+// pixels. The forward and backward passes form the same FP32 sum, so they cull the same
+// entries. run_distances gives the parts: squared distances of the centre coordinate c to N
+// consecutive runs of four pixel centres from pixel coordinate `first` on, clipped at `lim`.
+// Neighbouring sub-blocks share them: a tile takes 8 parts and 16 sums where 16 separate
+// tests took 32 parts.
+template <int N>
+__device__ __forceinline__ void run_distances(float c, int first, float lim, float (&d2)[N]) {
+    const float base = (float)first + 0.5f;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const float lo = base + (float)(4 * q), hi = fminf(lo + 3.0f, lim);
+        const float d = fmaxf(fmaxf(lo - c, c - hi), 0.0f);
+        d2[q] = d * d;
+    }
+}
+
+// `first` plus the number of set bits of m in lanes below this one.
+__device__ __forceinline__ uint32_t rank_from(uint64_t m, uint32_t first) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, first));
+}
 
 // One staged entry as loaded from global memory by its thread (k: the conic's B, C).
 struct EntryLoad {
@@ -142,64 +157,70 @@ __device__ __forceinline__ EntryLoad load_entry(const float4* __restrict__ recor
     return e;
 }
 
-// Stages the loaded entries of a batch (one per thread) and builds the 16 sub-block lists.
-// Returns the number of list steps of the calling wave (the longest of its four rows'
-// padded lists). Contains __syncthreads.
+// Stages the loaded entries of a batch (one per thread) and builds the 16 sub-block lists. The
+// list positions come from scalars (the wave's ballots and the waves' counts), about four
+// vector instructions per list. Contains __syncthreads.
 template <bool AN>
-__device__ __forceinline__ uint32_t stage_loaded(StagedSubT<AN>& sb, const EntryLoad& e, int tile_x0, int tile_y0,
+__device__ __forceinline__ SubLists stage_loaded(StagedSubT<AN>& sb, const EntryLoad& e, int tile_x0, int tile_y0,
                                                  float w_lim, float h_lim) {
-    const uint32_t t = threadIdx.x, w = t >> 6;
-    uint32_t mask = 0;
+    const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = lane_id();
+    float dxx[4], dyy[4], r2 = __builtin_nanf("");   // no entry: no comparison holds
     if (e.ok) {
-        const float4 f = e.f, c = e.c;
-        sb.fp[t] = staged_kernel<AN>(f);
+        sb.fp[t] = staged_kernel<AN>(e.f);
         if (AN) sb.cn[t] = staged_conic(e.k);
-        sb.col[t] = make_float4(c.x, c.y, c.z, __uint_as_float(t));   // w: the slot itself
-        const float r2 = c.w * c.w;
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-            if (sub_block_touched(f.x, f.y, r2, k, tile_x0, tile_y0, w_lim, h_lim)) mask |= 1u << k;
+        sb.col[t] = make_float4(e.c.x, e.c.y, e.c.z, __uint_as_float(t));   // w: the slot itself
+        r2 = e.c.w * e.c.w;
     }
     if (t == 0) {
         sb.fp[kDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());
-        if (AN) sb.cn[kDummy] = make_float2(0.0f, 0.0f);
+        if (AN) sb.cn[AN ? kDummy : 0] = make_float2(0.0f, 0.0f);
         sb.col[kDummy] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)kDummy));
     }
+    run_distances(e.f.x, tile_x0, w_lim, dxx);
+    run_distances(e.f.y, tile_y0, h_lim, dyy);
+    // (a sub-block beyond the image has no pixels and gets no list)
+    const int cols = __builtin_amdgcn_readfirstlane((int)(w_lim + 0.5f)) - tile_x0;
+    const int rows = __builtin_amdgcn_readfirstlane((int)(h_lim + 0.5f)) - tile_y0;
+    bool hit[16];
     uint64_t bal[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) bal[k] = ballot64((mask >> k) & 1u);
-    if (lane_id() < 16) {
-        uint32_t c = 0;
+    for (int k = 0; k < 16; ++k) {
+        const int qx = ((k >> 2) & 1) * 2 + (k & 1), qy = ((k >> 2) >> 1) * 2 + ((k & 3) >> 1);
+        hit[k] = dxx[qx] + dyy[qy] <= r2 && 4 * qx < cols && 4 * qy < rows;
+        bal[k] = ballot64(hit[k]);
+    }
+    if (l == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) c = (lane_id() == (uint32_t)k) ? (uint32_t)__popcll(bal[k]) : c;
-        sb.cnt[w][lane_id()] = c;
+        for (int k = 0; k < 16; ++k) sb.cnt[w][k] = (uint32_t)__popcll(bal[k]);
     }
     __syncthreads();
+    // lane k (mod 16): list k's length, and the entries of earlier waves in it
+    const uint32_t c0 = sb.cnt[0][l & 15u], c1 = sb.cnt[1][l & 15u], c2 = sb.cnt[2][l & 15u], c3 = sb.cnt[3][l & 15u];
+    const uint32_t n = c0 + c1 + c2 + c3, padded = (n + 3u) & ~3u;
+    const uint32_t before = w == 0 ? 0u : w == 1 ? c0 : w == 2 ? c0 + c1 : c0 + c1 + c2;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        if ((mask >> k) & 1u) {
-            uint32_t pos = rank_below(bal[k]);
-            pos += (w > 0 ? sb.cnt[0][k] : 0u) + (w > 1 ? sb.cnt[1][k] : 0u) + (w > 2 ? sb.cnt[2][k] : 0u);
-            sb.list[k][pos] = t * kSlotBytes;
-        }
+        const uint32_t first = __builtin_amdgcn_readlane(before, k);
+        if (hit[k]) sb.list[k][rank_from(bal[k], first)] = t * kSlotBytes;
     }
-    if (t < 64) {
-        // pad sub-block k = t / 4 with dummies up to a multiple of four
-        const uint32_t k = t >> 2;
-        const uint32_t n = sb.cnt[0][k] + sb.cnt[1][k] + sb.cnt[2][k] + sb.cnt[3][k];
-        const uint32_t padded = (n + 3u) & ~3u;
-        if (n + (t & 3u) < padded) sb.list[k][n + (t & 3u)] = kDummy * kSlotBytes;
-        sb.list[k][padded + (t & 3u)] = kDummy * kSlotBytes;   // four more: reads past the end
-        if ((t & 3u) == 0) sb.len[k] = padded;
+    if (w == 0) {
+        // pad list l / 4 with dummies up to a multiple of four, and four more: reads past the end
+        const int k = (int)(l >> 2);
+        const uint32_t nk = __shfl(n, k, kWave), pk = (nk + 3u) & ~3u, j = l & 3u;
+        if (nk + j < pk) sb.list[k][nk + j] = kDummy * kSlotBytes;
+        sb.list[k][pk + j] = kDummy * kSlotBytes;
     }
+    SubLists L;
+    L.len = __shfl(padded, (int)(4u * w + (l >> 4)), kWave);
+    L.steps = max(max(__builtin_amdgcn_readlane(L.len, 0), __builtin_amdgcn_readlane(L.len, 16)),
+                  max(__builtin_amdgcn_readlane(L.len, 32), __builtin_amdgcn_readlane(L.len, 48)));
     __syncthreads();
-    const uint32_t a = sb.len[4 * w], b = sb.len[4 * w + 1], c = sb.len[4 * w + 2], d = sb.len[4 * w + 3];
-    return __builtin_amdgcn_readfirstlane(max(max(a, b), max(c, d)));
+    return L;
 }
 
 // Loads and stages entries [first, first + n_in_batch). Contains __syncthreads.
 template <bool AN>
-__device__ __forceinline__ uint32_t stage_batch_sub(StagedSubT<AN>& sb, const float4* __restrict__ record,
+__device__ __forceinline__ SubLists stage_batch_sub(StagedSubT<AN>& sb, const float4* __restrict__ record,
                                                     const float2* __restrict__ conic,
                                                     const uint32_t* __restrict__ pidx, uint32_t n_particles,
                                                     uint32_t first, uint32_t n_in_batch, int tile_x0, int tile_y0,
