@@ -154,8 +154,8 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
             r2 = c.w * c.w;
         }
         // (a sub-block without pixels has gmax 0 and keeps no entry)
-        run_distances(f.x, tx * kTile, w_lim, dxx);
-        run_distances(f.y, ty * kTile, h_lim, dyy);
+        run_distances<false>(f.x, tx * kTile, w_lim, dxx);
+        run_distances<false>(f.y, ty * kTile, h_lim, dyy);
     }
     if (t == 0) {
         sb.fp[kBwdDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());

@@ -5,48 +5,53 @@
 
 namespace isogs {
 
+using f32x4 = float __attribute__((ext_vector_type(4)));
+
 // Composites one staged entry into a pixel's running state (branch-free; the dummy pad
 // record has log2(o) = -inf, so alpha = 0 and it changes nothing). T loses the weight it
-// gives away, T - alpha T; with LAST, `lastj` keeps the staged slot (carried in c.w) of the
-// last entry used in the current batch (slots only increase along a list). TERM: the pixel
-// stops after the entry that takes T below kTMin.
+// gives away, T - alpha T; with LAST, `lastoff` keeps the byte offset of the last entry used
+// in the current batch (offsets only increase along a list). TERM: the pixel stops after the
+// entry that takes T below kTMin.
+// The colour sums come from the matrix cores: v_mfma_f32_4x4x1 takes one entry for the 16
+// lane quads of the wave, whose lane i reads colour component i (`ch`) of the quad's entry,
+// and adds component * weight to all three sums of the quad's four pixels (rgb.w stays 0).
+// Beside three FMAs this saves three quarters of the LDS bytes of the colours, which every
+// lane would read whole.
 template <bool TERM, bool AN, bool LAST = true>
-__device__ __forceinline__ void composite_entry(const float4& f, const float4& c, const float2& k, float px, float py,
-                                                float& T, float& cr, float& cg, float& cb, uint32_t& lastj,
-                                                bool& done) {
+__device__ __forceinline__ void composite_entry(const float4& f, float ch, const float2& k, uint32_t off, float px,
+                                                float py, float& T, f32x4& rgb, uint32_t& lastoff, bool& done) {
     float g;
     float a = staged_alpha<AN>(px - f.x, py - f.y, f, k, g);
     const bool use = (a >= kAlphaMin) && !done;
     a = use ? a : 0.0f;
     const float wgt = a * T;
-    cr = fmaf(c.x, wgt, cr);
-    cg = fmaf(c.y, wgt, cg);
-    cb = fmaf(c.z, wgt, cb);
+    rgb = __builtin_amdgcn_mfma_f32_4x4x1f32(ch, wgt, rgb, 0, 0, 0);
     T = T - wgt;
-    if (LAST) lastj = use ? __float_as_uint(c.w) : lastj;
+    if (LAST) lastoff = use ? off : lastoff;
     if (TERM) done = done || (T < kTMin);
 }
 
-// The four entries of one list step: offsets -> staged records (k: conics, anisotropic).
+// The four entries of one list step: offsets -> staged records (k: conics, anisotropic) and
+// this lane's colour components.
 struct Step4 {
-    float4 f[4], c[4];
+    float4 f[4];
+    float c[4];
     float2 k[4];
+    uint32_t o[4];
 };
 
 template <bool AN>
-__device__ __forceinline__ void load_step(const StagedSubT<AN>& sb, const uint4& o, Step4& st) {
-    st.f[0] = staged_fp(sb, o.x);
-    st.f[1] = staged_fp(sb, o.y);
-    st.f[2] = staged_fp(sb, o.z);
-    st.f[3] = staged_fp(sb, o.w);
-    st.c[0] = staged_col(sb, o.x);
-    st.c[1] = staged_col(sb, o.y);
-    st.c[2] = staged_col(sb, o.z);
-    st.c[3] = staged_col(sb, o.w);
-    st.k[0] = staged_cn(sb, o.x);
-    st.k[1] = staged_cn(sb, o.y);
-    st.k[2] = staged_cn(sb, o.z);
-    st.k[3] = staged_cn(sb, o.w);
+__device__ __forceinline__ void load_step(const StagedSubT<AN>& sb, const uint2& o, Step4& st) {
+    st.o[0] = o.x & 0xFFFFu;
+    st.o[1] = o.x >> 16;
+    st.o[2] = o.y & 0xFFFFu;
+    st.o[3] = o.y >> 16;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        st.f[e] = staged_fp(sb, st.o[e]);
+        st.c[e] = staged_component(sb, st.o[e]);
+        st.k[e] = staged_cn(sb, st.o[e]);
+    }
 }
 
 // A lane's pixel in a tile, and the pixel's compositing state.
@@ -60,7 +65,8 @@ struct TilePixel {
 };
 
 struct PixelState {
-    float T, cr, cg, cb;
+    float T;
+    f32x4 rgb;
     uint32_t last;   // 1-based tile-list position of the last entry used, 0 if none
     bool done;
 };
@@ -118,10 +124,10 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
         g_next = batch_pidx(pidx, b0 + kBatch, batch_len(b0 + kBatch));
     }
     for (; b0 < end; b0 += kBatch) {
-        if (__syncthreads_and(s.done)) break;
+        if (b0 != p.start + lo && !any_alive(sb.alive, !s.done)) break;
         if (ckpt && chunked_list(p.len) && b0 > p.start && (b0 - p.start) % kCkptChunk == 0)
             ckpt[(size_t)ckpt_slot(p.start, (b0 - p.start) / kCkptChunk) * 256 + t] =
-                make_float4(s.T, s.cr, s.cg, s.cb);
+                make_float4(s.T, s.rgb.x, s.rgb.y, s.rgb.z);
         SubLists lists;
         if (PIPE) {
             nxt = load_entry<AN>(record, g_next, pk.n_particles, conic);
@@ -133,12 +139,12 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
         }
         const uint32_t pos0 = b0 - p.start + 1;   // 1-based list position of staged slot 0
         const uint32_t steps = lists.steps, len = lists.len;
-        uint32_t lastj = 0xFFFFFFFFu;
+        uint32_t lastoff = 0xFFFFFFFFu;
         auto composite_step = [&](const Step4& st) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                composite_entry<TERM, AN, LAST>(st.f[e], st.c[e], st.k[e], p.px, p.py, s.T, s.cr, s.cg, s.cb,
-                                                lastj, s.done);
+                composite_entry<TERM, AN, LAST>(st.f[e], st.c[e], st.k[e], st.o[e], p.px, p.py, s.T, s.rgb, lastoff,
+                                                s.done);
         };
         if (!PL) {
             for (uint32_t k = 0; k < steps; k += 4) {
@@ -152,7 +158,7 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
             // step is composited, the records of the next and the list words of the one
             // after are in flight (the barriers keep the reads ahead of the arithmetic)
             Step4 sa, sc;
-            uint4 o = list4_sub(sb, p.sbk, 0, len);
+            uint2 o = list4_sub(sb, p.sbk, 0, len);
             load_step(sb, o, sa);
             o = list4_sub(sb, p.sbk, 4, len);
             for (uint32_t k = 0; k < steps; k += 8) {
@@ -168,7 +174,7 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
                 if (TERM && ballot64(!s.done) == 0) break;
             }
         }
-        if (LAST && lastj != 0xFFFFFFFFu) s.last = pos0 + lastj;
+        if (LAST && lastoff != 0xFFFFFFFFu) s.last = pos0 + lastoff / kSlotBytes;
         if (PIPE) cur = nxt;
     }
 }
@@ -180,9 +186,9 @@ __device__ __forceinline__ void write_pixel(const TilePixel& p, const PixelState
     const size_t hw = (size_t)p.width * p.height;
     const size_t pix = (size_t)p.y * p.width + p.x;
     float* img = image + (size_t)3 * p.pix_off;
-    img[pix] = fmaf(s.T, bg_r, s.cr);
-    img[hw + pix] = fmaf(s.T, bg_g, s.cg);
-    img[2 * hw + pix] = fmaf(s.T, bg_b, s.cb);
+    img[pix] = fmaf(s.T, bg_r, s.rgb.x);
+    img[hw + pix] = fmaf(s.T, bg_g, s.rgb.y);
+    img[2 * hw + pix] = fmaf(s.T, bg_b, s.rgb.z);
     T_final[p.pix_off + pix] = s.T;
     if (n_last) n_last[p.pix_off + pix] = s.last;
 }
@@ -217,17 +223,20 @@ __device__ __forceinline__ void composite_tile(StagedSubT<AN>& sb, const RenderP
                                                float bg_b, float* __restrict__ image, float* __restrict__ T_final,
                                                uint32_t* __restrict__ n_last, float4* __restrict__ ckpt) {
     const TilePixel p = tile_pixel(pk, logical, ranges);
-    PixelState s{1.0f, 0.0f, 0.0f, 0.0f, 0u, !p.inside};
+    PixelState s{1.0f, {0.0f, 0.0f, 0.0f, 0.0f}, 0u, !p.inside};
     composite_range<true, PIPE, PL, AN, LAST>(sb, pk, p, record, conic, pidx, 0, p.len, s, ckpt);
     write_pixel(p, s, bg_r, bg_g, bg_b, image, T_final, n_last);
 }
 
-// Register budgets: the compact walk of large launches, six waves per SIMD (80 VGPRs), as
-// many resident workgroups as LDS allows hiding the staging gathers; the walk of the
-// remaining tiles of small launches also prefetches the next batch from global memory,
-// five waves per SIMD (at most 102 VGPRs).
-constexpr int kCompactWavesPerSimd = 6;
-constexpr int kPrefetchWavesPerSimd = 5;
+// Register budgets: the compact walk of large launches, seven waves per SIMD (at most 72
+// VGPRs), as many resident workgroups as hide the staging gathers; the walk of the remaining
+// tiles of small launches also prefetches the next batch from global memory, six waves per
+// SIMD (at most 80 VGPRs). Lists of 16-bit offsets, half the LDS of 32-bit ones (16.8 KB a
+// workgroup), let that many reside. Ten views of 1080p: 579 us with six and four waves and
+// 32-bit lists, 546 with 16-bit lists, 530 at seven waves, 538 at eight (which spill);
+// 4K x 8 with the prefetch 1657 us at five waves, 1561 at six.
+constexpr int kCompactWavesPerSimd = 7;
+constexpr int kPrefetchWavesPerSimd = 6;
 
 // One workgroup per tile, tiles in XCD-banded order.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kCompactWavesPerSimd))) composite_fwd_kernel(
@@ -258,8 +267,9 @@ struct StagedQuadT {
     float4 fp[kBatch + 1];
     float4 col[kBatch + 1];        // {r, g, b, slot bits}
     float2 cn[AN ? kBatch + 1 : 1];
-    uint32_t list[4][kBatch + 4];  // byte offsets, per sub-block of the quadrant
+    __align__(16) uint16_t list[4][kBatch + 4];  // byte offsets, per sub-block of the quadrant
     __align__(16) uint32_t cnt[4][4];   // [loader wave][sub-block]
+    __align__(16) uint32_t alive[4];    // [wave]: not 0 if a pixel of it is still open
 };
 
 // Stages a batch for quadrant `quad` of the tile: records of all entries, lists of the
@@ -282,15 +292,13 @@ __device__ __forceinline__ uint32_t stage_quad(StagedQuadT<AN>& sq, const EntryL
         sq.col[kDummy] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)kDummy));
     }
     const int qx0 = tile_x0 + (quad & 1) * 8, qy0 = tile_y0 + (quad >> 1) * 8;
-    run_distances(e.f.x, qx0, w_lim, dxx);
-    run_distances(e.f.y, qy0, h_lim, dyy);
-    const int cols = __builtin_amdgcn_readfirstlane((int)(w_lim + 0.5f)) - qx0;
-    const int rows = __builtin_amdgcn_readfirstlane((int)(h_lim + 0.5f)) - qy0;
+    run_distances<true>(e.f.x, qx0, w_lim, dxx);
+    run_distances<true>(e.f.y, qy0, h_lim, dyy);
     bool hit[4];
     uint64_t bal[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        hit[r] = dxx[r & 1] + dyy[r >> 1] <= r2 && 4 * (r & 1) < cols && 4 * (r >> 1) < rows;
+        hit[r] = dxx[r & 1] + dyy[r >> 1] <= r2;
         bal[r] = ballot64(hit[r]);
     }
     if (l == 0) {
@@ -304,14 +312,14 @@ __device__ __forceinline__ uint32_t stage_quad(StagedQuadT<AN>& sq, const EntryL
     const uint32_t before = w == 0 ? 0u : w == 1 ? c0 : w == 2 ? c0 + c1 : c0 + c1 + c2;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const uint32_t first = __builtin_amdgcn_readlane(before, r);
-        if (hit[r]) sq.list[r][rank_from(bal[r], first)] = t * kSlotBytes;
+        const uint32_t first = __builtin_amdgcn_readlane(2u * before, r);
+        if (hit[r]) list_word(sq.list[r], first, bal[r]) = (uint16_t)(t * kSlotBytes);
     }
     if (w == 0) {
         const uint32_t r = l >> 2, nr = __shfl(n, (int)r, kWave), pr = (nr + 3u) & ~3u, j = l & 3u;
         if (l < 16) {
-            if (nr + j < pr) sq.list[r][nr + j] = kDummy * kSlotBytes;
-            sq.list[r][pr + j] = kDummy * kSlotBytes;
+            if (nr + j < pr) sq.list[r][nr + j] = (uint16_t)(kDummy * kSlotBytes);
+            sq.list[r][pr + j] = (uint16_t)(kDummy * kSlotBytes);
         }
     }
     const uint32_t steps = __builtin_amdgcn_readlane(padded, (int)w);
@@ -355,7 +363,7 @@ __device__ __forceinline__ void composite_quadrant(StagedQuadT<AN>& sq, const Re
     EntryLoad cur = load_entry<AN>(record, batch_pidx(pidx, b0, batch_len(b0)), pk.n_particles, conic);
     uint32_t g_next = batch_pidx(pidx, b0 + kBatch, batch_len(b0 + kBatch));
     for (; b0 < end; b0 += kBatch) {
-        if (__syncthreads_and(done)) break;
+        if (b0 != start && !any_alive(sq.alive, !done)) break;
         if (ckpt && chunked_list(len) && b0 > start && (b0 - start) % kCkptChunk == 0 && e_idx == 0)
             ckpt[(size_t)ckpt_slot(start, (b0 - start) / kCkptChunk) * 256 + t_px] = make_float4(T, cr, cg, cb);
         const EntryLoad nxt = load_entry<AN>(record, g_next, pk.n_particles, conic);
@@ -476,11 +484,12 @@ struct WgStamp {
 // LAST: the caller asked for n_last (without it the walk does not track the last entry).
 template <bool PIPE, bool AN, bool LAST>
 __device__ __forceinline__ void ordered_tile(StagedSubT<AN>& sb, const RenderPack& pk, const OrderedArgs& a) {
-    if (*a.status != kStatusOk) return write_overflow_tile(pk, a.order[blockIdx.x], a.image, a.T_final, a.n_last);
+    const uint32_t item = a.order[queue_slot(blockIdx.x, gridDim.x)];
+    if (*a.status != kStatusOk) return write_overflow_tile(pk, item, a.image, a.T_final, a.n_last);
     const WgStamp stamp(a);
-    composite_tile<PIPE, PIPE, AN, LAST>(sb, pk, a.order[blockIdx.x], a.record, a.conic, a.pidx, a.ranges, a.bg_r, a.bg_g,
+    composite_tile<PIPE, PIPE, AN, LAST>(sb, pk, item, a.record, a.conic, a.pidx, a.ranges, a.bg_r, a.bg_g,
                                    a.bg_b, a.image, a.T_final, a.n_last, a.ckpt);
-    stamp.done(a, pk, a.order[blockIdx.x]);
+    stamp.done(a, pk, item);
 }
 
 template <bool LAST>
@@ -497,8 +506,8 @@ __global__ void __launch_bounds__(256) composite_fwd_ordered_pipe_kernel(const R
 }
 
 // The anisotropic family (eq. 5 kernels): the same walks with the conic staged beside each
-// record. Its larger staging (27.5 KB) fits five workgroups per CU, so the compact walk
-// gets the registers of five waves per SIMD.
+// record (18.9 KB a workgroup) and more registers per entry in flight: one 1080p view takes
+// 126 us with the prefetching walk at four waves per SIMD, 131 at five, 140 at six.
 constexpr int kAnisoCompactWavesPerSimd = 5;
 constexpr int kAnisoWideWavesPerSimd = 4;
 
@@ -720,16 +729,16 @@ template <bool AN>
 __device__ __forceinline__ void ordered_wide(unsigned char* smem, const RenderPack& pk, const OrderedArgs& a) {
     static_assert(sizeof(StagedQuadT<AN>) <= sizeof(StagedSubT<AN>), "one LDS buffer serves both walks");
     const uint32_t wide_slots = a.wide_slots;
+    const uint32_t b = queue_slot(blockIdx.x, gridDim.x);
     if (*a.status != kStatusOk) {
         // every tile is one of the remaining ones then (no list is long)
-        if (blockIdx.x >= 4 * wide_slots)
-            write_overflow_tile(pk, a.order[blockIdx.x - 4 * wide_slots], a.image, a.T_final, a.n_last);
+        if (b >= 4 * wide_slots)
+            write_overflow_tile(pk, a.order[b - 4 * wide_slots], a.image, a.T_final, a.n_last);
         return;
     }
     uint32_t n_wide = 0;
     for (int c = kWideMinLog2 + 1; c < kBuckets; ++c) n_wide += a.hist[c];
     n_wide = min(n_wide, wide_slots);
-    const uint32_t b = blockIdx.x;
     const WgStamp stamp(a);
     if (b < 4 * wide_slots) {
         if ((b >> 2) >= n_wide) return;

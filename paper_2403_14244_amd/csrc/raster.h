@@ -30,6 +30,17 @@ __host__ __device__ inline bool chunked_list(uint32_t len) { return len >= kChun
 constexpr int kBuckets = 33;
 constexpr int kDummy = kBatch; // staged slot of a zero-opacity record that pads the lists
 
+// Queue position that block b of nb takes: consecutive blocks run on different XCDs, so of
+// each 8 kQueueRun positions an XCD takes kQueueRun consecutive ones, mostly neighbouring tiles,
+// which share records in its L2. Ten views of 1080p forward: 618 us with runs of 1, 574 with 8,
+// 581 with 32, 622 with 128 (the longest lists then crowd on one XCD).
+constexpr uint32_t kQueueRun = 8;
+__device__ __forceinline__ uint32_t queue_slot(uint32_t b, uint32_t nb) {
+    constexpr uint32_t kGroup = 8u * kQueueRun;
+    const uint32_t in = b % kGroup;
+    return b - in + kGroup <= nb ? b - in + (in & 7u) * kQueueRun + (in >> 3) : b;
+}
+
 // Emit position of the entry (particle with footprint u, v, r; tile tx, ty): the
 // particle's offset plus the number of its member tiles before (tx, ty) in row-major
 // order, counted with the same FP32 test the binning used.
@@ -66,15 +77,16 @@ constexpr uint32_t kSlotBytes = 16;   // one staged float4
 // eq. 5 (an ellipse: the conic A, B, C of the screen covariance of eq. 7). Staged per entry:
 //   isotropic    fp {u, v, q = log2(e)/s^2, log2(o)}
 //   anisotropic  fp {u, v, nA = -A log2(e), log2(o)}, cn {nB2 = -2 B log2(e), nC = -C log2(e)}
-// and col {r, g, b, slot bits}. Both families share the footprint record's layout for
+// and col {r, g, b, 0}. Both families share the footprint record's layout for
 // what binning reads (centre, radius), so they share the bin sort.
 template <bool AN>
 struct StagedSubT {
     float4 fp[kBatch + 1];
     float4 col[kBatch + 1];
     float2 cn[AN ? kBatch + 1 : 1];
-    uint32_t list[16][kBatch + 4];   // byte offsets (16 x staged slot) into fp and col
+    __align__(16) uint16_t list[16][kBatch + 4];   // byte offsets (16 x staged slot) into fp and col
     __align__(16) uint32_t cnt[4][16];   // [loader wave][sub-block]
+    __align__(16) uint32_t alive[4];     // [wave]: not 0 if a pixel of it is still open
 };
 using StagedSub = StagedSubT<false>;
 
@@ -90,23 +102,31 @@ struct SubLists {
 // distance is a column part plus a row part; a sub-block starting beyond the image has no
 // pixels. The forward and backward passes form the same FP32 sum, so they cull the same
 // entries. run_distances gives the parts: squared distances of the centre coordinate c to N
-// consecutive runs of four pixel centres from pixel coordinate `first` on, clipped at `lim`.
-// Neighbouring sub-blocks share them: a tile takes 8 parts and 16 sums where 16 separate
-// tests took 32 parts.
-template <int N>
+// consecutive runs of four pixel centres from pixel coordinate `first` on, clipped at `lim`;
+// with EDGE, a run beyond `lim` is infinitely far. Neighbouring sub-blocks share them: a tile
+// takes 8 parts and 16 sums where 16 separate tests took 32 parts.
+template <bool EDGE, int N>
 __device__ __forceinline__ void run_distances(float c, int first, float lim, float (&d2)[N]) {
     const float base = (float)first + 0.5f;
 #pragma unroll
     for (int q = 0; q < N; ++q) {
         const float lo = base + (float)(4 * q), hi = fminf(lo + 3.0f, lim);
-        const float d = fmaxf(fmaxf(lo - c, c - hi), 0.0f);
+        const float from = EDGE && lo > lim ? __builtin_inff() : lo;
+        const float d = fmaxf(fmaxf(from - c, c - hi), 0.0f);
         d2[q] = d * d;
     }
 }
 
+// Whether the bit of this lane is set in the wave-uniform m: m becomes the lane mask as it is.
+__device__ __forceinline__ bool lane_bit(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 // `first` plus the number of set bits of m in lanes below this one.
 __device__ __forceinline__ uint32_t rank_from(uint64_t m, uint32_t first) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, first));
+}
+// The word of a list at byte `first` (wave-uniform) plus the lane's rank in m: one shift-add.
+__device__ __forceinline__ uint16_t& list_word(uint16_t* list, uint32_t first, uint64_t m) {
+    return *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(list) + (first + 2u * rank_from(m, 0u)));
 }
 
 // One staged entry as loaded from global memory by its thread (k: the conic's B, C).
@@ -157,37 +177,46 @@ __device__ __forceinline__ EntryLoad load_entry(const float4* __restrict__ recor
     return e;
 }
 
+// Whether a pixel of the workgroup is still open, between two batches (one barrier, where
+// __syncthreads_and takes two and the block's dimensions). Every wave passes `open`.
+__device__ __forceinline__ bool any_alive(uint32_t (&alive)[4], bool open) {
+    const uint32_t w = threadIdx.x >> 6;
+    const uint64_t m = ballot64(open);
+    if (lane_id() == 0) alive[w] = m != 0;
+    __syncthreads();   // (the last batch's lists have been read as well)
+    const uint4 v = *reinterpret_cast<const uint4*>(alive);
+    return __builtin_amdgcn_readfirstlane((int)(v.x | v.y | v.z | v.w)) != 0;
+}
+
 // Stages the loaded entries of a batch (one per thread) and builds the 16 sub-block lists. The
 // list positions come from scalars (the wave's ballots and the waves' counts), about four
-// vector instructions per list. Contains __syncthreads.
+// vector instructions per list; a wave without entries passes by. Contains __syncthreads.
 template <bool AN>
 __device__ __forceinline__ SubLists stage_loaded(StagedSubT<AN>& sb, const EntryLoad& e, int tile_x0, int tile_y0,
                                                  float w_lim, float h_lim) {
     const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = lane_id();
-    float dxx[4], dyy[4], r2 = __builtin_nanf("");   // no entry: no comparison holds
-    if (e.ok) {
-        sb.fp[t] = staged_kernel<AN>(e.f);
-        if (AN) sb.cn[t] = staged_conic(e.k);
-        sb.col[t] = make_float4(e.c.x, e.c.y, e.c.z, __uint_as_float(t));   // w: the slot itself
-        r2 = e.c.w * e.c.w;
+    const bool mine = ballot64(e.ok) != 0;
+    uint64_t bal[16] = {};   // lanes whose entry joins list k
+    if (mine) {
+        if (e.ok) {
+            sb.fp[t] = staged_kernel<AN>(e.f);
+            if (AN) sb.cn[t] = staged_conic(e.k);
+            sb.col[t] = make_float4(e.c.x, e.c.y, e.c.z, 0.0f);
+        }
+        float dxx[4], dyy[4];
+        run_distances<true>(e.f.x, tile_x0, w_lim, dxx);
+        run_distances<true>(e.f.y, tile_y0, h_lim, dyy);
+        const float r2 = e.ok ? e.c.w * e.c.w : __builtin_nanf("");   // no entry: no comparison holds
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int qx = ((k >> 2) & 1) * 2 + (k & 1), qy = ((k >> 2) >> 1) * 2 + ((k & 3) >> 1);
+            bal[k] = ballot64(dxx[qx] + dyy[qy] <= r2);
+        }
     }
     if (t == 0) {
         sb.fp[kDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());
         if (AN) sb.cn[AN ? kDummy : 0] = make_float2(0.0f, 0.0f);
-        sb.col[kDummy] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)kDummy));
-    }
-    run_distances(e.f.x, tile_x0, w_lim, dxx);
-    run_distances(e.f.y, tile_y0, h_lim, dyy);
-    // (a sub-block beyond the image has no pixels and gets no list)
-    const int cols = __builtin_amdgcn_readfirstlane((int)(w_lim + 0.5f)) - tile_x0;
-    const int rows = __builtin_amdgcn_readfirstlane((int)(h_lim + 0.5f)) - tile_y0;
-    bool hit[16];
-    uint64_t bal[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int qx = ((k >> 2) & 1) * 2 + (k & 1), qy = ((k >> 2) >> 1) * 2 + ((k & 3) >> 1);
-        hit[k] = dxx[qx] + dyy[qy] <= r2 && 4 * qx < cols && 4 * qy < rows;
-        bal[k] = ballot64(hit[k]);
+        sb.col[kDummy] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
     if (l == 0) {
 #pragma unroll
@@ -198,17 +227,19 @@ __device__ __forceinline__ SubLists stage_loaded(StagedSubT<AN>& sb, const Entry
     const uint32_t c0 = sb.cnt[0][l & 15u], c1 = sb.cnt[1][l & 15u], c2 = sb.cnt[2][l & 15u], c3 = sb.cnt[3][l & 15u];
     const uint32_t n = c0 + c1 + c2 + c3, padded = (n + 3u) & ~3u;
     const uint32_t before = w == 0 ? 0u : w == 1 ? c0 : w == 2 ? c0 + c1 : c0 + c1 + c2;
+    if (mine) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t first = __builtin_amdgcn_readlane(before, k);
-        if (hit[k]) sb.list[k][rank_from(bal[k], first)] = t * kSlotBytes;
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t first = __builtin_amdgcn_readlane(2u * before, k);
+            if (lane_bit(bal[k])) list_word(sb.list[k], first, bal[k]) = (uint16_t)(t * kSlotBytes);
+        }
     }
     if (w == 0) {
         // pad list l / 4 with dummies up to a multiple of four, and four more: reads past the end
         const int k = (int)(l >> 2);
         const uint32_t nk = __shfl(n, k, kWave), pk = (nk + 3u) & ~3u, j = l & 3u;
-        if (nk + j < pk) sb.list[k][nk + j] = kDummy * kSlotBytes;
-        sb.list[k][pk + j] = kDummy * kSlotBytes;
+        if (nk + j < pk) sb.list[k][nk + j] = (uint16_t)(kDummy * kSlotBytes);
+        sb.list[k][pk + j] = (uint16_t)(kDummy * kSlotBytes);
     }
     SubLists L;
     L.len = __shfl(padded, (int)(4u * w + (l >> 4)), kWave);
@@ -232,18 +263,19 @@ __device__ __forceinline__ SubLists stage_batch_sub(StagedSubT<AN>& sb, const fl
 // Byte offsets of four consecutive entries of this lane's sub-block list (padded length
 // `len`) from step k; a step at or past the end reads the four dummies that follow the list.
 template <bool AN>
-__device__ __forceinline__ uint4 list4_sub(const StagedSubT<AN>& sb, uint32_t sbk, uint32_t k, uint32_t len) {
-    return *reinterpret_cast<const uint4*>(&sb.list[sbk][min(k, len)]);
+__device__ __forceinline__ uint2 list4_sub(const StagedSubT<AN>& sb, uint32_t sbk, uint32_t k, uint32_t len) {
+    return *reinterpret_cast<const uint2*>(&sb.list[sbk][min(k, len)]);
 }
 
-// Staged record, colour and conic of the entry at byte offset `off` (16 bytes per slot).
+// Staged record of the entry at byte offset `off` (16 bytes per slot).
 template <bool AN>
 __device__ __forceinline__ float4 staged_fp(const StagedSubT<AN>& sb, uint32_t off) {
     return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(sb.fp) + off);
 }
+// Colour component (lane % 4) of the entry at byte offset `off`.
 template <bool AN>
-__device__ __forceinline__ float4 staged_col(const StagedSubT<AN>& sb, uint32_t off) {
-    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(sb.col) + off);
+__device__ __forceinline__ float staged_component(const StagedSubT<AN>& sb, uint32_t off) {
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(sb.col) + (off + 4u * (threadIdx.x & 3u)));
 }
 template <bool AN>
 __device__ __forceinline__ float2 staged_cn(const StagedSubT<AN>& sb, uint32_t off) {
