@@ -339,8 +339,8 @@ int isogs_aniso_render_fwd(const isogs_aniso_projected* proj, const int32_t* n_p
 
 /* isogs_render_bwd for the anisotropic family: gradients of the centre, the quaternion
  * (through its normalisation), the three scales, the opacity and the colour coefficients.
- * The workspace holds 48 bytes per entry of capacity (each entry's nine gradient sums)
- * instead of 32; everything else as isogs_render_bwd. */
+ * The workspace holds 49 bytes per entry of capacity (each entry's nine gradient sums and
+ * its mark) instead of 33; everything else as isogs_render_bwd. */
 int isogs_aniso_render_bwd(const isogs_aniso_scene* scenes, const isogs_camera* cams, int32_t n_views,
                            const isogs_aniso_projected* proj, const isogs_bins* bins, const float* bg,
                            const float* image, const float* dL_dimage, const float* T_final,

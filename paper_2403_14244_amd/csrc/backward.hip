@@ -59,8 +59,12 @@ constexpr int kTransPitch = 20;   // floats per row of the transposing buffer: b
 // longer lists leave less of a wave idle: with 48 entries a wave's four lists had 2.2
 // four-entry steps between two barriers. A round whose pairs exceed the capacity keeps only
 // its first entries; the rest go to the next round.
+// As many pairs as let four workgroups reside on a CU: a larger capacity with three, or a smaller
+// one with five (which cuts more rounds), is slower. One 1080p view, and eight 4K views of 6M
+// particles: 185 us and 4.92 ms with 640 pairs, 182 us and 4.75 ms with 744, 192 us and 5.44 ms
+// with 1008 (three workgroups), 198 us and 5.13 ms with 480 (five).
 template <bool AN>
-constexpr uint32_t kPairCap = AN ? 480 : 640;   // four workgroups' LDS per CU
+constexpr uint32_t kPairCap = AN ? 480 : 744;
 constexpr uint32_t kPairPad = 16 * 3;   // padding of the 16 lists at most
 template <bool AN>
 constexpr int kPartPitch = AN ? 12 : 8;
@@ -130,11 +134,24 @@ __device__ __forceinline__ uint32_t row_inclusive_scan(uint32_t x) {
     return x;
 }
 
-// Lanes l of wave w whose thread index 64 w + l is at least `first` (scalar arithmetic).
-__device__ __forceinline__ uint64_t lanes_from(uint32_t first, uint32_t w) {
-    const uint32_t s = first > 64u * w ? first - 64u * w : 0u;
-    return s < 64u ? ~0ull << s : 0ull;
+// Inclusive scan over the wave's lanes.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+    x = row_inclusive_scan(x);
+    const uint32_t r0 = __builtin_amdgcn_readlane(x, 15), r1 = r0 + __builtin_amdgcn_readlane(x, 31),
+                   r2 = r1 + __builtin_amdgcn_readlane(x, 47), l = lane_id();
+    return x + (l < 16u ? 0u : l < 32u ? r0 : l < 48u ? r1 : r2);
 }
+
+// The largest value of each 16-lane row, in the row's lanes.
+__device__ __forceinline__ uint32_t row_max(uint32_t x) {
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, true));   // row_ror:1
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));
+    return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));
+}
+
+// The lanes from `first` on (64: none), in scalar registers.
+__device__ __forceinline__ uint64_t lanes_from(uint32_t first) { return first < 64u ? ~0ull << first : 0ull; }
 
 // Stages a round's entries and builds the 16 sub-block lists. An entry joins a sub-block's
 // list when its binning disk reaches the sub-block (run_distances) and its position
@@ -144,18 +161,28 @@ template <bool AN>
 __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, uint32_t nb, uint32_t pos_hi, int tx,
                                               int ty, int tiles_x, int tiles_y, float w_lim, float h_lim) {
     const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = lane_id();
-    float dxx[4], dyy[4], r2 = __builtin_nanf("");   // no entry: no comparison holds
-    {
+    // lane k (mod 16): the wave's first lane whose entry list k takes (64: none); a sub-block
+    // without pixels has gmax 0 and takes none
+    const uint32_t gm = sb.gmax[l & 15u], skip = pos_hi > gm ? pos_hi - gm : 0u;
+    const uint32_t from = skip > 64u * w ? min(skip - 64u * w, 64u) : 0u;
+    const bool mine = ballot64(from < 64u) != 0 && 64u * w < nb;
+    uint64_t bal[16] = {};   // lanes whose entry joins list k
+    if (mine) {
         const float4 f = b.e.f, c = b.e.c;
         if (b.e.ok) {
             sb.fp[t] = staged_kernel<AN>(f);
             sb.col[t] = make_float4(c.x, c.y, c.z, __builtin_amdgcn_rcpf(f.w));   // once per entry
             if (AN) sb.cn[t] = staged_conic(b.e.k);
-            r2 = c.w * c.w;
         }
-        // (a sub-block without pixels has gmax 0 and keeps no entry)
+        float dxx[4], dyy[4];
         run_distances<false>(f.x, tx * kTile, w_lim, dxx);
         run_distances<false>(f.y, ty * kTile, h_lim, dyy);
+        const float r2 = b.e.ok ? c.w * c.w : __builtin_nanf("");   // no entry: no comparison holds
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int qx = ((k >> 2) & 1) * 2 + (k & 1), qy = ((k >> 2) >> 1) * 2 + ((k & 3) >> 1);
+            bal[k] = ballot64(dxx[qx] + dyy[qy] <= r2) & lanes_from(__builtin_amdgcn_readlane(from, k));
+        }
     }
     if (t == 0) {
         sb.fp[kBwdDummy] = make_float4(0.0f, 0.0f, 0.0f, -__builtin_inff());
@@ -164,13 +191,6 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
     }
     BwdLists L;
     L.kept = nb;
-    uint64_t bal[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t gm = __builtin_amdgcn_readfirstlane(sb.gmax[k]);
-        const int qx = ((k >> 2) & 1) * 2 + (k & 1), qy = ((k >> 2) >> 1) * 2 + ((k & 3) >> 1);
-        bal[k] = ballot64(dxx[qx] + dyy[qy] <= r2) & lanes_from(pos_hi > gm ? pos_hi - gm : 0u, w);
-    }
     uint32_t n = 0, before = 0, total = 0;   // lane k (mod 16): list k's length, entries of earlier waves
     for (int attempt = 0;; ++attempt) {
         if (l == 0) {
@@ -182,17 +202,13 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
                        c3 = sb.cnt[3][l & 15u];
         n = c0 + c1 + c2 + c3;
         before = (w > 0 ? c0 : 0u) + (w > 1 ? c1 : 0u) + (w > 2 ? c2 : 0u);
-        total = __builtin_amdgcn_readlane(row_inclusive_scan(n), 15);
-        if (attempt || total + kPairPad <= kPairCap<AN>) break;
+        total = __builtin_amdgcn_readlane(row_inclusive_scan((n + 3u) & ~3u), 15);   // with the padding
+        if (attempt || total <= kPairCap<AN>) break;
         // too many pairs: keep the first entries that fit (at least (cap - pad) / 16)
         uint32_t incl = 0;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) incl += (uint32_t)(bal[k] >> l) & 1u;
-#pragma unroll
-        for (uint32_t o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(incl, o, 64);
-            if (l >= o) incl += y;
-        }
+        for (int k = 0; k < 16; ++k) incl += lane_bit(bal[k]) ? 1u : 0u;
+        incl = wave_inclusive_scan(incl);
         if (l == 63) sb.kept[w] = incl;
         __syncthreads();
 #pragma unroll
@@ -208,17 +224,20 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
     // lists back to back: lane k (mod 16) holds list k's padded length and first index
     const uint32_t padded = (n + 3u) & ~3u;
     const uint32_t base = row_inclusive_scan(padded) - padded, at = base + before;
+    if (mine) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t first = __builtin_amdgcn_readlane(at, k);
-        if ((bal[k] >> l) & 1u) {
-            const uint32_t i = rank_from(bal[k], first);
-            sb.list[i] = (uint16_t)(t * kSlotBytes);
-            sb.link[i] = (uint16_t)b.head;
-            b.head = i | (uint32_t)k << kLinkShift;
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t first = __builtin_amdgcn_readlane(at, k);
+            if (lane_bit(bal[k])) {
+                const uint32_t i = first + rank_from(bal[k], 0u);
+                sb.list[i] = (uint16_t)(t * kSlotBytes);
+                sb.link[i] = (uint16_t)b.head;
+                b.head = i | (uint32_t)k << kLinkShift;
+            }
         }
+        if (b.head != kLinkEnd)
+            b.slot = emit_slot(b.slot, b.e.f.x, b.e.f.y, b.e.c.w, tx, ty, tiles_x, tiles_y, w_lim, h_lim);
     }
-    if (b.e.ok) b.slot = emit_slot(b.slot, b.e.f.x, b.e.f.y, b.e.c.w, tx, ty, tiles_x, tiles_y, w_lim, h_lim);
     if (w == 0) {
         // pad list l / 4 with dummies
         const int k = (int)(l >> 2);
@@ -298,13 +317,13 @@ __device__ __forceinline__ void composite_bwd_tile(
         }
     }
 
-    if (t < 16) sb.gmax[t] = 0u;
     sb.dL[w][0][lane] = dr;
     sb.dL[w][1][lane] = dg;
     sb.dL[w][2][lane] = db;
+    const uint32_t most = row_max(last > c_lo ? min(last, c_hi) : 0u);
+    if ((lane & 15u) == 0) sb.gmax[sbk] = most;
     __syncthreads();
-    if (last > c_lo) atomicMax(&sb.gmax[sbk], min(last, c_hi));
-    if (!__syncthreads_or(last > c_lo)) return;   // no pixel composited an entry from here on
+    if (ballot64(sb.gmax[lane & 15u] != 0u) == 0) return;   // no pixel composited an entry from here on
 
     // B operands of the reduction, one register per K step m (K index lane / 16, pixel
     // 4 (lane / 16) + m of a sub-block, i.e. X = m - 1.5, Y = lane / 16 - 1.5): column
