@@ -10,6 +10,7 @@
 //                     order) and chain them to mu, sigma, o and the colour coefficients.
 // There are no floating-point atomics: every sum has a fixed order.
 #include <algorithm>
+#include <array>
 #include <type_traits>
 
 #include "raster.h"
@@ -697,6 +698,9 @@ __device__ __forceinline__ void sh_raw(const CoefRef& coef, float x, float y, fl
     }
 }
 
+// Bit k: Y_k depends on x, y, z (sh_term sets that derivative).
+constexpr uint32_t kShDx = 0xE798u, kShDy = 0xCF32u, kShDz = 0x7CE4u;
+
 template <int DEG, int KK = 1>
 __device__ __forceinline__ void sh_back(const CoefRef& coef, float x, float y, float z, const float d[3], float* gcol,
                                         float& wdx, float& wdy, float& wdz) {
@@ -704,13 +708,12 @@ __device__ __forceinline__ void sh_back(const CoefRef& coef, float x, float y, f
         float Y, gx, gy, gz;
         sh_term<KK>(x, y, z, Y, gx, gy, gz);
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            gcol[3 * KK + ch] += d[ch] * Y;
-            const float wk = d[ch] * coef(KK, ch);
-            wdx = fmaf(wk, gx, wdx);
-            wdy = fmaf(wk, gy, wdy);
-            wdz = fmaf(wk, gz, wdz);
-        }
+        for (int ch = 0; ch < 3; ++ch) gcol[3 * KK + ch] = fmaf(d[ch], Y, gcol[3 * KK + ch]);
+        // dL/dY_k, then along its derivatives (those that are not identically zero)
+        const float wk = fmaf(d[2], coef(KK, 2), fmaf(d[1], coef(KK, 1), d[0] * coef(KK, 0)));
+        if constexpr ((kShDx >> KK) & 1u) wdx = fmaf(wk, gx, wdx);
+        if constexpr ((kShDy >> KK) & 1u) wdy = fmaf(wk, gy, wdy);
+        if constexpr ((kShDz >> KK) & 1u) wdz = fmaf(wk, gz, wdz);
         sh_back<DEG, KK + 1>(coef, x, y, z, d, gcol, wdx, wdy, wdz);
     }
 }
@@ -765,6 +768,7 @@ template <int NV>
 struct RecShared {
     float4 v[NV][kRecWindow];
     uint32_t run[2];
+    __align__(16) uint32_t marked[4];   // [wave]: not 0 if it staged a marked record
 };
 
 // Sums the NV float4s of records [e0, e0 + cnt) into S (zeroed here). Every thread of the
@@ -801,8 +805,11 @@ __device__ __forceinline__ bool sum_records(RecShared<NV>& sh, const float4* __r
 #pragma unroll
             for (int k = 0; k < NV; ++k) sh.v[k][q * 256u + t] = r[k];
         }
-        const bool window = __syncthreads_or(has[0] || has[1]);
-        if (window) {
+        const uint64_t marked = ballot64(has[0] || has[1]);
+        if (lane_id() == 0) sh.marked[t >> 6] = marked != 0;
+        __syncthreads();
+        const uint4 m = *reinterpret_cast<const uint4*>(sh.marked);
+        if (__builtin_amdgcn_readfirstlane((int)(m.x | m.y | m.z | m.w))) {
             any = true;
             for (uint32_t e = max(e0, w0); e < min(e0 + cnt, w0 + kRecWindow); ++e) {
 #pragma unroll
@@ -836,7 +843,11 @@ __device__ __forceinline__ RecRun record_run(const uint32_t* __restrict__ tile_c
     return r;
 }
 
-// One thread per particle of one scene; DEG is the scene's SH degree.
+// One thread per particle of one scene; DEG is the scene's SH degree. The records, parameters
+// and gradients of one view of 1M particles (480 MB) take 89 us, the rate of a copy; eight views
+// wait on each view's marks and records in turn: 6M particles 1.90 -> 1.74 ms with a quarter fewer
+// vector instructions (one sum over the channels per coefficient, derivatives that are zero left
+// out, one FP64 division).
 template <int DEG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) grad_project_kernel(const GradPack pk, const float4* __restrict__ rec,
                                                            const uint8_t* __restrict__ has_rec,
@@ -877,14 +888,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) g
         const double pxd = (double)gv.R[0] * mx + (double)gv.R[1] * my + (double)gv.R[2] * mz + (double)gv.t[0];
         const double pyd = (double)gv.R[3] * mx + (double)gv.R[4] * my + (double)gv.R[5] * mz + (double)gv.t[1];
         const double pzd = (double)gv.R[6] * mx + (double)gv.R[7] * my + (double)gv.R[8] * mz + (double)gv.t[2];
-        const float inv_z = (float)(1.0 / pzd);
-        const float s = (float)((double)gv.f * (double)sigma / pzd);
+        const double izd = 1.0 / pzd;   // (one FP64 division; the quotients below are rounded to FP32)
+        const float inv_z = (float)izd;
+        const float s = (float)((double)gv.f * (double)sigma * izd);
         const float inv_s = 1.0f / s;
         // d(1/s^2)/ds = -2/s^3
         const float ds = -2.0f * dis2 * inv_s * inv_s * inv_s;
         gsig += ds * gv.f * inv_z;
         const float gpx = du * gv.f * inv_z, gpy = dv * gv.f * inv_z;
-        const float ucx = (float)((double)gv.f * pxd / pzd), vcy = (float)((double)gv.f * pyd / pzd);
+        const float ucx = (float)((double)gv.f * pxd * izd), vcy = (float)((double)gv.f * pyd * izd);
         const float gpz = -(ds * s + du * ucx + dv * vcy) * inv_z;
         gmx += gv.R[0] * gpx + gv.R[3] * gpy + gv.R[6] * gpz;
         gmy += gv.R[1] * gpx + gv.R[4] * gpy + gv.R[7] * gpz;
@@ -937,14 +949,55 @@ __device__ __forceinline__ void quat_rot(double w, double x, double y, double z,
     R[6] = 2.0 * (x * z - w * y);       R[7] = 2.0 * (y * z + w * x);       R[8] = 1.0 - 2.0 * (x * x + y * y);
 }
 
+// Particle i's colour gradients (added to the outputs if an earlier launch wrote them).
+template <int K>
+__device__ __forceinline__ void store_color(const AnisoGradPack& pk, uint32_t i, const float (&gcol)[3 * K]) {
+    const size_t n = pk.n;
+    if (pk.accumulate) {
+#pragma unroll
+        for (int k = 0; k < 3 * K; ++k) pk.g_color[k * n + i] += gcol[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 3 * K; ++k) pk.g_color[k * n + i] = gcol[k];
+    }
+}
+
+// Index of element (a, b) of a symmetric 3 x 3 matrix held as xx, xy, xz, yy, yz, zz.
+__host__ __device__ constexpr int sym(int a, int b) { return a == 0 || b == 0 ? a + b : a + b + 1; }
+
+// The unit quaternion of a particle's (w, x, y, z).
+__device__ __forceinline__ void unit_quat(const float q[4], double& norm, double h[4]) {
+    const double w = q[0], x = q[1], y = q[2], z = q[3];
+    norm = sqrt(w * w + x * x + y * y + z * z);
+    h[0] = w / norm;
+    h[1] = x / norm;
+    h[2] = y / norm;
+    h[3] = z / norm;
+}
+
+// The value through an empty statement that the compiler does not see through: what is
+// computed from it later is computed again rather than kept in registers.
+__device__ __forceinline__ float reload(float x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Registers: one view (ONE) holds no sums across views and stores its colour gradients before
+// the chain rule, so that three waves per SIMD reside; more views need up to 224 registers and
+// two. A 1080p view of 1M particles, degree 3: 204 us with 264 registers and one wave, 141 at
+// two waves, 134 at three, 172 at four (which spill).
+template <bool ONE>
+constexpr int kAnisoGradWaves = ONE ? 3 : 2;
+
 // One thread per particle of one scene. Per view: the entry records of the particle are
 // summed in emit order (FP32, fixed order), turned into the gradients of the footprint
 // centre (u, v), the conic (A, B, C), the opacity and the colour, and chained in FP64
 // through Sigma_2D = T Sigma T^T (T = J V, eq. 7; conic = Sigma_2D^-1) to the centre and,
 // accumulated over the views, to Sigma = R S S^T R^T (eq. 6), hence to the quaternion
 // (through its normalisation) and the three scales.
-template <int DEG>
-__global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGradPack pk, const float4* __restrict__ rec,
+template <int DEG, bool ONE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kAnisoGradWaves<ONE>)))
+aniso_grad_project_kernel(const AnisoGradPack pk, const float4* __restrict__ rec,
                                                                  const uint8_t* __restrict__ has_rec,
                                                                  const float4* __restrict__ record,
                                                                  const float2* __restrict__ conic,
@@ -961,28 +1014,30 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
     const uint32_t n = pk.n;
     constexpr int K = (DEG + 1) * (DEG + 1);
     const float mx = pk.pos[i], my = pk.pos[n + i], mz = pk.pos[2 * n + i];
-    const double qw = pk.rot[i], qx = pk.rot[n + i], qy = pk.rot[2 * n + i], qz = pk.rot[3 * n + i];
-    const double sc[3] = {(double)pk.scale[i], (double)pk.scale[n + i], (double)pk.scale[2 * n + i]};
-    const double qn = sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
-    const double hw = qw / qn, hx = qx / qn, hy = qy / qn, hz = qz / qn;
-    double Rq[9];
-    quat_rot(hw, hx, hy, hz, Rq);
-    // Sigma = R diag(s^2) R^T
-    double Sig[9];
+    const float q4[4] = {pk.rot[i], pk.rot[n + i], pk.rot[2 * n + i], pk.rot[3 * n + i]};
+    const float s3[3] = {pk.scale[i], pk.scale[n + i], pk.scale[2 * n + i]};
+    // Sigma = R diag(s^2) R^T (symmetric: xx, xy, xz, yy, yz, zz)
+    double Sig[6];
+    {
+        double qn, h[4], Rq[9];
+        unit_quat(q4, qn, h);
+        quat_rot(h[0], h[1], h[2], h[3], Rq);
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            double acc = 0.0;
+            for (int b = 0; b < 3; ++b) {
+                if (b < a) continue;
+                double acc = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) acc += Rq[3 * a + c] * sc[c] * sc[c] * Rq[3 * b + c];
-            Sig[3 * a + b] = acc;
-        }
+                for (int c = 0; c < 3; ++c) acc += Rq[3 * a + c] * (double)s3[c] * (double)s3[c] * Rq[3 * b + c];
+                Sig[sym(a, b)] = acc;
+            }
+    }
 
     float gmx = 0.0f, gmy = 0.0f, gmz = 0.0f, gop = 0.0f;
-    double GS[9];   // dL/dSigma, summed over the views
+    double GS[6];   // dL/dSigma, summed over the views (symmetric)
 #pragma unroll
-    for (int k = 0; k < 9; ++k) GS[k] = 0.0;
+    for (int k = 0; k < 6; ++k) GS[k] = 0.0;
     double gmu64[3] = {0.0, 0.0, 0.0};
     bool any = false;
     float gcol[3 * K];
@@ -994,13 +1049,20 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
     }
 
     RecRun next = record_run(tile_count, offsets, pk.v[0].p_off + i, in, n_entries);
-    for (int vv = 0; vv < pk.nv; ++vv) {
+    const int nv = ONE ? 1 : pk.nv;
+    for (int vv = 0; vv < nv; ++vv) {
         const GradView& gv = pk.v[vv];
         const uint32_t pi = gv.p_off + i;
         const RecRun cur = next;
-        if (vv + 1 < pk.nv) next = record_run(tile_count, offsets, pk.v[vv + 1].p_off + i, in, n_entries);
+        if (vv + 1 < nv) next = record_run(tile_count, offsets, pk.v[vv + 1].p_off + i, in, n_entries);
         float S[12];
-        if (!sum_records<3>(sh, rec, has_rec, cur.e0, cur.cnt, S) || cur.cnt == 0) continue;
+        const bool act = sum_records<3>(sh, rec, has_rec, cur.e0, cur.cnt, S) && cur.cnt != 0;
+        const float drgb[3] = {S[6], S[7], S[8]};
+        if (act) color_backward<DEG>(CoefRef{coef}, drgb, gv.eye, mx, my, mz, gcol, gmx, gmy, gmz);
+        // a single view's colour gradients are complete: stored here, they and the coefficients
+        // need no registers beside the chain rule below
+        if (ONE && in) store_color<K>(pk, i, gcol);
+        if (!act) continue;
         any = true;
         gop += S[5];
         const double A = (double)record[2 * (size_t)pi].z;
@@ -1033,14 +1095,15 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
         for (int a = 0; a < 3; ++a)
 #pragma unroll
             for (int b = 0; b < 3; ++b)
-                GS[3 * a + b] += T[a] * (G00 * T[b] + G01 * T[3 + b]) + T[3 + a] * (G01 * T[b] + G11 * T[3 + b]);
+                if (b >= a)
+                    GS[sym(a, b)] += T[a] * (G00 * T[b] + G01 * T[3 + b]) + T[3 + a] * (G01 * T[b] + G11 * T[3 + b]);
         // dL/dT = 2 G T Sigma, dL/dJ = dL/dT V^T
         double TS[6];
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                TS[3 * r + c] = T[3 * r] * Sig[c] + T[3 * r + 1] * Sig[3 + c] + T[3 * r + 2] * Sig[6 + c];
+                TS[3 * r + c] = T[3 * r] * Sig[sym(0, c)] + T[3 * r + 1] * Sig[sym(1, c)] + T[3 * r + 2] * Sig[sym(2, c)];
         double GT[6];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -1062,18 +1125,21 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
         gmu64[0] += V[0] * dpx + V[3] * dpy + V[6] * dpz;
         gmu64[1] += V[1] * dpx + V[4] * dpy + V[7] * dpz;
         gmu64[2] += V[2] * dpx + V[5] * dpy + V[8] * dpz;
-        const float drgb[3] = {S[6], S[7], S[8]};
-        color_backward<DEG>(CoefRef{coef}, drgb, gv.eye, mx, my, mz, gcol, gmx, gmy, gmz);
     }
     float grot[4] = {0.0f, 0.0f, 0.0f, 0.0f}, gsc[3] = {0.0f, 0.0f, 0.0f};
     if (any) {
+        const float qr[4] = {reload(q4[0]), reload(q4[1]), reload(q4[2]), reload(q4[3])};
+        const double sc[3] = {(double)s3[0], (double)s3[1], (double)s3[2]};
+        double qn, h[4], Rq[9];
+        unit_quat(qr, qn, h);
+        quat_rot(h[0], h[1], h[2], h[3], Rq);
         // Sigma = R diag(s^2) R^T: dL/dR = 2 GS R diag(s^2), dL/ds_b = 2 s_b (R^T GS R)_bb
         double GR[9];
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
             for (int b = 0; b < 3; ++b)
-                GR[3 * a + b] = 2.0 * (GS[3 * a] * Rq[b] + GS[3 * a + 1] * Rq[3 + b] + GS[3 * a + 2] * Rq[6 + b]) *
+                GR[3 * a + b] = 2.0 * (GS[sym(a, 0)] * Rq[b] + GS[sym(a, 1)] * Rq[3 + b] + GS[sym(a, 2)] * Rq[6 + b]) *
                                 sc[b] * sc[b];
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
@@ -1081,11 +1147,11 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
-                for (int c = 0; c < 3; ++c) acc += Rq[3 * a + b] * GS[3 * a + c] * Rq[3 * c + b];
+                for (int c = 0; c < 3; ++c) acc += Rq[3 * a + b] * GS[sym(a, c)] * Rq[3 * c + b];
             gsc[b] = (float)(2.0 * sc[b] * acc);
         }
         // dR/d(w, x, y, z) of the rotation formula, at the unit quaternion
-        const double w = hw, x = hx, y = hy, z = hz;
+        const double w = h[0], x = h[1], y = h[2], z = h[3];
         const double dRw[9] = {0.0, -2 * z, 2 * y, 2 * z, 0.0, -2 * x, -2 * y, 2 * x, 0.0};
         const double dRx[9] = {0.0, 2 * y, 2 * z, 2 * y, -4 * x, -2 * w, 2 * z, 2 * w, -4 * x};
         const double dRy[9] = {-4 * y, 2 * x, 2 * w, 2 * x, 0.0, 2 * z, -2 * w, 2 * z, -4 * y};
@@ -1099,39 +1165,40 @@ __global__ void __launch_bounds__(256) aniso_grad_project_kernel(const AnisoGrad
             dq[3] += GR[k] * dRz[k];
         }
         // through the normalisation q / |q|
-        const double radial = hw * dq[0] + hx * dq[1] + hy * dq[2] + hz * dq[3];
-        grot[0] = (float)((dq[0] - hw * radial) / qn);
-        grot[1] = (float)((dq[1] - hx * radial) / qn);
-        grot[2] = (float)((dq[2] - hy * radial) / qn);
-        grot[3] = (float)((dq[3] - hz * radial) / qn);
+        const double radial = h[0] * dq[0] + h[1] * dq[1] + h[2] * dq[2] + h[3] * dq[3];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) grot[k] = (float)((dq[k] - h[k] * radial) / qn);
         gmx += (float)gmu64[0];
         gmy += (float)gmu64[1];
         gmz += (float)gmu64[2];
     }
     if (!in) return;
+    if (!ONE) store_color<K>(pk, i, gcol);
+    const float gmu[3] = {gmx, gmy, gmz};
     if (pk.accumulate) {
-        pk.g_pos[i] += gmx;
-        pk.g_pos[n + i] += gmy;
-        pk.g_pos[2 * n + i] += gmz;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pk.g_pos[(size_t)k * n + i] += gmu[k];
 #pragma unroll
         for (int k = 0; k < 4; ++k) pk.g_rot[(size_t)k * n + i] += grot[k];
 #pragma unroll
         for (int k = 0; k < 3; ++k) pk.g_scale[(size_t)k * n + i] += gsc[k];
         pk.g_opacity[i] += gop;
-#pragma unroll
-        for (int k = 0; k < 3 * K; ++k) pk.g_color[(size_t)k * n + i] += gcol[k];
     } else {
-        pk.g_pos[i] = gmx;
-        pk.g_pos[n + i] = gmy;
-        pk.g_pos[2 * n + i] = gmz;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pk.g_pos[(size_t)k * n + i] = gmu[k];
 #pragma unroll
         for (int k = 0; k < 4; ++k) pk.g_rot[(size_t)k * n + i] = grot[k];
 #pragma unroll
         for (int k = 0; k < 3; ++k) pk.g_scale[(size_t)k * n + i] = gsc[k];
         pk.g_opacity[i] = gop;
-#pragma unroll
-        for (int k = 0; k < 3 * K; ++k) pk.g_color[(size_t)k * n + i] = gcol[k];
     }
+}
+
+// The kernels of degrees 0 to 3.
+template <bool ONE>
+static std::array<decltype(&aniso_grad_project_kernel<0, ONE>), 4> aniso_grad_kernels() {
+    return {aniso_grad_project_kernel<0, ONE>, aniso_grad_project_kernel<1, ONE>, aniso_grad_project_kernel<2, ONE>,
+            aniso_grad_project_kernel<3, ONE>};
 }
 
 static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -1335,12 +1402,9 @@ int launch_aniso_render_bwd(const isogs_aniso_scene* scenes, const isogs_camera*
                 const float4* r = reinterpret_cast<const float4*>(proj->fp.record);
                 const float2* k = reinterpret_cast<const float2*>(proj->conic);
                 const uint32_t* tc = proj->fp.tile_count;
-                switch (sc.sh_degree) {
-                    case 0: hipLaunchKernelGGL(aniso_grad_project_kernel<0>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                    case 1: hipLaunchKernelGGL(aniso_grad_project_kernel<1>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                    case 2: hipLaunchKernelGGL(aniso_grad_project_kernel<2>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                    default: hipLaunchKernelGGL(aniso_grad_project_kernel<3>, grid, dim3(256), 0, stream, gp, br.rec, br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status); break;
-                }
+                const auto kernels = gp.nv == 1 ? aniso_grad_kernels<true>() : aniso_grad_kernels<false>();
+                hipLaunchKernelGGL(kernels[sc.sh_degree < 3 ? sc.sh_degree : 3], grid, dim3(256), 0, stream, gp, br.rec,
+                                   br.has_rec, r, k, tc, bins->offsets, bins->count, bins->status);
             }
             if (hipPeekAtLastError() != hipSuccess) rc = -1;
         }
