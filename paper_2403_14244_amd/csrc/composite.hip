@@ -10,25 +10,24 @@ using f32x4 = float __attribute__((ext_vector_type(4)));
 // Composites one staged entry into a pixel's running state (branch-free; the dummy pad
 // record has log2(o) = -inf, so alpha = 0 and it changes nothing). T loses the weight it
 // gives away, T - alpha T; with LAST, `lastoff` keeps the byte offset of the last entry used
-// in the current batch (offsets only increase along a list). TERM: the pixel stops after the
-// entry that takes T below kTMin.
+// in the current batch (offsets only increase along a list). The pixel stops after the entry
+// that takes T below kTMin.
 // The colour sums come from the matrix cores: v_mfma_f32_4x4x1 takes one entry for the 16
 // lane quads of the wave, whose lane i reads colour component i (`ch`) of the quad's entry,
 // and adds component * weight to all three sums of the quad's four pixels (rgb.w stays 0).
 // Beside three FMAs this saves three quarters of the LDS bytes of the colours, which every
 // lane would read whole.
-template <bool TERM, bool AN, bool LAST = true>
+template <bool AN, bool LAST>
 __device__ __forceinline__ void composite_entry(const float4& f, float ch, const float2& k, uint32_t off, float px,
-                                                float py, float& T, f32x4& rgb, uint32_t& lastoff, bool& done) {
+                                                float py, float& T, f32x4& rgb, uint32_t& lastoff) {
     float g;
     float a = staged_alpha<AN>(px - f.x, py - f.y, f, k, g);
-    const bool use = (a >= kAlphaMin) && !done;
+    const bool use = a >= kAlphaMin && !(T < kTMin);
     a = use ? a : 0.0f;
     const float wgt = a * T;
     rgb = __builtin_amdgcn_mfma_f32_4x4x1f32(ch, wgt, rgb, 0, 0, 0);
     T = T - wgt;
     if (LAST) lastoff = use ? off : lastoff;
-    if (TERM) done = done || (T < kTMin);
 }
 
 // The four entries of one list step: offsets -> staged records (k: conics, anisotropic) and
@@ -65,10 +64,10 @@ struct TilePixel {
 };
 
 struct PixelState {
-    float T;
+    float T;         // below kTMin: closed (a pixel outside the image from the start, with 0)
     f32x4 rgb;
     uint32_t last;   // 1-based tile-list position of the last entry used, 0 if none
-    bool done;
+    __device__ __forceinline__ bool open() const { return !(T < kTMin); }
 };
 
 __device__ __forceinline__ TilePixel tile_pixel(const RenderPack& pk, uint32_t logical,
@@ -106,7 +105,7 @@ __device__ __forceinline__ TilePixel tile_pixel(const RenderPack& pk, uint32_t l
 // wait on dependent round trips.
 // LAST: track the last entry used (s.last); without it s.last stays 0.
 // Contains __syncthreads.
-template <bool TERM, bool PIPE, bool PL, bool AN, bool LAST = true>
+template <bool PIPE, bool PL, bool AN, bool LAST = true>
 __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const RenderPack& pk, const TilePixel& p,
                                                 const float4* __restrict__ record, const float2* __restrict__ conic,
                                                 const uint32_t* __restrict__ pidx, uint32_t lo, uint32_t hi,
@@ -124,7 +123,7 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
         g_next = batch_pidx(pidx, b0 + kBatch, batch_len(b0 + kBatch));
     }
     for (; b0 < end; b0 += kBatch) {
-        if (b0 != p.start + lo && !any_alive(sb.alive, !s.done)) break;
+        if (b0 != p.start + lo && !any_alive(sb.alive, s.open())) break;
         if (ckpt && chunked_list(p.len) && b0 > p.start && (b0 - p.start) % kCkptChunk == 0)
             ckpt[(size_t)ckpt_slot(p.start, (b0 - p.start) / kCkptChunk) * 256 + t] =
                 make_float4(s.T, s.rgb.x, s.rgb.y, s.rgb.z);
@@ -143,15 +142,14 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
         auto composite_step = [&](const Step4& st) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                composite_entry<TERM, AN, LAST>(st.f[e], st.c[e], st.k[e], st.o[e], p.px, p.py, s.T, s.rgb, lastoff,
-                                                s.done);
+                composite_entry<AN, LAST>(st.f[e], st.c[e], st.k[e], st.o[e], p.px, p.py, s.T, s.rgb, lastoff);
         };
         if (!PL) {
             for (uint32_t k = 0; k < steps; k += 4) {
                 Step4 st;
                 load_step(sb, list4_sub(sb, p.sbk, k, len), st);
                 composite_step(st);
-                if (TERM && ballot64(!s.done) == 0) break;
+                if (ballot64(s.open()) == 0) break;
             }
         } else {
             // two register sets in turn, unrolled so that neither is copied: while one
@@ -166,12 +164,12 @@ __device__ __forceinline__ void composite_range(StagedSubT<AN>& sb, const Render
                 o = list4_sub(sb, p.sbk, k + 8, len);
                 __builtin_amdgcn_sched_barrier(0);
                 composite_step(sa);
-                if (TERM && ballot64(!s.done) == 0) break;
+                if (ballot64(s.open()) == 0) break;
                 load_step(sb, o, sa);
                 o = list4_sub(sb, p.sbk, k + 12, len);
                 __builtin_amdgcn_sched_barrier(0);
                 composite_step(sc);   // past the end of the lists: dummies only
-                if (TERM && ballot64(!s.done) == 0) break;
+                if (ballot64(s.open()) == 0) break;
             }
         }
         if (LAST && lastoff != 0xFFFFFFFFu) s.last = pos0 + lastoff / kSlotBytes;
@@ -223,8 +221,8 @@ __device__ __forceinline__ void composite_tile(StagedSubT<AN>& sb, const RenderP
                                                float bg_b, float* __restrict__ image, float* __restrict__ T_final,
                                                uint32_t* __restrict__ n_last, float4* __restrict__ ckpt) {
     const TilePixel p = tile_pixel(pk, logical, ranges);
-    PixelState s{1.0f, {0.0f, 0.0f, 0.0f, 0.0f}, 0u, !p.inside};
-    composite_range<true, PIPE, PL, AN, LAST>(sb, pk, p, record, conic, pidx, 0, p.len, s, ckpt);
+    PixelState s{p.inside ? 1.0f : 0.0f, {0.0f, 0.0f, 0.0f, 0.0f}, 0u};
+    composite_range<PIPE, PL, AN, LAST>(sb, pk, p, record, conic, pidx, 0, p.len, s, ckpt);
     write_pixel(p, s, bg_r, bg_g, bg_b, image, T_final, n_last);
 }
 
