@@ -709,21 +709,17 @@ uint32_t* launch_tile_queue(uint32_t* q, const uint32_t* ranges, uint32_t tile0,
     return order;
 }
 
-int resident_blocks(const void* kernel, int threads) {
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    return cus * per_cu;
-}
-
 // Workgroups [0, 4 wide_slots) take the quadrants of the long tiles (those of at least
 // 2^kWideMinLog2 entries: the first ones of the queue, counted from its length classes;
 // wide_slots bounds their number, and a workgroup past it leaves at once) with the wide
 // walk, the others the remaining tiles of the queue with the walk that prefetches the next
-// batch.
-template <bool AN>
+// batch. LOOP: for launches whose entries could make more than kWideSlots long tiles, a
+// quadrant's workgroups take every wide_slots-th long tile: eight 4K views of 6M particles
+// started 200 thousand workgroups that found none (1.55 -> 1.46 ms). The loop costs registers:
+// one 1080p view takes 79 us with it and 75 without.
+constexpr uint32_t kWideSlots = 4096;
+
+template <bool AN, bool LOOP>
 __device__ __forceinline__ void ordered_wide(unsigned char* smem, const RenderPack& pk, const OrderedArgs& a) {
     static_assert(sizeof(StagedQuadT<AN>) <= sizeof(StagedSubT<AN>), "one LDS buffer serves both walks");
     const uint32_t wide_slots = a.wide_slots;
@@ -736,13 +732,18 @@ __device__ __forceinline__ void ordered_wide(unsigned char* smem, const RenderPa
     }
     uint32_t n_wide = 0;
     for (int c = kWideMinLog2 + 1; c < kBuckets; ++c) n_wide += a.hist[c];
-    n_wide = min(n_wide, wide_slots);
+    n_wide = min(n_wide, LOOP ? gridDim.x - 4 * wide_slots : wide_slots);
     const WgStamp stamp(a);
     if (b < 4 * wide_slots) {
-        if ((b >> 2) >= n_wide) return;
-        composite_quadrant(*reinterpret_cast<StagedQuadT<AN>*>(smem), pk, a.order[b >> 2], (int)(b & 3u), a.record,
-                           a.conic, a.pidx, a.ranges, a.bg_r, a.bg_g, a.bg_b, a.image, a.T_final, a.n_last, a.ckpt);
-        stamp.done(a, pk, a.order[b >> 2]);
+        uint32_t j = b >> 2;
+        if (j >= n_wide) return;
+        do {
+            composite_quadrant(*reinterpret_cast<StagedQuadT<AN>*>(smem), pk, a.order[j], (int)(b & 3u), a.record,
+                               a.conic, a.pidx, a.ranges, a.bg_r, a.bg_g, a.bg_b, a.image, a.T_final, a.n_last, a.ckpt);
+            stamp.done(a, pk, a.order[j]);
+            if (LOOP) __syncthreads();   // the tile's LDS has been read
+            j += wide_slots;
+        } while (LOOP && j < n_wide);
     } else {
         const uint32_t j = b - 4 * wide_slots;
         if (j < n_wide) return;
@@ -753,16 +754,18 @@ __device__ __forceinline__ void ordered_wide(unsigned char* smem, const RenderPa
     }
 }
 
+template <bool LOOP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPrefetchWavesPerSimd)))
 composite_fwd_ordered_wide_kernel(const RenderPack pk, const OrderedArgs a) {
     __shared__ __align__(16) unsigned char smem[sizeof(StagedSubT<false>)];
-    ordered_wide<false>(smem, pk, a);
+    ordered_wide<false, LOOP>(smem, pk, a);
 }
 
+template <bool LOOP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kAnisoWideWavesPerSimd)))
 aniso_fwd_ordered_wide_kernel(const RenderPack pk, const OrderedArgs a) {
     __shared__ __align__(16) unsigned char smem[sizeof(StagedSubT<true>)];
-    ordered_wide<true>(smem, pk, a);
+    ordered_wide<true, LOOP>(smem, pk, a);
 }
 
 int launch_render_fwd_ordered(const isogs_projected* proj, const float* conic, const int32_t* n_per_view,
@@ -793,9 +796,13 @@ int launch_render_fwd_ordered(const isogs_projected* proj, const float* conic, c
                       stamps ? stamps + 2 * 5 * (size_t)tile0 : nullptr};
         if (flags & ISOGS_FWD_WIDE) {
             // a long tile holds at least 2^kWideMinLog2 of the group's entries
-            a.wide_slots = (uint32_t)std::min<uint64_t>(blocks, (uint64_t)pk.n_entries_cap / (1u << kWideMinLog2) + 1);
-            hipLaunchKernelGGL(an ? aniso_fwd_ordered_wide_kernel : composite_fwd_ordered_wide_kernel,
-                               dim3(4 * a.wide_slots + blocks), dim3(256), 0, stream, pk, a);
+            const uint64_t long_tiles =
+                std::min<uint64_t>(blocks, (uint64_t)pk.n_entries_cap / (1u << kWideMinLog2) + 1);
+            const bool loop = long_tiles > kWideSlots;
+            a.wide_slots = loop ? kWideSlots : (uint32_t)long_tiles;
+            auto k = an ? (loop ? aniso_fwd_ordered_wide_kernel<true> : aniso_fwd_ordered_wide_kernel<false>)
+                        : (loop ? composite_fwd_ordered_wide_kernel<true> : composite_fwd_ordered_wide_kernel<false>);
+            hipLaunchKernelGGL(k, dim3(4 * a.wide_slots + blocks), dim3(256), 0, stream, pk, a);
         } else if (blocks <= kPipeTileLimit) {
             auto k = an ? (n_last ? aniso_fwd_ordered_pipe_kernel<true> : aniso_fwd_ordered_pipe_kernel<false>)
                         : (n_last ? composite_fwd_ordered_pipe_kernel<true> : composite_fwd_ordered_pipe_kernel<false>);

@@ -45,8 +45,6 @@ uint32_t max_group_tiles(const isogs_camera* cams, int32_t nv);
 // The tiles of a launch in longest-list-first order (length classes 0 and 32 - clz(len)).
 uint32_t* launch_tile_queue(uint32_t* q, const uint32_t* ranges, uint32_t tile0, uint32_t n_tiles, uint32_t cap,
                             hipStream_t stream);
-// Workgroups of `threads` threads of `kernel` resident on the whole GPU at once.
-int resident_blocks(const void* kernel, int threads);
 
 // an: the anisotropic family (48-byte entry records instead of 32)
 size_t render_bwd_ws(uint64_t capacity, const isogs_camera* cams, int32_t nv, bool an);
