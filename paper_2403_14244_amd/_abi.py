@@ -175,6 +175,22 @@ def check(rc):
     return rc
 
 
+def call_with_workspace(fn, args, ws, stream):
+    """Calls fn(*args, workspace, size, stream) with the kept workspace `ws` (a uint8 tensor).
+    The size is asked for only when the call refuses the workspace as too small (it launches
+    nothing then) or there is none yet. Returns the workspace to keep."""
+    if ws.numel():
+        rc = fn(*args, ws.data_ptr(), ctypes.byref(ctypes.c_size_t(ws.numel())), stream)
+        if rc != ISOGS_ERR_WORKSPACE:
+            check(rc)
+            return ws
+    need = ctypes.c_size_t(0)
+    check(fn(*args, None, ctypes.byref(need), stream))
+    ws = ws.new_empty(max(int(need.value), 1))
+    check(fn(*args, ws.data_ptr(), ctypes.byref(ctypes.c_size_t(ws.numel())), stream))
+    return ws
+
+
 def camera_struct(cam) -> Camera:
     """Any object with R (3x3), t, eye, f, cx, cy, width, height and optionally near."""
     c = Camera()
@@ -191,7 +207,17 @@ def camera_struct(cam) -> Camera:
     return c
 
 
+class CameraBatch(list):
+    """Cameras with their ABI array, formed once for the calls of a pass."""
+
+    def __init__(self, cams):
+        super().__init__(cams)
+        self.array = camera_array(list(self))
+
+
 def camera_array(cams):
+    if isinstance(cams, CameraBatch):
+        return cams.array
     arr = (Camera * len(cams))()
     for i, cam in enumerate(cams):
         arr[i] = camera_struct(cam)

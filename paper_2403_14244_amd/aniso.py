@@ -127,11 +127,7 @@ class AnisoRasterizer(Rasterizer):
         args = (ctypes.byref(af.aniso_abi()), A.int_array(n_per_view), ctypes.byref(bins.abi()),
                 A.camera_array(cams), len(cams), bgc, _p(image), _p(T), _p(n_last), _p(ckpt),
                 A.ISOGS_FWD_WIDE if wide else 0)
-        need = ctypes.c_size_t(0)
-        A.check(A.lib().isogs_aniso_render_fwd(*args, None, ctypes.byref(need), _stream()))
-        ws = self._workspace_q(need.value)
-        have = ctypes.c_size_t(ws.numel())
-        A.check(A.lib().isogs_aniso_render_fwd(*args, _p(ws), ctypes.byref(have), _stream()))
+        self._wsq = A.call_with_workspace(A.lib().isogs_aniso_render_fwd, args, self._wsq, _stream())
         return image, T, n_last
 
     def render_bwd(self, scenes, cams, af: AnisoFootprints, bins: TileBins, bg, dL_dimage, T_final, n_last,
@@ -147,13 +143,10 @@ class AnisoRasterizer(Rasterizer):
         sc = (A.AnisoScene * len(scenes))(*[s.abi() for s in scenes])
         gs = (A.AnisoScene * len(scenes))(*[g.abi() for g in grads])
         bgc = (ctypes.c_float * 3)(*[float(b) for b in bg])
+        dL = dL_dimage.contiguous()
         args = (sc, A.camera_array(cams), len(cams), ctypes.byref(af.aniso_abi()), ctypes.byref(bins.abi()), bgc,
-                _p(image), _p(dL_dimage.contiguous()), _p(T_final), _p(n_last), _p(ckpt), gs)
-        need = ctypes.c_size_t(0)
-        A.check(A.lib().isogs_aniso_render_bwd(*args, None, ctypes.byref(need), _stream()))
-        ws = self._workspace(need.value)
-        have = ctypes.c_size_t(ws.numel())
-        A.check(A.lib().isogs_aniso_render_bwd(*args, _p(ws), ctypes.byref(have), _stream()))
+                _p(image), _p(dL), _p(T_final), _p(n_last), _p(ckpt), gs)
+        self._ws = A.call_with_workspace(A.lib().isogs_aniso_render_bwd, args, self._ws, _stream())
         out, seen = [], set()
         for g in grads:
             if g.pos.data_ptr() not in seen:
@@ -174,6 +167,7 @@ class AnisoGSRender(torch.autograd.Function):
                                    color.contiguous(), int(sh_degree))
         if len({(int(c.width), int(c.height)) for c in cams}) != 1:
             raise ValueError("AnisoGSRender: every camera must have the same size")
+        cams = A.CameraBatch(cams)
         images, st = rasterizer.render([scene] * len(cams), cams, bg, check="deferred", checkpoints=True, wide=True)
         if not any(ctx.needs_input_grad[:5]):
             rasterizer.verify(st)

@@ -49,10 +49,6 @@ class Field2DRenderer:
         self._ws = torch.empty(0, dtype=torch.uint8, device=self.device)
         self._wsb = torch.empty(0, dtype=torch.uint8, device=self.device)
 
-    @staticmethod
-    def _grow(buf, nbytes):
-        return buf if buf.numel() >= nbytes else torch.empty(int(nbytes), dtype=torch.uint8, device=buf.device)
-
     def tiles_bound(self) -> int:
         return (math.ceil(2.0 * self.support / 16.0) + 2) ** 2
 
@@ -71,13 +67,9 @@ class Field2DRenderer:
             cap = int(capacity)
         for _ in range(2):
             bins = _alloc_bins(cap, K, self.tiles, self.device)
-            ab = bins.abi()
-            need = ctypes.c_size_t(0)
-            args = (ctypes.byref(f), self.width, self.height, self.support, ctypes.byref(fp.abi()), ctypes.byref(ab))
-            A.check(A.lib().isogs_field2d_bin(*args, None, ctypes.byref(need), _stream()))
-            self._ws = self._grow(self._ws, need.value)
-            have = ctypes.c_size_t(self._ws.numel())
-            A.check(A.lib().isogs_field2d_bin(*args, _p(self._ws), ctypes.byref(have), _stream()))
+            args = (ctypes.byref(f), self.width, self.height, self.support, ctypes.byref(fp.abi()),
+                    ctypes.byref(bins.abi()))
+            self._ws = A.call_with_workspace(A.lib().isogs_field2d_bin, args, self._ws, _stream())
             if not check:
                 return fp, bins
             st = int(bins.status.item())
@@ -103,13 +95,9 @@ class Field2DRenderer:
         gamp = torch.empty((3, K), dtype=_F32, device=self.device)
         g = _field(gmu, gsig, gamp)
         dl = dL_dimage.contiguous()
-        need = ctypes.c_size_t(0)
         args = (ctypes.byref(fp.abi()), int(K), ctypes.byref(bins.abi()), self.width, self.height, self.support,
                 _p(dl), ctypes.byref(g))
-        A.check(A.lib().isogs_field2d_bwd(*args, None, ctypes.byref(need), _stream()))
-        self._wsb = self._grow(self._wsb, max(need.value, 1))
-        have = ctypes.c_size_t(self._wsb.numel())
-        A.check(A.lib().isogs_field2d_bwd(*args, _p(self._wsb), ctypes.byref(have), _stream()))
+        self._wsb = A.call_with_workspace(A.lib().isogs_field2d_bwd, args, self._wsb, _stream())
         return gmu, gsig, gamp
 
 
@@ -141,14 +129,9 @@ class Field2DAnisoRenderer(Field2DRenderer):
             cap = int(capacity)
         for _ in range(2):
             bins = _alloc_bins(cap, K, self.tiles, self.device)
-            ab = bins.abi()
-            need = ctypes.c_size_t(0)
             args = (ctypes.byref(f), self.width, self.height, self.support, ctypes.byref(fp.abi()), _p(conic_c),
-                    ctypes.byref(ab))
-            A.check(A.lib().isogs_field2d_aniso_bin(*args, None, ctypes.byref(need), _stream()))
-            self._ws = self._grow(self._ws, need.value)
-            have = ctypes.c_size_t(self._ws.numel())
-            A.check(A.lib().isogs_field2d_aniso_bin(*args, _p(self._ws), ctypes.byref(have), _stream()))
+                    ctypes.byref(bins.abi()))
+            self._ws = A.call_with_workspace(A.lib().isogs_field2d_aniso_bin, args, self._ws, _stream())
             if not check:
                 return fp, conic_c, bins
             st = int(bins.status.item())
@@ -172,13 +155,10 @@ class Field2DAnisoRenderer(Field2DRenderer):
         out = (torch.empty((2, K), dtype=_F32, device=self.device), torch.empty(K, dtype=_F32, device=self.device),
                torch.empty((2, K), dtype=_F32, device=self.device), torch.empty((3, K), dtype=_F32, device=self.device))
         f, g = _field_aniso(mu, theta, scale, amp), _field_aniso(*out)
-        need = ctypes.c_size_t(0)
+        dl = dL_dimage.contiguous()
         args = (ctypes.byref(f), ctypes.byref(fp.abi()), _p(conic_c), ctypes.byref(bins.abi()), self.width,
-                self.height, self.support, _p(dL_dimage.contiguous()), ctypes.byref(g))
-        A.check(A.lib().isogs_field2d_aniso_bwd(*args, None, ctypes.byref(need), _stream()))
-        self._wsb = self._grow(self._wsb, max(need.value, 1))
-        have = ctypes.c_size_t(self._wsb.numel())
-        A.check(A.lib().isogs_field2d_aniso_bwd(*args, _p(self._wsb), ctypes.byref(have), _stream()))
+                self.height, self.support, _p(dl), ctypes.byref(g))
+        self._wsb = A.call_with_workspace(A.lib().isogs_field2d_aniso_bwd, args, self._wsb, _stream())
         return out
 
 

@@ -17,11 +17,13 @@ _F32 = torch.float32
 
 
 def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current stream of the current device (the object that
+    torch.cuda.current_stream() makes of it costs 2 us, and every library call asks)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def sh_count(deg: int) -> int:
@@ -127,7 +129,7 @@ def tiles_of(cam) -> int:
 
 def _alloc_bins(capacity, n_total, tiles_total, device, with_keys=False) -> TileBins:
     cap = max(int(capacity), 1)
-    words = torch.zeros(2, dtype=torch.int32, device=device)   # {count, status}: one fill, one read-back
+    words = torch.empty(2, dtype=torch.int32, device=device)   # {count, status}: written by every binning
     return TileBins(keys=torch.empty(cap, dtype=torch.int64, device=device) if with_keys else None,
                     pidx=torch.empty(cap, dtype=torch.int32, device=device),
                     ranges=torch.empty((tiles_total, 2), dtype=torch.int32, device=device),
@@ -149,12 +151,8 @@ class Rasterizer:
         # training step can be captured in a HIP graph; the capacity must be sized first
         # (an eager step), and a pass that overflows it shows NaN images and loss
         self.sync_free = False
-        self._ws = torch.empty(0, dtype=torch.uint8, device=self.device)
-
-    def _workspace(self, nbytes):
-        if self._ws.numel() < nbytes:
-            self._ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
-        return self._ws
+        self._ws = torch.empty(0, dtype=torch.uint8, device=self.device)    # binning and backward
+        self._wsq = torch.empty(0, dtype=torch.uint8, device=self.device)   # forward: the tile queue
 
     # -- the four ABI calls -----------------------------------------------------------
     def project(self, scenes, cams) -> Footprints:
@@ -174,14 +172,8 @@ class Rasterizer:
         cap = self.capacity if capacity is None else capacity
         for _ in range(2):
             bins = _alloc_bins(cap, n_total, tiles_total, self.device, with_keys)
-            ab = bins.abi()
-            need = ctypes.c_size_t(0)
-            A.check(A.lib().isogs_bin_sort(ctypes.byref(fp.abi()), npv, carr, len(cams), ctypes.byref(ab), None,
-                                           ctypes.byref(need), _stream()))
-            ws = self._workspace(need.value)
-            have = ctypes.c_size_t(ws.numel())
-            A.check(A.lib().isogs_bin_sort(ctypes.byref(fp.abi()), npv, carr, len(cams), ctypes.byref(ab),
-                                           _p(ws), ctypes.byref(have), _stream()))
+            args = (ctypes.byref(fp.abi()), npv, carr, len(cams), ctypes.byref(bins.abi()))
+            self._ws = A.call_with_workspace(A.lib().isogs_bin_sort, args, self._ws, _stream())
             if not check:
                 return bins
             st = int(bins.status.item())
@@ -244,14 +236,10 @@ class Rasterizer:
         bgc = (ctypes.c_float * 3)(*[float(b) for b in bg])
         carr = A.camera_array(cams)
         npv = A.int_array(n_per_view)
-        need = ctypes.c_size_t(0)
         flags = (A.ISOGS_FWD_WIDE if wide else 0) | (A.ISOGS_FWD_TIMES if times else 0)
         args = (ctypes.byref(fp.abi()), npv, ctypes.byref(bins.abi()), carr, len(cams), bgc, _p(image), _p(T),
                 _p(n_last), _p(ckpt), flags)
-        A.check(A.lib().isogs_render_fwd_ordered(*args, None, ctypes.byref(need), _stream()))
-        ws = self._workspace_q(need.value)
-        have = ctypes.c_size_t(ws.numel())
-        A.check(A.lib().isogs_render_fwd_ordered(*args, _p(ws), ctypes.byref(have), _stream()))
+        ws = self._wsq = A.call_with_workspace(A.lib().isogs_render_fwd_ordered, args, self._wsq, _stream())
         if not times:
             return image, T, n_last
         base = ctypes.c_size_t(0)
@@ -261,11 +249,6 @@ class Rasterizer:
         off = base.value - 256
         stamps = ws[off:off + tiles * 5 * 16].view(torch.int64).view(tiles * 5, 2)
         return image, T, n_last, stamps
-
-    def _workspace_q(self, nbytes):
-        if not hasattr(self, "_wsq") or self._wsq.numel() < nbytes:
-            self._wsq = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
-        return self._wsq
 
     def render_bwd(self, scenes, cams, fp: Footprints, bins: TileBins, bg, dL_dimage, T_final, n_last, grads=None,
                    image=None, ckpt=None):
@@ -281,14 +264,10 @@ class Rasterizer:
         sc = (A.Scene * len(scenes))(*[s.abi() for s in scenes])
         gs = (A.Scene * len(scenes))(*[g.abi() for g in grads])
         bgc = (ctypes.c_float * 3)(*[float(b) for b in bg])
-        need = ctypes.c_size_t(0)
-        ab = bins.abi()
-        args = (sc, A.camera_array(cams), len(cams), ctypes.byref(fp.abi()), ctypes.byref(ab), bgc, _p(image),
-                _p(dL_dimage.contiguous()), _p(T_final), _p(n_last), _p(ckpt), gs)
-        A.check(A.lib().isogs_render_bwd(*args, None, ctypes.byref(need), _stream()))
-        ws = self._workspace(need.value)
-        have = ctypes.c_size_t(ws.numel())
-        A.check(A.lib().isogs_render_bwd(*args, _p(ws), ctypes.byref(have), _stream()))
+        dL = dL_dimage.contiguous()
+        args = (sc, A.camera_array(cams), len(cams), ctypes.byref(fp.abi()), ctypes.byref(bins.abi()), bgc, _p(image),
+                _p(dL), _p(T_final), _p(n_last), _p(ckpt), gs)
+        self._ws = A.call_with_workspace(A.lib().isogs_render_bwd, args, self._ws, _stream())
         out, seen = [], set()
         for g in grads:
             if g.pos.data_ptr() not in seen:
@@ -311,6 +290,7 @@ class Rasterizer:
         (same images bitwise; with `wide`, the longest tiles of small launches are
         composited four lanes per pixel, equal up to rounding). `checkpoints` keeps the
         compositing checkpoints for the backward in the state."""
+        cams = cams if isinstance(cams, A.CameraBatch) else A.CameraBatch(cams)
         fp = self.project(scenes, cams)
         npv = [s.n for s in scenes]
         if self.ordered_fwd:
@@ -382,6 +362,7 @@ class IsoGSRender(torch.autograd.Function):
         scenes = [scene] * len(cams)
         if len({(int(c.width), int(c.height)) for c in cams}) != 1:
             raise ValueError("IsoGSRender: every camera must have the same size")
+        cams = A.CameraBatch(cams)
         check = False if rasterizer.sync_free else "deferred"
         images, st = rasterizer.render(scenes, cams, bg, check=check, checkpoints=True, wide=True)
         if not any(ctx.needs_input_grad[:4]):
