@@ -454,7 +454,7 @@ struct OrderedArgs {
     float* T_final;
     uint32_t* n_last;
     float4* ckpt;
-    const uint32_t* order;
+    const uint32_t* order;    // NULL: tiles in index order
     const uint32_t* hist;
     uint32_t wide_slots;
     uint64_t* times;          // ISOGS_FWD_TIMES: {start, end} per workgroup of the launch, else NULL
@@ -482,7 +482,7 @@ struct WgStamp {
 // LAST: the caller asked for n_last (without it the walk does not track the last entry).
 template <bool PIPE, bool AN, bool LAST>
 __device__ __forceinline__ void ordered_tile(StagedSubT<AN>& sb, const RenderPack& pk, const OrderedArgs& a) {
-    const uint32_t item = a.order[queue_slot(blockIdx.x, gridDim.x)];
+    const uint32_t item = a.order ? a.order[queue_slot(blockIdx.x, gridDim.x)] : blockIdx.x;
     if (*a.status != kStatusOk) return write_overflow_tile(pk, item, a.image, a.T_final, a.n_last);
     const WgStamp stamp(a);
     composite_tile<PIPE, PIPE, AN, LAST>(sb, pk, item, a.record, a.conic, a.pidx, a.ranges, a.bg_r, a.bg_g,
@@ -525,6 +525,11 @@ __global__ void __launch_bounds__(256) aniso_fwd_ordered_pipe_kernel(const Rende
 // Launches of at most this many tiles use the pipelined walk (measured crossover on the
 // 1M-particle 1080p views: between two and four views, 16320 and 32640 tiles).
 constexpr uint32_t kPipeTileLimit = 24576;
+
+// Launches of at most this many tiles need no queue (the wide one reads its classes): all their
+// workgroups reside at once, three or more of the pipelined walk on each of 256 CUs. A
+// 256 x 256 view saves the 4 us of sorting its 256 tiles.
+constexpr uint32_t kAtOnceTiles = 3 * 256;
 
 __global__ void __launch_bounds__(128) fill_u32_kernel_c(uint32_t* __restrict__ p, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
@@ -789,12 +794,16 @@ int launch_render_fwd_ordered(const isogs_projected* proj, const float* conic, c
         fill_render_pack(pk, cams, n_per_view, v0, nv, p_off, tile_base, pix_off, blocks);
         set_render_limits(pk, n_per_view, nv, bins->capacity);
         if (!blocks) continue;
-        const uint32_t* order = launch_tile_queue(q, bins->ranges, tile0, blocks, pk.n_entries_cap, stream);
+        const bool wide = flags & ISOGS_FWD_WIDE;
+        const uint32_t* order =
+            wide || blocks > kAtOnceTiles
+                ? launch_tile_queue(q, bins->ranges, tile0, blocks, pk.n_entries_cap, stream)
+                : nullptr;
         OrderedArgs a{reinterpret_cast<const float4*>(proj->record), reinterpret_cast<const float2*>(conic),
                       bins->pidx, bins->ranges, bins->status, bg[0], bg[1], bg[2], image, T_final, n_last,
                       reinterpret_cast<float4*>(ckpt), order, q, 0u,
                       stamps ? stamps + 2 * 5 * (size_t)tile0 : nullptr};
-        if (flags & ISOGS_FWD_WIDE) {
+        if (wide) {
             // a long tile holds at least 2^kWideMinLog2 of the group's entries
             const uint64_t long_tiles =
                 std::min<uint64_t>(blocks, (uint64_t)pk.n_entries_cap / (1u << kWideMinLog2) + 1);
