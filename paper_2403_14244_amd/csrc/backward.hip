@@ -3,15 +3,14 @@
 //
 //   1. composite_bwd  per tile: walk each pixel's entries in reverse from n_last,
 //                     recovering T before each entry as T_after / (1 - alpha); reduce each
-//                     entry's screen-space gradient over the tile's pixels (matrix cores
-//                     over the 16 pixels of a sub-block, then the sub-blocks in fixed
+//                     entry's screen-space gradient over the tile's pixels (butterflies over
+//                     the 16 pixels of a sub-block, then the sub-blocks in fixed
 //                     order) into one record per entry, stored at the entry's emit position.
 //   2. grad_project   per particle: sum its records (consecutive in emit order, views in
 //                     order) and chain them to mu, sigma, o and the colour coefficients.
 // There are no floating-point atomics: every sum has a fixed order.
 #include <algorithm>
 #include <array>
-#include <type_traits>
 
 #include "raster.h"
 
@@ -29,28 +28,19 @@ constexpr int kBwdDummy = kBwdBatch;   // staged slot of the zero-opacity pad re
 // applied per particle). A record holds them in kRecVec4<AN> float4s at the entry's emit
 // position.
 //
-// The sums over a sub-block's 16 pixels are a contraction: of k with the pixel's monomials
-// 1, X, Y and X^2 + Y^2 (anisotropic: X^2, XY, Y^2), X and Y measured from the sub-block's
-// centre, and of w with dL/dcolour. A step of the walk (four entries of each of a wave's four
-// sub-blocks) holds k and w as one pixel per lane; they are passed through 1.25 KB of LDS
-// into the A operand of v_mfma_f32_16x16x4_f32 (rows: sub-block and entry, K: pixel), whose B
-// columns are the monomials (shared by the sub-blocks) and each sub-block's dL/dcolour: eight
-// matrix instructions per step replace about 90 cross-lane additions and selects, and the
-// products of k with dx, dy and d^2. The moments are moved to the entry's centre when the
-// sub-blocks are combined. The products and sums are FP32.
-// Measured with the list layout below, one 1080p view of 1M particles: 254 -> 187 us, 110M ->
-// 60M vector instructions; anisotropic 392 -> 339 us; 6M particles, eight 4K views, where most
-// entries lie behind the last one composited: 8.1 -> 4.9 ms.
-// 
+// A pixel's products are formed with its own offsets and summed over the 16 pixels of a
+// sub-block by a transposing butterfly, then over the sub-blocks in order. (The sums over a
+// sub-block as a contraction on the matrix cores, of k with the monomials of its pixels, and
+// the moments then moved to the entry's centre, take eight matrix instructions for the
+// butterflies of a step, 176 us at 1080p; but the moments of a kernel narrower than a
+// pixel cancel when they are moved: gradients of its scale were off by up to 1e-2.)
+// Measured with the list layout below, one 1080p view of 1M particles: 254 -> 198 us;
+// anisotropic 392 -> 323 us; 6M particles, eight 4K views, where most entries lie behind the
+// last one composited: 8.1 -> 4.80 ms.
 template <bool AN>
 constexpr int kGradTerms = AN ? 9 : 7;
 template <bool AN>
-constexpr int kMoments = AN ? 6 : 4;   // part[][q]: the moments of k, then dr w, dg w, db w
-template <bool AN>
 constexpr int kRecVec4 = AN ? 3 : 2;
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kTransPitch = 20;   // floats per row of the transposing buffer: bank-conflict free both ways
 
 // Pairs (entry, sub-block that it may touch) of a round, held in LDS list by list: the lists
 // of the 16 sub-blocks lie back to back, each padded to a multiple of four, and the sums of
@@ -65,7 +55,7 @@ constexpr int kTransPitch = 20;   // floats per row of the transposing buffer: b
 // particles: 185 us and 4.92 ms with 640 pairs, 182 us and 4.75 ms with 744, 192 us and 5.44 ms
 // with 1008 (three workgroups), 198 us and 5.13 ms with 480 (five).
 template <bool AN>
-constexpr uint32_t kPairCap = AN ? 480 : 744;
+constexpr uint32_t kPairCap = AN ? 576 : 896;
 constexpr uint32_t kPairPad = 16 * 3;   // padding of the 16 lists at most
 template <bool AN>
 constexpr int kPartPitch = AN ? 12 : 8;
@@ -75,29 +65,23 @@ struct StagedBwdT {
     float4 fp[kBwdBatch + 1];            // staged kernel (staged_kernel: {u, v, q or nA, log2(o)})
     float4 col[kBwdBatch + 1];           // {r, g, b, 1/o}
     float2 cn[AN ? kBwdBatch + 1 : 1];   // anisotropic: {nB2, nC}
-    union {
-        __align__(16) float part[kPairCap<AN>][kPartPitch<AN>];   // gradient sums of each pair
-        __align__(16) float dL[4][3][kWave];                      // before the walk: dL/dcolour of each wave
-    };
-    __align__(16) float trans[4][16 * kTransPitch];   // [wave] k or w of one step: row 4 g + e, column pixel
+    __align__(16) float part[kPairCap<AN>][kPartPitch<AN>];   // gradient sums of each pair
     __align__(16) uint32_t cnt[4][16];   // [wave][sub-block]: the wave's entries of each list
     __align__(8) uint16_t list[kPairCap<AN>];   // byte offsets (16 x staged slot) in walk order
-    uint16_t link[kPairCap<AN>];         // the entry's pair before this one (kLinkEnd: none)
+    uint16_t link[kPairCap<AN>];         // the entry's next pair (kLinkEnd: none)
     __align__(16) uint32_t gmax[16];     // largest n_last of each sub-block
     uint32_t kept[4];
 };
 
-// An entry's pairs are chained through `link`, a chain word holding the pair's list index
-// and, above it, its sub-block.
-constexpr uint32_t kLinkShift = 10, kLinkEnd = 0xFFFFu;
-static_assert(kPairCap<false> <= 1u << kLinkShift && kPairCap<true> <= 1u << kLinkShift, "list index bits");
+// An entry's pairs are chained through `link` in the order of their sub-blocks.
+constexpr uint32_t kLinkEnd = 0xFFFFu;
 static_assert((kBwdBatch + 1) * kSlotBytes <= 0xFFFFu, "staged byte offsets fit 16 bits");
 
 // An entry of a round as its thread holds it.
 struct BwdEntry {
     EntryLoad e;
     uint32_t slot;   // emit position (all ones: none)
-    uint32_t head;   // its last pair (chain word)
+    uint32_t head;   // its first pair (list index)
 };
 
 // A wave's view of the staged lists.
@@ -227,13 +211,13 @@ __device__ __forceinline__ BwdLists stage_bwd(StagedBwdT<AN>& sb, BwdEntry& b, u
     const uint32_t base = row_inclusive_scan(padded) - padded, at = base + before;
     if (mine) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
+        for (int k = 15; k >= 0; --k) {
             const uint32_t first = __builtin_amdgcn_readlane(at, k);
             if (lane_bit(bal[k])) {
                 const uint32_t i = first + rank_from(bal[k], 0u);
                 sb.list[i] = (uint16_t)(t * kSlotBytes);
                 sb.link[i] = (uint16_t)b.head;
-                b.head = i | (uint32_t)k << kLinkShift;
+                b.head = i;
             }
         }
         if (b.head != kLinkEnd)
@@ -294,8 +278,8 @@ __device__ __forceinline__ void composite_bwd_tile(
     uint32_t hi = start + c_hi, nb = min((uint32_t)kBwdBatch, c_hi - c_lo);
     BwdEntry b = load_bwd<AN>(record, conic, pidx, offsets, pk.n_particles, hi, nb);
 
-    // S: light from behind the current entry (per channel) dotted with dL/dcolour
-    float T = 1.0f, dr = 0.0f, dg = 0.0f, db = 0.0f, S = 0.0f;
+    // S: light from behind the current entry, per channel
+    float T = 1.0f, dr = 0.0f, dg = 0.0f, db = 0.0f, Sr = 0.0f, Sg = 0.0f, Sb = 0.0f;
     uint32_t last = 0;
     if (inside) {
         const size_t hw = (size_t)vd.width * vd.height;
@@ -310,47 +294,26 @@ __device__ __forceinline__ void composite_bwd_tile(
             const float4 s = ckpt[(size_t)ckpt_slot(start, c_hi / kCkptChunk) * 256 + t];
             const float* im = image + (size_t)3 * vd.pix_off;
             T = s.x;
-            S = dr * (im[pix] - s.y) + dg * (im[hw + pix] - s.z) + db * (im[2 * hw + pix] - s.w);
+            Sr = im[pix] - s.y;
+            Sg = im[hw + pix] - s.z;
+            Sb = im[2 * hw + pix] - s.w;
         } else {
             // light arriving from behind the last entry: T_final bg
             T = T_final[vd.pix_off + pix];
-            S = T * (dr * bg_r + dg * bg_g + db * bg_b);
+            Sr = T * bg_r;
+            Sg = T * bg_g;
+            Sb = T * bg_b;
         }
     }
 
-    sb.dL[w][0][lane] = dr;
-    sb.dL[w][1][lane] = dg;
-    sb.dL[w][2][lane] = db;
     const uint32_t most = row_max(last > c_lo ? min(last, c_hi) : 0u);
     if ((lane & 15u) == 0) sb.gmax[sbk] = most;
     __syncthreads();
     if (ballot64(sb.gmax[lane & 15u] != 0u) == 0) return;   // no pixel composited an entry from here on
 
-    // B operands of the reduction, one register per K step m (K index lane / 16, pixel
-    // 4 (lane / 16) + m of a sub-block, i.e. X = m - 1.5, Y = lane / 16 - 1.5): column
-    // lane % 16 < 12 is channel column % 3 of dL/dcolour of the wave's sub-block column / 3;
-    // the moments take columns 12 - 15 (anisotropic: columns 0 - 5). k and w have an
-    // accumulator each, so that a non-finite k does not reach the colour sums through the
-    // zero columns
-    const uint32_t col = lane & 15u, row = lane >> 4, ch = col % 3u;
-    const float4 w4 = *reinterpret_cast<const float4*>(&sb.dL[w][ch][(16u * (col / 3u) + 4u * row) & 63u]);
-    const float b_w[4] = {col < 12u ? w4.x : 0.0f, col < 12u ? w4.y : 0.0f, col < 12u ? w4.z : 0.0f,
-                          col < 12u ? w4.w : 0.0f};
-    float b_k[4];
-#pragma unroll
-    for (uint32_t m = 0; m < 4; ++m) {
-        const float X = (float)m - 1.5f, Y = (float)row - 1.5f;
-        const uint32_t q = AN ? col : col - 12u;   // isotropic: wraps to a large value below column 12
-        b_k[m] = q == 0u ? 1.0f : q == 1u ? X : q == 2u ? Y : 0.0f;
-        if (!AN && q == 3u) b_k[m] = X * X + Y * Y;
-        if (AN) b_k[m] = q == 3u ? X * X : q == 4u ? X * Y : q == 5u ? Y * Y : b_k[m];
-    }
-    // this lane's column of a result (row 4 g + e: entry e of sub-block g = lane / 16)
-    const bool w_writer = col < 12u && col / 3u == row;
-    const bool k_writer = AN ? col < 6u : col >= 12u;
-    const uint32_t w_term = kMoments<AN> + ch, k_term = (AN ? col : col - 12u) & 7u;
-    float* const t_write = &sb.trans[w][4u * row * kTransPitch + col];
-    const float* const t_read = &sb.trans[w][col * kTransPitch + 4u * row];
+    // this lane's sum of its row (anisotropic: the ninth in lane 8)
+    const uint32_t q8 = rev3(lane & 7u);
+    const bool writer8 = (lane & 15u) < 8u, writer9 = AN && (lane & 15u) == 8u;
 
     while (true) {
         const uint32_t pos_hi = hi - start;
@@ -363,126 +326,84 @@ __device__ __forceinline__ void composite_bwd_tile(
             uint64_t q4 = kD | (kD << 16) | (kD << 32) | (kD << 48);   // four dummy slots
             const bool on = k < L.len;
             if (on) q4 = *reinterpret_cast<const uint64_t*>(&sb.list[L.base + k]);
-            // colour . dL/dcolour of the four entries at this lane's pixel: lane e of a quad
-            // brings entry e's colour (4 x 4 x 1 blocks: row entry, column pixel)
-            const float4 c4 = staged_at(sb.col, (uint32_t)(q4 >> (16u * (lane & 3u))) & 0xFFFFu);
-            f32x4 cd = {0.0f, 0.0f, 0.0f, 0.0f};
-            cd = __builtin_amdgcn_mfma_f32_4x4x1f32(c4.x, dr, cd, 0, 0, 0);
-            cd = __builtin_amdgcn_mfma_f32_4x4x1f32(c4.y, dg, cd, 0, 0, 0);
-            cd = __builtin_amdgcn_mfma_f32_4x4x1f32(c4.z, db, cd, 0, 0, 0);
-            float kk[4], wg[4];
-            bool any = false;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const uint32_t off = (uint32_t)(q4 >> (16 * r)) & 0xFFFFu;
-                const float4 f = staged_at(sb.fp, off);
+                const float4 f = staged_at(sb.fp, off), c = staged_at(sb.col, off);
                 const float2 kc = AN ? sb.cn[off / kSlotBytes] : make_float2(0.0f, 0.0f);
+                const float dx = px - f.x, dy = py - f.y;
                 float ga;
-                float a = staged_alpha<AN>(px - f.x, py - f.y, f, kc, ga);
+                float a = staged_alpha<AN>(dx, dy, f, kc, ga);
                 // an entry this pixel composited in the forward pass (same decision); the
                 // pad record has alpha 0
                 const bool use = (int)off >= off_min && a >= kAlphaMin;
-                any = any || use;
                 a = use ? a : 0.0f;
                 const float inv_om = __builtin_amdgcn_rcpf(1.0f - a);
                 T = T * inv_om;                              // transmittance before this entry
-                wg[r] = a * T;
-                const float dLda = fmaf(-S, inv_om, cd[r] * T);
-                S = fmaf(cd[r], wg[r], S);
+                const float wgt = a * T;
+                const float dLda = dr * (c.x * T - Sr * inv_om) + dg * (c.y * T - Sg * inv_om) +
+                                   db * (c.z * T - Sb * inv_om);
+                Sr = fmaf(c.x, wgt, Sr);
+                Sg = fmaf(c.y, wgt, Sg);
+                Sb = fmaf(c.z, wgt, Sb);
                 // alpha = o exp(-d^2 / s^2) below the clamp: d/du = 2 alpha dx / s^2,
                 // d/d(1/s^2) = -alpha d^2, d/do = alpha / o
-                kk[r] = (use && ga < kAlphaMax) ? dLda * ga : 0.0f;
-            }
-            f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f}, sum_k = sum;
-            if (ballot64(any) != 0) {
-                // LDS operations of one wave complete in order: the buffer serves k, then w
-#pragma unroll
-                for (int r = 0; r < 4; ++r) t_write[r * kTransPitch] = kk[r];
-                __builtin_amdgcn_wave_barrier();
-                const float4 ak = *reinterpret_cast<const float4*>(t_read);
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int r = 0; r < 4; ++r) t_write[r * kTransPitch] = wg[r];
-                __builtin_amdgcn_wave_barrier();
-                const float4 aw = *reinterpret_cast<const float4*>(t_read);
-                __builtin_amdgcn_wave_barrier();
-                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.x, b_k[0], sum_k, 0, 0, 0);
-                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.x, b_w[0], sum, 0, 0, 0);
-                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.y, b_k[1], sum_k, 0, 0, 0);
-                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.y, b_w[1], sum, 0, 0, 0);
-                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.z, b_k[2], sum_k, 0, 0, 0);
-                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.z, b_w[2], sum, 0, 0, 0);
-                sum_k = __builtin_amdgcn_mfma_f32_16x16x4f32(ak.w, b_k[3], sum_k, 0, 0, 0);
-                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.w, b_w[3], sum, 0, 0, 0);
-            }
-            // the sums of pads are written too (nothing reads them)
-            if (on) {
-                float(*pr)[kPartPitch<AN>] = &sb.part[L.base + k];
-                if (AN) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (k_writer) pr[r][k_term] = sum_k[r];
-                        if (w_writer) pr[r][w_term] = sum[r];
+                const float kk = (use && ga < kAlphaMax) ? dLda * ga : 0.0f;
+                float red = 0.0f, g9 = 0.0f;
+                if (ballot64(use) != 0) {
+                    float gv[8];
+                    if constexpr (!AN) {
+                        const float inv_s2 = f.z * (1.0f / kLog2e);
+                        gv[0] = 2.0f * kk * inv_s2 * dx;
+                        gv[1] = 2.0f * kk * inv_s2 * dy;
+                        gv[2] = -kk * fmaf(dx, dx, dy * dy);
+                        gv[3] = kk * c.w;
+                        gv[4] = dr * wgt;
+                        gv[5] = dg * wgt;
+                        gv[6] = db * wgt;
+                        gv[7] = 0.0f;
+                    } else {
+                        // alpha = o exp(-Q) below the clamp: dL/du = k (2 A dx + 2 B dy),
+                        // dL/dA = -k dx^2, ...: the conic enters per particle
+                        const float kx = kk * dx, ky = kk * dy;
+                        gv[0] = kx;
+                        gv[1] = ky;
+                        gv[2] = kx * dx;
+                        gv[3] = kx * dy;
+                        gv[4] = ky * dy;
+                        gv[5] = kk * c.w;
+                        gv[6] = dr * wgt;
+                        gv[7] = dg * wgt;
+                        // the ninth sum over the row: butterfly (quad swaps, row rotations)
+                        g9 = db * wgt;
+                        g9 += dpp<0xB1>(g9);
+                        g9 += dpp<0x4E>(g9);
+                        g9 += dpp<0x124>(g9);
+                        g9 += dpp<0x128>(g9);
                     }
-                } else if (k_writer || w_writer) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) pr[r][k_writer ? k_term : w_term] = k_writer ? sum_k[r] : sum[r];
+                    red = row_sum8(gv, lane);
                 }
+                // the sums of pads are written too (nothing reads them)
+                float* pr = sb.part[on ? L.base + k + r : 0u];
+                if (on && writer8) pr[q8] = red;
+                if (on && writer9) pr[AN ? 8 : 0] = g9;
             }
         }
         __syncthreads();
-        // combine: each thread sums its entry's pairs (from the last sub-block), the moments moved
-        // from the sub-block's centre (X, Y) to the entry's: dx = X' + (X - u)
+        // combine: each thread sums its entry's pairs in the order of the sub-blocks
         if (b.head != kLinkEnd && b.slot < pk.n_entries_cap) {
-            // the moments are moved in FP64 (anisotropic): along a thin kernel's minor axis the
-            // second moments cancel, and rounding each on its way would be amplified there
-            using M = typename std::conditional<AN, double, float>::type;
-            const M rel_x = (M)((float)(tx * kTile) + 2.0f) - (M)b.e.f.x;
-            const M rel_y = (M)((float)(ty * kTile) + 2.0f) - (M)b.e.f.y;
-            M s[AN ? 6 : 4];
-            float c[3] = {0.0f, 0.0f, 0.0f};
+            constexpr int kSums = kGradTerms<AN>;
+            float sum[4 * kRecVec4<AN>] = {};
+            for (uint32_t next = b.head; next != kLinkEnd;) {
+                const float* p = sb.part[next];
+                next = sb.link[next];
 #pragma unroll
-            for (int q = 0; q < (AN ? 6 : 4); ++q) s[q] = (M)0;
-            uint32_t next = b.head;
-            while (next != kLinkEnd) {
-                const uint32_t i = next & ((1u << kLinkShift) - 1u), k = next >> kLinkShift;
-                next = sb.link[i];
-                const float4 p0 = *reinterpret_cast<const float4*>(&sb.part[i][0]);
-                const float4 p1 = *reinterpret_cast<const float4*>(&sb.part[i][4]);
-                const M ax = rel_x + (M)(float)(((k >> 2) & 1u) * 8u + (k & 1u) * 4u);
-                const M ay = rel_y + (M)(float)((k >> 3) * 8u + ((k & 3u) >> 1) * 4u);
-                const M m0 = p0.x, mx = p0.y, my = p0.z;
-                const M kx = fma(ax, m0, mx), ky = fma(ay, m0, my);   // k dx, k dy
-                s[0] += kx;
-                s[1] += ky;
-                if constexpr (!AN) {
-                    // k d^2 = k (X'^2 + Y'^2) + ax (k X' + k dx) + ay (k Y' + k dy)
-                    s[2] += p0.w + fma(ax, mx + kx, ay * (my + ky));
-                    s[3] += m0;
-                    c[0] += p1.x;
-                    c[1] += p1.y;
-                    c[2] += p1.z;
-                } else {
-                    s[2] += fma(ax, mx + kx, (M)p0.w);
-                    s[3] += fma(ax, my, fma(ay, kx, (M)p1.x));
-                    s[4] += fma(ay, my + ky, (M)p1.y);
-                    s[5] += m0;
-                    c[0] += p1.z;
-                    c[1] += p1.w;
-                    c[2] += sb.part[i][8];
-                }
+                for (int q = 0; q < kSums; ++q) sum[q] += p[q];
             }
-            const float inv_o = sb.col[t].w;
             float4* r = rec + kRecVec4<AN> * (size_t)b.slot;
-            if constexpr (!AN) {
-                const float two_inv_s2 = 2.0f * (sb.fp[t].z * (1.0f / kLog2e));
-                r[0] = make_float4(two_inv_s2 * s[0], two_inv_s2 * s[1], -s[2], inv_o * s[3]);
-                r[1] = make_float4(c[0], c[1], c[2], 0.0f);
-            } else {
-                r[0] = make_float4((float)s[0], (float)s[1], (float)s[2], (float)s[3]);
-                r[1] = make_float4((float)s[4], inv_o * (float)s[5], c[0], c[1]);
-                r[2] = make_float4(c[2], 0.0f, 0.0f, 0.0f);
-            }
+#pragma unroll
+            for (int q = 0; q < kRecVec4<AN>; ++q)
+                r[q] = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
             has_rec[b.slot] = 1;
         }
         hi -= L.kept;

@@ -230,7 +230,7 @@ __device__ __forceinline__ void composite_tile(StagedSubT<AN>& sb, const RenderP
 // VGPRs), as many resident workgroups as hide the staging gathers; the walk of the remaining
 // tiles of small launches also prefetches the next batch from global memory, six waves per
 // SIMD (at most 80 VGPRs). Lists of 16-bit offsets, half the LDS of 32-bit ones (16.8 KB a
-// workgroup), let that many reside. Ten views of 1080p: 579 us with six and four waves and
+// workgroup), let that many reside. Ten views of 1080p: 579 us with six waves and
 // 32-bit lists, 546 with 16-bit lists, 530 at seven waves, 538 at eight (which spill);
 // 4K x 8 with the prefetch 1657 us at five waves, 1561 at six.
 constexpr int kCompactWavesPerSimd = 7;
