@@ -34,9 +34,9 @@ constexpr int kBwdDummy = kBwdBatch;   // staged slot of the zero-opacity pad re
 // the moments then moved to the entry's centre, take eight matrix instructions for the
 // butterflies of a step, 176 us at 1080p; but the moments of a kernel narrower than a
 // pixel cancel when they are moved: gradients of its scale were off by up to 1e-2.)
-// Measured with the list layout below, one 1080p view of 1M particles: 254 -> 198 us;
-// anisotropic 392 -> 323 us; 6M particles, eight 4K views, where most entries lie behind the
-// last one composited: 8.1 -> 4.80 ms.
+// Measured with the list layout below, one 1080p view of 1M particles: 254 -> 190 us;
+// anisotropic 392 -> 316 us; 6M particles, eight 4K views, where most entries lie behind the
+// last one composited: 8.1 -> 4.41 ms.
 template <bool AN>
 constexpr int kGradTerms = AN ? 9 : 7;
 template <bool AN>
@@ -50,12 +50,12 @@ constexpr int kRecVec4 = AN ? 3 : 2;
 // longer lists leave less of a wave idle: with 48 entries a wave's four lists had 2.2
 // four-entry steps between two barriers. A round whose pairs exceed the capacity keeps only
 // its first entries; the rest go to the next round.
-// As many pairs as let four workgroups reside on a CU: a larger capacity with three, or a smaller
-// one with five (which cuts more rounds), is slower. One 1080p view, and eight 4K views of 6M
-// particles: 185 us and 4.92 ms with 640 pairs, 182 us and 4.75 ms with 744, 192 us and 5.44 ms
-// with 1008 (three workgroups), 198 us and 5.13 ms with 480 (five).
+// One 1080p view, four 720p views and eight 4K views of 6M particles take 190, 295 us and 4.41 ms
+// with 640 pairs (31.6 KB of LDS), 201, 326 us and 4.87 ms with 672, 190 us and 4.66 ms with 896,
+// 196, 320 us and 4.59 ms with 512, 211 us and 5.35 ms with 1248; anisotropic 1080p 333 us with
+// 480, 320 with 528, 316 with 576 (four workgroups on a CU).
 template <bool AN>
-constexpr uint32_t kPairCap = AN ? 576 : 896;
+constexpr uint32_t kPairCap = AN ? 576 : 640;
 constexpr uint32_t kPairPad = 16 * 3;   // padding of the 16 lists at most
 template <bool AN>
 constexpr int kPartPitch = AN ? 12 : 8;
@@ -528,11 +528,10 @@ struct BwdArgs {
 // LOOP: a workgroup takes every gridDim.x-th item. Otherwise it takes one, and leaves at once
 // past the last: the number of items is known on the device only, at most tiles + capacity /
 // kCkptChunk, and where much of the lists lies behind opaque particles most workgroups find none,
-// after waiting for 40 KB of LDS and two loads (two thirds of 760 thousand in eight 4K views of
-// 6M particles: 4.63 ms, and 4.45 ms with 32768 workgroups that loop, 4.47 with 16384 or 131072,
-// 4.90 with the 1024 that reside). The loop costs registers and a barrier per item: one 1080p
-// view (15 thousand items at most) takes 180 us with it and 175 without, so it is for launches
-// of more than kBwdLoopItems.
+// after waiting for LDS and two loads (two thirds of 760 thousand in eight 4K views of
+// 6M particles: 3 to 4% longer than 16384 to 131072 workgroups that loop; the 1024 that reside
+// are 6% slower). The loop costs registers and a barrier per item, 3% of one 1080p view (15
+// thousand items at most), so it is for launches of more than kBwdLoopItems.
 constexpr uint32_t kBwdLoopGrid = 32768, kBwdLoopItems = 2 * kBwdLoopGrid;
 
 template <bool AN, bool LOOP>
