@@ -1104,10 +1104,15 @@ static uint32_t view_tiles(const isogs_camera& c) {
 // The chunking of a call: particles per chunk. Two workgroups of 1024 threads fit a CU (one with
 // the larger band), so the chunks of all views together are at most what runs at once: 512, or
 // 256 where fewer particles are worth less than the matrix rows (4 bytes per tile of the view)
-// that more chunks cost.
-static uint32_t chunk_particles(uint64_t n_total, int32_t nv, bool large_band) {
+// that more chunks cost. Every band of a view takes each chunk, so a view of several bands has
+// that many times fewer chunks (twice those 256 workgroups above four bands, whose shares of the
+// particles differ more): the matrix then has at most 256 kBandLarge counts (512 above four bands),
+// 38 MB (75 MB), and a row per view, however many tiles.
+static uint32_t chunk_particles(uint64_t n_total, int32_t nv, bool large_band, uint32_t bands) {
     const uint32_t least = n_total <= kGroupMaxParticles ? 128u : 1024u;
-    const uint32_t target = large_band || n_total < 4000000 ? kMaxChunks / 2 : kMaxChunks;
+    const uint32_t target = bands > 4                         ? std::max(kMaxChunks / bands, 1u)
+                            : large_band || n_total < 4000000 ? kMaxChunks / 2 / bands
+                                                              : kMaxChunks;
     const uint32_t rows = std::max(target - std::min<uint32_t>((uint32_t)nv, target / 2), 1u);
     return (uint32_t)std::max<uint64_t>(least, (n_total + rows - 1) / rows);
 }
@@ -1126,16 +1131,18 @@ BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, i
     p.n_total = (uint32_t)n;
     p.tiles_total = (uint32_t)tiles;
     p.large_band = most_tiles > kBandSmall;
+    const uint32_t bands = p.large_band ? (most_tiles + kBandLarge - 1) / kBandLarge : 1u;
     // The size that callers are told: 20 bytes per entry of capacity and tile, a tile digit
     // histogram per 4096 entries and the tables of the long segments. The layout below takes
-    // less for all but scenes of many more particles than entries; a caller whose workspace
-    // cannot grow (`limit`) then gets a layout without the packed boxes (step 4 reads the
-    // records again), or also with one chunk per view, which never takes more.
+    // more for scenes of many more particles than entries (the boxes) and for few entries in
+    // many tiles (the matrix); a caller whose workspace cannot grow (`limit`) then gets a layout
+    // without the packed boxes (step 4 reads the records again), or also with one chunk per view,
+    // which never takes more.
     const uint64_t sort_tiles = (capacity + 4095) / 4096, long_max = std::min<uint64_t>(tiles, capacity / 16385 + 1);
     const size_t told = 5 * align256(capacity * 4) + (size_t)sort_tiles * 2048 + (size_t)(sort_tiles + long_max) * 1028 +
                         (size_t)long_max * 40 + (size_t)tiles * 20 + (n + 2047) / 2048 * 4 + 40960;
     for (int small = 0;; ++small) {
-        p.per = small > 1 ? 0x7FFFFFFFu : chunk_particles(n, nv, p.large_band);
+        p.per = small > 1 ? 0x7FFFFFFFu : chunk_particles(n, nv, p.large_band, bands);
         uint64_t chunks = 0, blocks = 0, m = 0;
         for (int v = 0; v < nv; ++v) {
             const uint64_t c = ((uint64_t)n_per_view[v] + p.per - 1) / p.per, vt = view_tiles(cams[v]);
