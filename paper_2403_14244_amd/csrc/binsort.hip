@@ -1136,13 +1136,14 @@ BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, i
     // histogram per 4096 entries and the tables of the long segments. The layout below takes
     // more for scenes of many more particles than entries (the boxes) and for few entries in
     // many tiles (the matrix); a caller whose workspace cannot grow (`limit`) then gets a layout
-    // without the packed boxes (step 4 reads the records again), or also with one chunk per view,
-    // which never takes more.
+    // without the packed boxes (step 4 reads the records again), and where that is not enough
+    // with half the chunks, as often as it takes: at one per view it never takes more.
     const uint64_t sort_tiles = (capacity + 4095) / 4096, long_max = std::min<uint64_t>(tiles, capacity / 16385 + 1);
     const size_t told = 5 * align256(capacity * 4) + (size_t)sort_tiles * 2048 + (size_t)(sort_tiles + long_max) * 1028 +
                         (size_t)long_max * 40 + (size_t)tiles * 20 + (n + 2047) / 2048 * 4 + 40960;
+    p.per = chunk_particles(n, nv, p.large_band, bands);
     for (int small = 0;; ++small) {
-        p.per = small > 1 ? 0x7FFFFFFFu : chunk_particles(n, nv, p.large_band, bands);
+        if (small > 1) p.per = (uint32_t)std::min<uint64_t>(2ull * p.per, 0x7FFFFFFFu);
         uint64_t chunks = 0, blocks = 0, m = 0;
         for (int v = 0; v < nv; ++v) {
             const uint64_t c = ((uint64_t)n_per_view[v] + p.per - 1) / p.per, vt = view_tiles(cams[v]);
@@ -1177,7 +1178,7 @@ BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, i
         p.off_items = take((size_t)p.item_max * 2 * sizeof(SortItem));
         p.off_stack = take((capacity / kBigMax + 2) * 8);
         p.bytes = std::max(off, told);
-        if (p.bytes <= limit || small == 2 || told > limit) break;
+        if (p.bytes <= limit || told > limit || (small && p.per >= n)) break;
     }
     return p;
 }

@@ -71,13 +71,28 @@ def _groups(nv, n, w, h, chunks):
 
 @pytest.mark.parametrize("n,w,h,cap", [(200_000, 7680, 4320, 3_000_000), (300_000, 7680, 4320, 3_000_000),
                                        (1_000_000, 7680, 4320, 3_000_000), (1_000_000, 7680, 4320, 5_000_000),
-                                       (1_000_000, 5120, 2880, 5_000_000)])
+                                       (1_000_000, 5120, 2880, 5_000_000), (20_000, 16384, 16384, 5_200_000),
+                                       (1_000_000, 16384, 16384, 4_500_000)])
 def test_static_scratch_keeps_the_gpu_busy(plan, n, w, h, cap):
     (nbytes, chunks, _), (_, free, _) = plan([(1, n, w, h, cap, STATIC), (1, n, w, h, cap, 0)])
     assert nbytes <= STATIC
     # half the chunks that no limit would give, at least: one halving leaves 128 workgroups
     assert chunks >= (free + 1) // 2
     assert _groups(1, n, w, h, chunks) >= min(100, n // 2048)
+
+
+def test_static_scratch_is_enough_whenever_it_was(plan):
+    """Every call whose stated size fits the scratch has a layout that fits; the others stay refused."""
+    rng = np.random.default_rng(3)
+    calls = []
+    for _ in range(3000):
+        nv = int(rng.integers(1, 4)) if rng.uniform() < 0.8 else int(2 ** rng.uniform(0, 12))
+        w, h = (int(2 ** rng.uniform(0, 15)) for _ in range(2))
+        calls.append((nv, min(int(2 ** rng.uniform(0, 25)), (2 ** 31 - 1) // nv), w, h, int(2 ** rng.uniform(0, 22.9)), STATIC))
+    told = np.array([_told(*c[:5]) for c in calls])
+    got = plan(calls)[:, 0]
+    assert 500 < (told <= STATIC).sum() < 2900
+    np.testing.assert_array_equal(got <= STATIC, told <= STATIC)
 
 
 def test_memory_is_bounded_however_many_tiles(plan):
