@@ -53,6 +53,7 @@ struct BinPack {
     uint32_t chunk_begin[kMaxViews + 1];   // chunks of earlier views in this launch
     uint32_t block_begin[kMaxViews + 1];   // column-scan blocks of earlier views
     uint32_t tile0, tiles;                 // global tiles of the launch
+    uint32_t bands;                        // of its view with the most tiles
     BinView v[kMaxViews];
 };
 
@@ -79,12 +80,13 @@ struct BinArrays {
     uint32_t* missing_at;   // [views] and their first position
     uint32_t* block_sum;    // [64-tile blocks], scanned by step 3
     uint64_t* chunk_sum;    // [chunks], scanned by step 3
+    uint32_t* miss;         // [chunks][bands] entries without a tile, where a view has several bands
     uint32_t* counters;
     uint32_t *mid, *big;    // tiles listed by segment length
     SortItem *large, *mid_item, *big_item;
     uint2* stack;           // pending ranges of step 5: slots start / 4096 .. of each segment
     uint32_t list_max, large_max, item_max;
-    uint32_t blocks, chunks, views;
+    uint32_t blocks, chunks, views, bands;
 };
 
 // Inclusive scan over the 64 lanes of a wave: DPP shifts inside the four 16-lane rows, then the
@@ -139,6 +141,14 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T* s_tmp, T& total) {
     return before + inc - x;
 }
 
+// Orders the LDS accesses of a wave before and after (the hardware completes a wave's LDS
+// operations in order; this holds the compiler to it).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- Tile boxes -----------------------------------------------------------------------------
 
 // The candidate tiles of a particle, row-major cells of a w x h box.
@@ -146,6 +156,11 @@ struct TileBox {
     float u, v, r2, w_lim, h_lim;
     int tx0, ty0, w, h;
     __device__ bool member(int cx, int cy) const { return tile_member(u, v, r2, tx0 + cx, ty0 + cy, w_lim, h_lim); }
+    // the tiles of the view from its first cell to its last (an empty box: tile 0)
+    __device__ uint2 span(const BinView& vd) const {
+        const uint32_t first = (uint32_t)(ty0 * vd.tiles_x + tx0);
+        return w ? make_uint2(first, first + (uint32_t)((h - 1) * vd.tiles_x + w - 1)) : make_uint2(0u, 0u);
+    }
 };
 
 // What a particle's box is made of.
@@ -257,28 +272,92 @@ __device__ __forceinline__ uint32_t count_members(const TileBox& b, uint32_t wan
     return n;
 }
 
+// Chunk and band of workgroup b of work_blocks: the bands of a chunk, which read the same
+// particles, follow each other on one XCD (b mod 8). Eight chunks at a time, some past the last;
+// of fewer than kXcdChunks that would leave XCDs idle. 6M particles in 5120 x 2880: 519 -> 497 us,
+// in 7680 x 4320 779 -> 734; with 28 chunks on eight XCDs 12288 x 6912 took 1569 us against 1327.
+constexpr uint32_t kXcdChunks = 32;
+struct ChunkBand {
+    uint32_t chunk, band;
+};
+__host__ __device__ constexpr uint32_t work_blocks(uint32_t chunks, uint32_t bands) {
+    return bands == 1 ? chunks : (chunks >= kXcdChunks ? (chunks + 7u) / 8u * 8u : chunks) * bands;
+}
+template <bool BANDED>
+__device__ __forceinline__ ChunkBand chunk_band(uint32_t b, uint32_t chunks, uint32_t bands) {
+    if (!BANDED || bands == 1) return {b, 0u};
+    if (chunks < kXcdChunks) return {b % chunks, b / chunks};
+    const uint32_t group = b / (8u * bands), in = b - group * 8u * bands;
+    return {8u * group + (in & 7u), in >> 3};
+}
+
 __device__ __forceinline__ int view_of_chunk(const BinPack& pk, uint32_t b) {
     int v = 0;
     for (int i = 1; i < pk.nv; ++i) v = (b >= pk.chunk_begin[i]) ? i : v;
     return __builtin_amdgcn_readfirstlane(v);
 }
 
+// A wave's particles whose boxes reach into the workgroup's band, gathered until there is one per
+// lane: a view of many bands has few of any 64 particles in one of them, and a wave walks as long
+// for one particle as for 64. From kQueueDirect lanes on they are walked where they are, which
+// saves loading them again. Bin sort of one view, walked by every band and ungathered before,
+// and now: 1M particles, 7680 x 4320, 428 -> 273 us, 12288 x 6912 1.40 -> 0.47 ms, 16384 x 16384
+// 11.4 -> 1.7 ms; 300k in 32768 x 32768 130 -> 5.3 ms. From 8 lanes on 12288 x 6912 takes 664 us,
+// from 16 521; never, 477, but 6M particles in 7680 x 4320 724 us against 685.
+constexpr int kQueueDirect = 24;
+struct BoxQueue {
+    uint32_t* at;        // this wave's 2 kWave words of LDS
+    uint32_t held = 0;   // uniform over the wave
+    // Adds `value` of the lanes with `in`; calls fn(value) for the G lanes of each particle taken.
+    // Where enough of the wave is in, now() walks those at once.
+    template <int G, typename Fn, typename Now>
+    __device__ __forceinline__ void add(bool in, uint32_t value, Fn fn, Now now) {
+        const uint64_t m = ballot64(in);
+        if (G == 1 && __popcll(m) >= kQueueDirect) {   // uniform
+            if (in) now();
+            return;
+        }
+        if (in) at[held + rank_below(m)] = value;
+        held += (uint32_t)__popcll(m);
+        if (held < (uint32_t)kWave) return;   // uniform
+        held -= kWave;
+        take<G>(held, kWave, fn);
+    }
+    template <int G, typename Fn>
+    __device__ __forceinline__ void end(Fn fn) {
+        take<G>(0, held, fn);
+    }
+
+private:
+    template <int G, typename Fn>
+    __device__ __forceinline__ void take(uint32_t from, uint32_t n, Fn fn) {
+        wave_lds_order();
+        for (uint32_t q = lane_id() / G; q < n; q += kWave / G) fn(at[from + q]);
+        wave_lds_order();
+    }
+};
+
 // Step 1. A particle has no more entries than its tile count says; missing ones (the count may
 // come from elsewhere) belong to no tile and go behind all others. G lanes share a particle
-// (small scenes: few particles, large boxes), blockIdx.y is the band of tiles. Bound by the
-// records' bytes and the walk over the box.
-template <uint32_t BT, int G>
+// (small scenes: few particles, large boxes). Bound by the records' bytes and the walk over the box.
+// BANDED: a view of the call has several bands. Each of them reads every particle and walks those
+// that reach into it, and the band of a box's first tile counts its missing entries and keeps its
+// packed form.
+template <uint32_t BT, int G, bool BANDED>
 __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk, const float4* __restrict__ record,
                                                                 const uint32_t* __restrict__ tile_count,
                                                                 const BinArrays A) {
     __shared__ uint32_t s_h[BT];
     __shared__ unsigned long long s_sum;
     __shared__ uint32_t s_miss;
+    constexpr uint32_t kStep = BANDED ? kBinThreads : kBinThreads / G;   // particles per turn
     const uint32_t t = threadIdx.x, j = t % G;
-    const int vi = view_of_chunk(pk, blockIdx.x);
+    const ChunkBand cb = chunk_band<BANDED>(blockIdx.x, pk.chunk_begin[pk.nv], pk.bands);
+    if (BANDED && cb.chunk >= pk.chunk_begin[pk.nv]) return;
+    const int vi = view_of_chunk(pk, cb.chunk);
     const BinView& vd = pk.v[vi];
-    const uint32_t row = blockIdx.x - pk.chunk_begin[vi], t0 = blockIdx.y * BT;
-    if (t0 >= vd.tiles && blockIdx.y) return;   // (uniform) fewer bands than the launch's largest view
+    const uint32_t row = cb.chunk - pk.chunk_begin[vi], t0 = cb.band * BT;
+    if (t0 >= vd.tiles && cb.band) return;   // (uniform) fewer bands than the launch's largest view
     const uint32_t nt = min(BT, vd.tiles - t0);
     for (uint32_t q = t; q < nt; q += kBinThreads) s_h[q] = 0u;
     if (t == 0) {
@@ -289,26 +368,13 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
     const uint32_t c0 = row * vd.per, c1 = min(vd.n, c0 + vd.per);
     unsigned long long sum = 0;
     uint32_t miss = 0;
-    // the next particle is loaded while this one is walked (past the end: the last one again)
-    const uint32_t last = vd.p_off + max(c1, 1u) - 1u, first = vd.p_off + c0 + t / G;
-    BoxLoad next_box{0.0f, 0.0f, 0.0f};
-    uint32_t next_want = 0;
-    if (c0 < c1) {
-        next_box = load_footprint(record, min(first, last));
-        next_want = tile_count[min(first, last)];
-    }
-    for (uint32_t q = c0; q < c1; q += kBinThreads / G) {
-        const uint32_t i = q + t / G, g = vd.p_off + i;
-        const BoxLoad load = next_box;
-        const uint32_t want = i < c1 ? next_want : 0u;
-        next_box = load_footprint(record, min(g + kBinThreads / G, last));
-        next_want = tile_count[min(g + kBinThreads / G, last)];
-        if (!want) continue;   // whole groups
-        const TileBox b = make_box(vd, load);
+    // one particle, by its G lanes
+    auto walk = [&](uint32_t g, uint32_t want, const TileBox& b) {
         auto put = [&](uint32_t tile) {
             if (tile - t0 < nt) atomicAdd(&s_h[tile - t0], 1u);
         };
-        uint2 packed = make_uint2(0u, kBoxWalk);
+        const uint2 span = BANDED ? b.span(vd) : make_uint2(0u, 0u);
+        uint2 packed = make_uint2(span.x, kBoxWalk | span.y);
         uint32_t n;
         const uint32_t mask = b.w <= 4 && b.h <= 4 ? box_mask4(b) : 0u;
         if ((uint32_t)__popc(mask) == want && (b.tx0 | b.ty0) < 4096) {
@@ -318,22 +384,61 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
         } else {
             n = walk_box<G>(vd, b, want, j, put);
         }
-        if (j == 0) {
-            sum += want;
+        if (j == 0 && span.x - t0 < nt) {   // (one band: always)
             miss += want - n;
-            if (A.box && blockIdx.y == 0) A.box[g] = packed;
+            if (A.box) A.box[g] = packed;
+        }
+    };
+    // the next particle is loaded while this one is walked (past the end: the last one again)
+    const uint32_t mine = BANDED ? t : t / G;
+    const uint32_t last = vd.p_off + max(c1, 1u) - 1u, first = vd.p_off + c0 + mine;
+    BoxLoad next_box{0.0f, 0.0f, 0.0f};
+    uint32_t next_want = 0;
+    if (c0 < c1) {
+        next_box = load_footprint(record, min(first, last));
+        next_want = tile_count[min(first, last)];
+    }
+    auto next = [&](uint32_t g, BoxLoad& load, uint32_t& want) {
+        load = next_box;
+        want = g < vd.p_off + c1 ? next_want : 0u;
+        next_box = load_footprint(record, min(g + kStep, last));
+        next_want = tile_count[min(g + kStep, last)];
+    };
+    BoxLoad load;
+    uint32_t want;
+    if constexpr (BANDED) {
+        __shared__ uint32_t s_queue[kBinWaves][2 * kWave];
+        BoxQueue queue{s_queue[t >> 6]};
+        auto gathered = [&](uint32_t g) { walk(g, tile_count[g], make_box(vd, load_footprint(record, g))); };
+        for (uint32_t q = c0; q < c1; q += kStep) {
+            const uint32_t g = vd.p_off + q + t;
+            next(g, load, want);
+            const uint2 span = make_box(vd, load).span(vd);
+            sum += want;
+            queue.add<G>(want && span.x < t0 + nt && span.y >= t0, g, gathered,
+                         [&] { walk(g, want, make_box(vd, load)); });
+        }
+        queue.end<G>(gathered);
+    } else {
+        for (uint32_t q = c0; q < c1; q += kStep) {
+            const uint32_t g = vd.p_off + q + mine;
+            next(g, load, want);
+            if (!want) continue;   // whole groups
+            if (j == 0) sum += want;
+            walk(g, want, make_box(vd, load));
         }
     }
-    if (blockIdx.y == 0 && sum) {
-        atomicAdd(&s_sum, sum);
-        if (miss) atomicAdd(&s_miss, miss);
-    }
+    if (sum && cb.band == 0) atomicAdd(&s_sum, sum);
+    if (miss) atomicAdd(&s_miss, miss);
     __syncthreads();
     uint32_t* m = A.m + vd.m_off + (size_t)row * (vd.tiles + 1);
     for (uint32_t q = t; q < nt; q += kBinThreads) m[t0 + q] = s_h[q];
-    if (t == 0 && blockIdx.y == 0) {
-        m[vd.tiles] = s_miss;
-        A.chunk_sum[vd.chunk0 + row] = s_sum;
+    if (t == 0) {
+        if (cb.band == 0) A.chunk_sum[vd.chunk0 + row] = s_sum;
+        if (BANDED)
+            A.miss[(size_t)(vd.chunk0 + row) * A.bands + cb.band] = s_miss;
+        else
+            m[vd.tiles] = s_miss;
     }
 }
 
@@ -355,6 +460,15 @@ __global__ void __launch_bounds__(kBinThreads) bin_columns_kernel(const BinPack 
     uint32_t x[kRows], sum = 0;
 #pragma unroll
     for (uint32_t r = 0; r < kRows; ++r) x[r] = on && r < rows && r0 + r < vd.chunks ? m[(r0 + r) * pitch] : 0u;
+    if (A.bands > 1 && col == vd.tiles) {   // the entries without a tile are kept by band
+        const uint32_t bands = (vd.tiles + kBandLarge - 1) / kBandLarge;
+#pragma unroll
+        for (uint32_t r = 0; r < kRows; ++r) {
+            x[r] = 0u;
+            if (r >= rows || r0 + r >= vd.chunks) continue;
+            for (uint32_t b = 0; b < bands; ++b) x[r] += A.miss[(size_t)(vd.chunk0 + r0 + r) * A.bands + b];
+        }
+    }
 #pragma unroll
     for (uint32_t r = 0; r < kRows; ++r) sum += x[r];
     s_part[w][l] = sum;
@@ -454,10 +568,10 @@ __device__ __forceinline__ void bin_ranges(const BinPack& pk, const BinArrays& A
     if (c == 2u) A.large[at] = SortItem{start, n, pk.tile0 + i, 0u};
 }
 
-// Step 4. Workgroups past the chunks write tile ranges. The key writes are scattered: a chunk
-// has a few entries for each of thousands of tiles, so they are bound by the caches' handling
-// of partial lines rather than by bytes.
-template <uint32_t BT, int G>
+// Step 4. A workgroup takes a chunk and a band; those past them write tile ranges. The key writes
+// are scattered: a chunk has a few entries for each of thousands of tiles, so they are bound by
+// the caches' handling of partial lines rather than by bytes.
+template <uint32_t BT, int G, bool BANDED>
 __global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_eu(BT == kBandSmall ? 8 : 4))) bin_place_kernel(const BinPack pk, const float4* __restrict__ record,
                                                                 const float* __restrict__ depth,
                                                                 const uint32_t* __restrict__ tile_count,
@@ -470,20 +584,24 @@ __global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_e
     __shared__ uint32_t s_tmp[kBinWaves];
     const uint32_t t = threadIdx.x, j = t % G;
     const bool ok = *status == kStatusOk;
-    if (blockIdx.x >= pk.chunk_begin[pk.nv]) {
-        if (blockIdx.y == 0) bin_ranges(pk, A, blockIdx.x - pk.chunk_begin[pk.nv], ok, ranges);
+    const uint32_t n_chunks = pk.chunk_begin[pk.nv], n_work = BANDED ? work_blocks(n_chunks, pk.bands) : n_chunks;
+    if (blockIdx.x >= n_work) {
+        bin_ranges(pk, A, blockIdx.x - n_work, ok, ranges);
         return;
     }
-    const int vi = view_of_chunk(pk, blockIdx.x);
+    const ChunkBand cb = chunk_band<BANDED>(blockIdx.x, n_chunks, pk.bands);
+    if (BANDED && cb.chunk >= n_chunks) return;
+    const int vi = view_of_chunk(pk, cb.chunk);
     const BinView& vd = pk.v[vi];
-    const uint32_t row = blockIdx.x - pk.chunk_begin[vi], t0 = blockIdx.y * BT;
-    if (t0 >= vd.tiles && blockIdx.y) return;
+    const uint32_t row = cb.chunk - pk.chunk_begin[vi], t0 = cb.band * BT;
+    if (t0 >= vd.tiles && cb.band) return;
     const uint32_t nt = min(BT, vd.tiles - t0), count = *count_p;
     const uint32_t* m = A.m + vd.m_off + (size_t)row * (vd.tiles + 1);
     if (ok)
+#pragma unroll 4
         for (uint32_t q = t; q < nt; q += kBinThreads) s_c[q] = tile_start(A, vd, t0 + q) + m[t0 + q];
     const uint32_t c0 = row * vd.per, c1 = min(vd.n, c0 + vd.per);
-    if (blockIdx.y == 0) {
+    if (cb.band == 0) {
         // emit offsets, and the entries without a tile (emit order)
         const uint32_t n_missing = ok ? m[vd.tiles] : 0u;   // (of earlier chunks: a prefix)
         const bool any_missing = ok && A.missing[pk.view0 + vi] != 0u;
@@ -505,18 +623,9 @@ __global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_e
     }
     if (!ok || c0 >= c1) return;
     __syncthreads();
-    const uint32_t last = vd.p_off + c1 - 1u, first = min(vd.p_off + c0 + t / G, last);
-    uint32_t next_want = tile_count[first], next_z = __float_as_uint(depth[first]);
-    uint2 next_box = A.box ? A.box[first] : make_uint2(0u, kBoxWalk);
-    for (uint32_t q = c0; q < c1; q += kBinThreads / G) {
-        const uint32_t i = q + t / G, g = vd.p_off + i, ahead = min(g + kBinThreads / G, last);
-        const uint32_t want = i < c1 ? next_want : 0u;
-        const uint64_t key = (uint64_t)next_z << 32 | g;
-        const uint2 b = next_box;
-        next_want = tile_count[ahead];
-        next_z = __float_as_uint(depth[ahead]);
-        if (A.box) next_box = A.box[ahead];
-        if (!want) continue;
+    // one particle, by its G lanes
+    auto place = [&](uint32_t g, uint32_t want, uint32_t z, const uint2& b) {
+        const uint64_t key = (uint64_t)z << 32 | g;
         auto put = [&](uint32_t tile) {
             if (tile - t0 >= nt) return;
             const uint32_t p = atomicAdd(&s_c[tile - t0], 1u);
@@ -526,6 +635,48 @@ __global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_e
             walk_box<G>(vd, make_box(vd, load_footprint(record, g)), want, j, put);
         else if (j == 0)
             put_mask4(b.x, (b.y >> 12) * (uint32_t)vd.tiles_x + (b.y & 0xFFFu), (uint32_t)vd.tiles_x, put);
+    };
+    constexpr uint32_t kStep = BANDED ? kBinThreads : kBinThreads / G;
+    const uint32_t mine = BANDED ? t : t / G;
+    const uint32_t last = vd.p_off + c1 - 1u, first = min(vd.p_off + c0 + mine, last);
+    uint32_t next_want = tile_count[first], next_z = __float_as_uint(depth[first]);
+    uint2 next_box = A.box ? A.box[first] : make_uint2(0u, kBoxWalk);
+    if constexpr (BANDED) {
+        __shared__ uint32_t s_queue[kBinWaves][2 * kWave];
+        BoxQueue queue{s_queue[t >> 6]};
+        auto gathered = [&](uint32_t g) {
+            place(g, tile_count[g], __float_as_uint(depth[g]), A.box ? A.box[g] : make_uint2(0u, kBoxWalk));
+        };
+        for (uint32_t q = c0; q < c1; q += kStep) {
+            const uint32_t g = vd.p_off + q + t, ahead = min(g + kStep, last);
+            const uint32_t want = q + t < c1 ? next_want : 0u, z = next_z;
+            const uint2 b = next_box;
+            next_want = tile_count[ahead];
+            next_z = __float_as_uint(depth[ahead]);
+            if (A.box) next_box = A.box[ahead];
+            uint2 span;
+            if (!A.box) {
+                span = make_box(vd, load_footprint(record, min(g, last))).span(vd);
+            } else if (b.y & kBoxWalk) {
+                span = make_uint2(b.x, b.y & ~kBoxWalk);
+            } else {   // (four rows: no member lies beyond)
+                span.x = (b.y >> 12) * (uint32_t)vd.tiles_x + (b.y & 0xFFFu);
+                span.y = span.x + 3u * (uint32_t)vd.tiles_x + 3u;
+            }
+            queue.add<G>(want && span.x < t0 + nt && span.y >= t0, g, gathered,
+                         [&] { place(g, want, z, b); });
+        }
+        queue.end<G>(gathered);
+    } else {
+        for (uint32_t q = c0; q < c1; q += kStep) {
+            const uint32_t i = q + mine, g = vd.p_off + i, ahead = min(g + kStep, last);
+            const uint32_t want = i < c1 ? next_want : 0u, z = next_z;
+            const uint2 b = next_box;
+            next_want = tile_count[ahead];
+            next_z = __float_as_uint(depth[ahead]);
+            if (A.box) next_box = A.box[ahead];
+            if (want) place(g, want, z, b);   // whole groups
+        }
     }
 }
 
@@ -1131,7 +1282,7 @@ BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, i
     p.n_total = (uint32_t)n;
     p.tiles_total = (uint32_t)tiles;
     p.large_band = most_tiles > kBandSmall;
-    const uint32_t bands = p.large_band ? (most_tiles + kBandLarge - 1) / kBandLarge : 1u;
+    p.bands = p.large_band ? (most_tiles + kBandLarge - 1) / kBandLarge : 1u;
     // The size that callers are told: 20 bytes per entry of capacity and tile, a tile digit
     // histogram per 4096 entries and the tables of the long segments. The layout below takes
     // more for scenes of many more particles than entries (the boxes) and for few entries in
@@ -1141,7 +1292,7 @@ BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, i
     const uint64_t sort_tiles = (capacity + 4095) / 4096, long_max = std::min<uint64_t>(tiles, capacity / 16385 + 1);
     const size_t told = 5 * align256(capacity * 4) + (size_t)sort_tiles * 2048 + (size_t)(sort_tiles + long_max) * 1028 +
                         (size_t)long_max * 40 + (size_t)tiles * 20 + (n + 2047) / 2048 * 4 + 40960;
-    p.per = chunk_particles(n, nv, p.large_band, bands);
+    p.per = chunk_particles(n, nv, p.large_band, p.bands);
     for (int small = 0;; ++small) {
         if (small > 1) p.per = (uint32_t)std::min<uint64_t>(2ull * p.per, 0x7FFFFFFFu);
         uint64_t chunks = 0, blocks = 0, m = 0;
@@ -1173,6 +1324,7 @@ BinSortPlan plan_bin_sort(const int32_t* n_per_view, const isogs_camera* cams, i
         p.off_missing = take((size_t)nv * 8);
         p.off_block_sum = take(blocks * 4);
         p.off_chunk_sum = take(chunks * 8);
+        p.off_miss = take(p.bands > 1 ? (size_t)chunks * p.bands * 4 : 0);
         p.off_counters = take(kCounterWords * 4);
         p.off_lists = take((size_t)p.list_max * 8 + (size_t)p.large_max * sizeof(SortItem) + 16);
         p.off_items = take((size_t)p.item_max * 2 * sizeof(SortItem));
@@ -1211,8 +1363,13 @@ int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const 
     A.blocks = plan.blocks;
     A.chunks = plan.chunks;
     A.views = (uint32_t)nv;
+    A.bands = plan.bands;
+    A.miss = at(plan.off_miss);
     const float4* record = reinterpret_cast<const float4*>(proj->record);
-    const bool group = plan.n_total <= kGroupMaxParticles;
+    // eight lanes per particle: few particles, or (a view of several bands) boxes of many tiles,
+    // told by a capacity of 16 entries per particle: 300k particles with 50 each in 16384 x 16384
+    // take 1.28 ms with eight lanes and 1.65 with one, 6M with 10 each 4.17 and 3.33
+    const bool group = plan.n_total <= kGroupMaxParticles || (plan.bands > 1 && plan.capacity >= 16ull * plan.n_total);
     const uint32_t band = plan.large_band ? kBandLarge : kBandSmall;
 
     // groups of up to kMaxViews views: counts and columns, then (all views) the scans, then
@@ -1258,17 +1415,24 @@ int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const 
             pk.chunk_begin[pk.nv] = chunks;
             pk.block_begin[pk.nv] = blocks;
             pk.tiles = tile_base - pk.tile0;
+            pk.bands = bands;
             if (stage == 0) {
-                auto count = plan.large_band ? (group ? bin_count_kernel<kBandLarge, 8> : bin_count_kernel<kBandLarge, 1>)
-                                             : (group ? bin_count_kernel<kBandSmall, 8> : bin_count_kernel<kBandSmall, 1>);
+                auto count = plan.bands > 1
+                                 ? (group ? bin_count_kernel<kBandLarge, 8, true> : bin_count_kernel<kBandLarge, 1, true>)
+                             : plan.large_band
+                                 ? (group ? bin_count_kernel<kBandLarge, 8, false> : bin_count_kernel<kBandLarge, 1, false>)
+                                 : (group ? bin_count_kernel<kBandSmall, 8, false> : bin_count_kernel<kBandSmall, 1, false>);
                 if (chunks)
-                    hipLaunchKernelGGL(count, dim3(chunks, bands), dim3(kBinThreads), 0, stream, pk, record,
+                    hipLaunchKernelGGL(count, dim3(work_blocks(chunks, bands)), dim3(kBinThreads), 0, stream, pk, record,
                                        proj->tile_count, A);
                 hipLaunchKernelGGL(bin_columns_kernel, dim3(blocks), dim3(kBinThreads), 0, stream, pk, A);
             } else {
-                auto place = plan.large_band ? (group ? bin_place_kernel<kBandLarge, 8> : bin_place_kernel<kBandLarge, 1>)
-                                             : (group ? bin_place_kernel<kBandSmall, 8> : bin_place_kernel<kBandSmall, 1>);
-                hipLaunchKernelGGL(place, dim3(chunks + (pk.tiles + kBinThreads - 1) / kBinThreads, bands),
+                auto place = plan.bands > 1
+                                 ? (group ? bin_place_kernel<kBandLarge, 8, true> : bin_place_kernel<kBandLarge, 1, true>)
+                             : plan.large_band
+                                 ? (group ? bin_place_kernel<kBandLarge, 8, false> : bin_place_kernel<kBandLarge, 1, false>)
+                                 : (group ? bin_place_kernel<kBandSmall, 8, false> : bin_place_kernel<kBandSmall, 1, false>);
+                hipLaunchKernelGGL(place, dim3(work_blocks(chunks, bands) + (pk.tiles + kBinThreads - 1) / kBinThreads),
                                    dim3(kBinThreads), 0, stream, pk, record, proj->depth, proj->tile_count, A,
                                    bins->status, bins->count, bins->ranges, bins->offsets, bins->pidx);
             }

@@ -18,10 +18,11 @@ struct BinSortPlan {
     uint32_t tiles_total;   // global tiles over all views
     bool large_band;        // a view has more tiles than the smaller kernels count at once
     bool boxes;             // packed tile boxes are kept between the two passes over the particles
+    uint32_t bands;         // of the view with the most tiles
     uint32_t per;           // particles per chunk
     uint32_t chunks, blocks;   // chunks and 64-tile blocks over all views
     uint32_t list_max, large_max, item_max;   // bounds on the listed segments and their pieces
-    size_t off_key, off_z, off_box, off_m, off_tile_pre, off_tile_tot, off_missing, off_block_sum, off_chunk_sum,
+    size_t off_key, off_z, off_box, off_m, off_tile_pre, off_tile_tot, off_missing, off_block_sum, off_chunk_sum, off_miss,
         off_counters, off_lists, off_items, off_stack, bytes;
 };
 
