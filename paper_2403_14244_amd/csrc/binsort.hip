@@ -723,7 +723,8 @@ template <int THREADS, int ITEMS>
 struct __align__(16) SortShared {
     union {
         uint64_t key[THREADS * ITEMS];
-        uint32_t part[THREADS * 4 + 4];   // before the entries are stored
+        uint32_t part[THREADS * 4 + 4];     // before the entries are stored
+        uint32_t sorted[THREADS * ITEMS];   // their indices in order, after the keys have been read
     };
     uint32_t base[THREADS * ITEMS + 4];
     uint32_t red[2][THREADS / kWave];
@@ -734,7 +735,7 @@ struct __align__(16) SortShared {
 template <int THREADS>
 __device__ __forceinline__ void group_sync() {
     if (THREADS == kWave)
-        __builtin_amdgcn_wave_barrier();   // LDS operations of one wave complete in order
+        wave_lds_order();
     else
         __syncthreads();
 }
@@ -871,7 +872,6 @@ __device__ __forceinline__ void sort_piece(SortShared<THREADS, ITEMS>& sh, uint6
         if (len[i]) sh.key[lo[i] + (slot[i] >> 16)] = k[i];
     }
     group_sync<THREADS>();
-    uint32_t* out = reinterpret_cast<uint32_t*>(sh.key);
     if (most <= kBucketMax) {
         // the ITEMS buckets side by side, so that their reads are in flight together
         uint32_t rank[ITEMS], longest = 0;
@@ -893,7 +893,7 @@ __device__ __forceinline__ void sort_piece(SortShared<THREADS, ITEMS>& sh, uint6
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             if (!len[i]) continue;
-            out[lo[i] + rank[i]] = (uint32_t)k[i];
+            sh.sorted[lo[i] + rank[i]] = (uint32_t)k[i];
             if (keys64) keys64[start + lo[i] + rank[i]] = (uint64_t)tile << 32 | k[i] >> 32;
         }
         group_sync<THREADS>();
@@ -923,7 +923,7 @@ __device__ __forceinline__ void sort_piece(SortShared<THREADS, ITEMS>& sh, uint6
         for (int i = 0; i < ITEMS; ++i) {
             const uint32_t p = (uint32_t)i * THREADS + t;
             if (p >= n) continue;
-            out[p] = (uint32_t)r[i];
+            sh.sorted[p] = (uint32_t)r[i];
             if (keys64) keys64[start + p] = (uint64_t)tile << 32 | r[i] >> 32;
         }
         group_sync<THREADS>();
@@ -931,7 +931,7 @@ __device__ __forceinline__ void sort_piece(SortShared<THREADS, ITEMS>& sh, uint6
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const uint32_t p = (uint32_t)i * THREADS + t;
-        if (p < n) pidx[start + p] = out[p];
+        if (p < n) pidx[start + p] = sh.sorted[p];
     }
 }
 
