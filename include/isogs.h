@@ -160,7 +160,11 @@ int isogs_project(const isogs_scene* scenes, const isogs_camera* cams, int32_t n
  * and, if requested, the keys.
  *   n_per_view  host array [V]: particles of each view (the n of its scene)
  *   ws, ws_bytes  workspace; with ws == NULL only *ws_bytes is written (the bytes needed
- *                 for this capacity and these views), and nothing is launched.
+ *                 for this capacity and these views), and nothing is launched. About 21
+ *                 bytes per entry of capacity, 20 bytes per tile and 0.3 MB, or, where that
+ *                 is more, 12 bytes per entry, 8 per particle, 16 per tile and the counts
+ *                 of entries per tile, 2 KB per tile at most and 38 MB (75 MB with a view of
+ *                 more than 147456 tiles).
  * Errors: ISOGS_ERR_INVALID (bad arguments), ISOGS_ERR_WORKSPACE (ws too small),
  * ISOGS_ERR_DEVICE; overflow of `capacity` is reported in *status on the device. */
 int isogs_bin_sort(const isogs_projected* proj, const int32_t* n_per_view,
@@ -173,10 +177,11 @@ int isogs_bin_sort(const isogs_projected* proj, const int32_t* n_per_view,
  * static device array of ISOGS_STATIC_SCRATCH_BYTES that the library holds on each GPU it
  * runs on until the process ends (its address is looked up once per device, on the first
  * call with that device current). The caller still owns and passes proj and bins.
- *   - Limit: the call needs the scratch isogs_bin_sort reports for the same arguments
- *     (about 21 bytes per entry of capacity, 20 bytes per tile and 0.3 MB); above
- *     ISOGS_STATIC_SCRATCH_BYTES it returns ISOGS_ERR_WORKSPACE and launches nothing
- *     (128 MiB: about 6M entries, three 1080p views of a 1M-particle scene).
+ *   - Limit: the call needs about 21 bytes per entry of capacity, 20 bytes per tile and
+ *     0.3 MB; above ISOGS_STATIC_SCRATCH_BYTES it returns ISOGS_ERR_WORKSPACE and launches
+ *     nothing (128 MiB: about 6M entries, three 1080p views of a 1M-particle scene). Where
+ *     isogs_bin_sort reports more for the same arguments and the array has no room for it,
+ *     the call reads the particles' records twice, or counts with fewer workgroups.
  *   - No hipMalloc, hipFree or allocating library call is made; the bookkeeping that must
  *     start at zero is cleared by a kernel on `stream` at every call.
  *   - Every call on one GPU shares that GPU's array, which keeps the last call's contents:
@@ -219,11 +224,13 @@ int isogs_render_fwd(const isogs_projected* proj, const int32_t* n_per_view,
 #define ISOGS_FWD_TIMES 2u  /* per-workgroup clock stamps in the workspace (see below) */
 
 /* Same outputs as isogs_render_fwd (bitwise), with the tiles dispatched longest entry list
- * first: a queue of the tiles sorted by list length is built on the device and workgroup b
- * composites the tile at queue position b, so that the few very long tiles of skewed scenes
- * start first instead of trailing the launch. Launches of few tiles (at most 24576 per group
- * of 16 views) use a software-pipelined walk that shortens the longest tiles; larger ones a
- * compact walk that keeps more workgroups resident.
+ * first: a queue of the tiles sorted by list length is built on the device and taken from the
+ * front, eight consecutive positions by each XCD in turn, so that the few very long tiles of
+ * skewed scenes start first instead of trailing the launch. A launch of at most 768 tiles
+ * without ISOGS_FWD_WIDE, whose workgroups all start at once, takes its tiles in index order
+ * and builds no queue. Launches of few tiles (at most 24576 per group of 16 views) use a
+ * software-pipelined walk that shortens the longest tiles; larger ones a compact walk that
+ * keeps more workgroups resident.
  *   flags  0, or ISOGS_FWD_WIDE: every tile of at least 2048 entries is composited by
  *          four workgroups, one per 8x8 quadrant, with four lanes per pixel that take the
  *          four entries of a list step together (transmittance products scanned across
@@ -237,7 +244,10 @@ int isogs_render_fwd(const isogs_projected* proj, const int32_t* n_per_view,
  *          {start, end} pair of uint64 stamps of the GPU's constant 100 MHz clock per
  *          workgroup: the workgroups of the launch for the group of views whose first tile
  *          is the call's tile t occupy pairs 5t, 5t + 1, ...; a workgroup whose list was
- *          empty, or that had no tile, leaves {0, 0}. The images are the same as without it.
+ *          empty, or that had no tile, leaves {0, 0}. With ISOGS_FWD_WIDE, where the capacity
+ *          and the group's tiles allow more than 4096 tiles of 2048 entries, a quadrant's
+ *          workgroup composites several of them in turn and its pair runs from the start of
+ *          the first to the end of the last. The images are the same as without it.
  *   ws, ws_bytes  workspace (query with ws == NULL, with the same flags): the queue, 4 bytes
  *                 per tile of the largest group of 16 views, plus bookkeeping
  * Errors: ISOGS_ERR_INVALID, ISOGS_ERR_WORKSPACE, ISOGS_ERR_DEVICE. */

@@ -225,8 +225,9 @@ class Rasterizer:
         `last=False`: no n_last (None), for a forward that no backward pass follows (the
         walk then skips tracking the last entry). `times`: also returns the per-workgroup
         {start, end} stamps of the 100 MHz clock, int64 [5 * tiles, 2] ({0, 0} for
-        workgroups without a non-empty list), as a view of the workspace that the next call
-        on this rasterizer overwrites."""
+        workgroups without a non-empty list; with `wide` and more than 4096 possible long
+        tiles one pair spans the several tiles that a workgroup takes), as a view of the
+        workspace that the next call on this rasterizer overwrites."""
         pix = sum(int(c.width) * int(c.height) for c in cams)
         if out is None:
             out = (torch.empty(3 * pix, dtype=_F32, device=self.device),
