@@ -528,11 +528,13 @@ struct BwdArgs {
 // LOOP: a workgroup takes every gridDim.x-th item. Otherwise it takes one, and leaves at once
 // past the last: the number of items is known on the device only, at most tiles + capacity /
 // kCkptChunk, and where much of the lists lies behind opaque particles most workgroups find none,
-// after waiting for LDS and two loads (two thirds of 760 thousand in eight 4K views of
-// 6M particles: 3 to 4% longer than 16384 to 131072 workgroups that loop; the 1024 that reside
-// are 6% slower). The loop costs registers and a barrier per item, 3% of one 1080p view (15
-// thousand items at most), so it is for launches of more than kBwdLoopItems.
-constexpr uint32_t kBwdLoopGrid = 32768, kBwdLoopItems = 2 * kBwdLoopGrid;
+// after waiting for LDS and two loads (two thirds of 760 thousand in eight 4K views of 6M
+// particles, with 16384 to 131072 workgroups alike; the 1024 that reside are 6% slower). The
+// loop costs registers and a barrier per item, so it is for launches of more than kBwdLoopItems.
+// Without and with it: 1080p views of 1M particles, one (17 thousand items) 245 and 246 us, four (67)
+// 761 and 776, ten (166) 1.87 and 1.92 ms, 16 (265) 3.06 and 3.11, 20 (298) 3.90 and 3.91; eight 4K
+// views (370) 3.45 and 3.43, of 6M particles four (382) 2.54 and 2.52, eight (766) 5.14 and 5.04.
+constexpr uint32_t kBwdLoopGrid = 32768, kBwdLoopItems = 10 * kBwdLoopGrid;
 
 template <bool AN, bool LOOP>
 __device__ __forceinline__ void bwd_ordered(StagedBwdT<AN>& sb, const RenderPack& pk, const BwdArgs& A) {
