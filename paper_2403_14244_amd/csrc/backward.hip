@@ -917,7 +917,7 @@ __device__ __forceinline__ float reload(float x) {
 // Registers: one view (ONE) holds no sums across views and stores its colour gradients before
 // the chain rule, so that three waves per SIMD reside; more views need up to 224 registers and
 // two. A 1080p view of 1M particles, degree 3: 204 us with 264 registers and one wave, 141 at
-// two waves, 134 at three, 172 at four (which spill).
+// two waves, 134 at three (which spill six registers), 172 at four (which spill more).
 template <bool ONE>
 constexpr int kAnisoGradWaves = ONE ? 3 : 2;
 

@@ -29,7 +29,10 @@ constexpr int kBinWaves = kBinThreads / kWave;
 constexpr uint32_t kColTiles = 64;                      // tiles per column-scan workgroup
 constexpr uint32_t kMaxChunks = 512;                    // rows of a view's matrix at most
 // tiles a workgroup counts at once (one LDS word each): views of up to 1080p, and larger ones
-// (4K has 32400) with one workgroup per CU; a view with more tiles is taken in bands
+// (4K has 32400) with one workgroup per CU; a view with more tiles is taken in bands. Two
+// workgroups of 18432 tiles would fit a CU as well: 2560 x 1440 views of 1M particles take 114 us
+// with either, two 166, ten 712 and 715, and only four (358 and 334, by the chunks of that build)
+// differ.
 constexpr uint32_t kBandSmall = 9216, kBandLarge = 36864;
 constexpr uint32_t kSmallMax = 256;                     // sorted by one wave
 constexpr uint32_t kMidMax = 1024;                      // by four
@@ -1255,10 +1258,13 @@ static uint32_t view_tiles(const isogs_camera& c) {
 // The chunking of a call: particles per chunk. Two workgroups of 1024 threads fit a CU (one with
 // the larger band), so the chunks of all views together are at most what runs at once: 512, or
 // 256 where fewer particles are worth less than the matrix rows (4 bytes per tile of the view)
-// that more chunks cost. Every band of a view takes each chunk, so a view of several bands has
-// that many times fewer chunks (twice those 256 workgroups above four bands, whose shares of the
-// particles differ more): the matrix then has at most 256 kBandLarge counts (512 above four bands),
-// 38 MB (75 MB), and a row per view, however many tiles.
+// that more chunks cost. With 256 and 512, 1080p views of 1M particles: one 97 and 104 us, three 186
+// and 195, four 291 and 283, six 366 and 362, ten 623 and 614. Every band of a view takes each
+// chunk, so a view of several bands has that many times fewer chunks (twice those 256 workgroups
+// above four bands, whose shares of the particles differ more): the matrix then has at most 256
+// kBandLarge counts (512 above four bands), 38 MB (75 MB), and a row per view, however many tiles.
+// With 256 and 512 workgroups: 5120 x 2880 of 1M particles (two bands) 190 and 220 us, 12288 x 6912 of
+// 300k (nine) 451 and 423, 16384 x 16384 of 1M (28) 1.96 and 1.80 ms.
 static uint32_t chunk_particles(uint64_t n_total, int32_t nv, bool large_band, uint32_t bands) {
     const uint32_t least = n_total <= kGroupMaxParticles ? 128u : 1024u;
     const uint32_t target = bands > 4                         ? std::max(kMaxChunks / bands, 1u)

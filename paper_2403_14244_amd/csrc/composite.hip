@@ -584,8 +584,10 @@ __global__ void __launch_bounds__(256) tile_class_scatter_kernel(const uint32_t*
 
 // The whole queue by one workgroup, for launches of few tiles: the class counts and cursors stay
 // in LDS (a wave adds once per class it holds). At 256 tiles one launch of 4 us where clearing,
-// counting and placing took three of 6 us together; at 8160 tiles the one workgroup takes
-// 19 us against 9 us, so the line lies between.
+// counting and placing took three of 6 us together. A forward of next to no entries takes with
+// the one workgroup and with three launches 13.6 and 20.0 us at 1536 tiles, 14.0 and 19.9 at 2048,
+// 17.5 and 20.5 at 3072, 18.7 and 20.4 at 3600, 24.0 and 23.0 at 5130, 32.9 and 28.8 at 8160: the
+// line is where the gain is still whole, at two tiles per thread.
 constexpr uint32_t kOneQueueTiles = 2048;
 constexpr int kOneQueueThreads = 1024;
 
@@ -721,7 +723,11 @@ uint32_t* launch_tile_queue(uint32_t* q, const uint32_t* ranges, uint32_t tile0,
 // batch. LOOP: for launches whose entries could make more than kWideSlots long tiles, a
 // quadrant's workgroups take every wide_slots-th long tile: eight 4K views of 6M particles
 // started 200 thousand workgroups that found none (1.55 -> 1.46 ms). The loop costs registers:
-// one 1080p view takes 79 us with it and 75 without.
+// one 1080p view takes 79 us with it and 75 without. Without and with it, 1080p views of 1M
+// particles: two (2115 possible long tiles) 160 and 166 us, four (4235) 295 and 295, six (6336) 439
+// and 435, ten (10489) 728 and 715, 20 (20969) 1526 and 1450; one and two 4K views of 6M (7680 and
+// 15487) 248 and 246, 471 and 450; 1080p views of 6M, where most entries are in long tiles, stay 1 to
+// 2% slower with it (one, 5185: 943 and 960; four, 20962: 1369 and 1382).
 constexpr uint32_t kWideSlots = 4096;
 
 template <bool AN, bool LOOP>
