@@ -347,7 +347,7 @@ struct SsimWs {
     size_t off_m1, off_e11, off_e12, off_blocks, bytes, off_l1, loss_bytes;
 };
 
-int tiles_of(int32_t n, int edge) { return (n + edge - 1) / edge; }
+int tiles_of(int32_t n, int edge) { return (int)(((int64_t)n + edge - 1) / edge); }
 
 SsimWs ssim_layout(int32_t channels, int32_t height, int32_t width) {
     const size_t n = (size_t)channels * height * width;
