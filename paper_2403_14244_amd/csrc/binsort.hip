@@ -57,6 +57,8 @@ struct BinPack {
     uint32_t block_begin[kMaxViews + 1];   // column-scan blocks of earlier views
     uint32_t tile0, tiles;                 // global tiles of the launch
     uint32_t bands;                        // of its view with the most tiles
+    uint32_t miss_pitch;
+    uint32_t* miss;                        // [chunks][miss_pitch] entries without a tile (views of several bands)
     BinView v[kMaxViews];
 };
 
@@ -83,13 +85,12 @@ struct BinArrays {
     uint32_t* missing_at;   // [views] and their first position
     uint32_t* block_sum;    // [64-tile blocks], scanned by step 3
     uint64_t* chunk_sum;    // [chunks], scanned by step 3
-    uint32_t* miss;         // [chunks][bands] entries without a tile, where a view has several bands
     uint32_t* counters;
     uint32_t *mid, *big;    // tiles listed by segment length
     SortItem *large, *mid_item, *big_item;
     uint2* stack;           // pending ranges of step 5: slots start / 4096 .. of each segment
     uint32_t list_max, large_max, item_max;
-    uint32_t blocks, chunks, views, bands;
+    uint32_t blocks, chunks, views;
 };
 
 // Inclusive scan over the 64 lanes of a wave: DPP shifts inside the four 16-lane rows, then the
@@ -387,7 +388,7 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
         } else {
             n = walk_box<G>(vd, b, want, j, put);
         }
-        if (j == 0 && span.x - t0 < nt) {   // (one band: always)
+        if (j == 0 && (!BANDED || span.x - t0 < nt)) {
             miss += want - n;
             if (A.box) A.box[g] = packed;
         }
@@ -401,9 +402,10 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
         next_box = load_footprint(record, min(first, last));
         next_want = tile_count[min(first, last)];
     }
-    auto next = [&](uint32_t g, BoxLoad& load, uint32_t& want) {
+    auto next = [&](uint32_t i, BoxLoad& load, uint32_t& want) {
+        const uint32_t g = vd.p_off + i;
         load = next_box;
-        want = g < vd.p_off + c1 ? next_want : 0u;
+        want = i < c1 ? next_want : 0u;
         next_box = load_footprint(record, min(g + kStep, last));
         next_want = tile_count[min(g + kStep, last)];
     };
@@ -415,7 +417,7 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
         auto gathered = [&](uint32_t g) { walk(g, tile_count[g], make_box(vd, load_footprint(record, g))); };
         for (uint32_t q = c0; q < c1; q += kStep) {
             const uint32_t g = vd.p_off + q + t;
-            next(g, load, want);
+            next(q + t, load, want);
             const uint2 span = make_box(vd, load).span(vd);
             sum += want;
             queue.add<G>(want && span.x < t0 + nt && span.y >= t0, g, gathered,
@@ -424,11 +426,10 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
         queue.end<G>(gathered);
     } else {
         for (uint32_t q = c0; q < c1; q += kStep) {
-            const uint32_t g = vd.p_off + q + mine;
-            next(g, load, want);
+            next(q + mine, load, want);
             if (!want) continue;   // whole groups
+            walk(vd.p_off + q + mine, want, make_box(vd, load));
             if (j == 0) sum += want;
-            walk(g, want, make_box(vd, load));
         }
     }
     if (sum && cb.band == 0) atomicAdd(&s_sum, sum);
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
     if (t == 0) {
         if (cb.band == 0) A.chunk_sum[vd.chunk0 + row] = s_sum;
         if (BANDED)
-            A.miss[(size_t)(vd.chunk0 + row) * A.bands + cb.band] = s_miss;
+            pk.miss[(size_t)(vd.chunk0 + row) * pk.miss_pitch + cb.band] = s_miss;
         else
             m[vd.tiles] = s_miss;
     }
@@ -447,6 +448,7 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(const BinPack pk
 
 // Step 2: 64 columns (tiles; the last column of a view holds the entries without a tile) per
 // workgroup, a wave per run of up to kMaxChunks / 16 rows held in registers.
+template <bool BANDED>
 __global__ void __launch_bounds__(kBinThreads) bin_columns_kernel(const BinPack pk, const BinArrays A) {
     __shared__ uint32_t s_part[kBinWaves][kColTiles];
     constexpr uint32_t kRows = kMaxChunks / kBinWaves;
@@ -463,13 +465,13 @@ __global__ void __launch_bounds__(kBinThreads) bin_columns_kernel(const BinPack 
     uint32_t x[kRows], sum = 0;
 #pragma unroll
     for (uint32_t r = 0; r < kRows; ++r) x[r] = on && r < rows && r0 + r < vd.chunks ? m[(r0 + r) * pitch] : 0u;
-    if (A.bands > 1 && col == vd.tiles) {   // the entries without a tile are kept by band
+    if (BANDED && col == vd.tiles) {   // the entries without a tile are kept by band
         const uint32_t bands = (vd.tiles + kBandLarge - 1) / kBandLarge;
 #pragma unroll
         for (uint32_t r = 0; r < kRows; ++r) {
             x[r] = 0u;
             if (r >= rows || r0 + r >= vd.chunks) continue;
-            for (uint32_t b = 0; b < bands; ++b) x[r] += A.miss[(size_t)(vd.chunk0 + r0 + r) * A.bands + b];
+            for (uint32_t b = 0; b < bands; ++b) x[r] += pk.miss[(size_t)(vd.chunk0 + r0 + r) * pk.miss_pitch + b];
         }
     }
 #pragma unroll
@@ -601,7 +603,7 @@ __global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_e
     const uint32_t nt = min(BT, vd.tiles - t0), count = *count_p;
     const uint32_t* m = A.m + vd.m_off + (size_t)row * (vd.tiles + 1);
     if (ok)
-#pragma unroll 4
+#pragma unroll(BT == kBandLarge ? 4 : 1)
         for (uint32_t q = t; q < nt; q += kBinThreads) s_c[q] = tile_start(A, vd, t0 + q) + m[t0 + q];
     const uint32_t c0 = row * vd.per, c1 = min(vd.n, c0 + vd.per);
     if (cb.band == 0) {
@@ -1369,8 +1371,6 @@ int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const 
     A.blocks = plan.blocks;
     A.chunks = plan.chunks;
     A.views = (uint32_t)nv;
-    A.bands = plan.bands;
-    A.miss = at(plan.off_miss);
     const float4* record = reinterpret_cast<const float4*>(proj->record);
     // eight lanes per particle: few particles, or (a view of several bands) boxes of many tiles,
     // told by a capacity of 16 entries per particle: 300k particles with 50 each in 16384 x 16384
@@ -1422,6 +1422,8 @@ int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const 
             pk.block_begin[pk.nv] = blocks;
             pk.tiles = tile_base - pk.tile0;
             pk.bands = bands;
+            pk.miss_pitch = plan.bands;
+            pk.miss = at(plan.off_miss);
             if (stage == 0) {
                 auto count = plan.bands > 1
                                  ? (group ? bin_count_kernel<kBandLarge, 8, true> : bin_count_kernel<kBandLarge, 1, true>)
@@ -1431,7 +1433,8 @@ int launch_bin_sort(const BinSortPlan& plan, const isogs_projected* proj, const 
                 if (chunks)
                     hipLaunchKernelGGL(count, dim3(work_blocks(chunks, bands)), dim3(kBinThreads), 0, stream, pk, record,
                                        proj->tile_count, A);
-                hipLaunchKernelGGL(bin_columns_kernel, dim3(blocks), dim3(kBinThreads), 0, stream, pk, A);
+                auto columns = plan.bands > 1 ? bin_columns_kernel<true> : bin_columns_kernel<false>;
+                hipLaunchKernelGGL(columns, dim3(blocks), dim3(kBinThreads), 0, stream, pk, A);
             } else {
                 auto place = plan.bands > 1
                                  ? (group ? bin_place_kernel<kBandLarge, 8, true> : bin_place_kernel<kBandLarge, 1, true>)
