@@ -1266,7 +1266,7 @@ static uint32_t view_tiles(const isogs_camera& c) {
 // above four bands, whose shares of the particles differ more): the matrix then has at most 256
 // kBandLarge counts (512 above four bands), 38 MB (75 MB), and a row per view, however many tiles.
 // With 256 and 512 workgroups: 5120 x 2880 of 1M particles (two bands) 190 and 220 us, 12288 x 6912 of
-// 300k (nine) 451 and 423, 16384 x 16384 of 1M (28) 1.96 and 1.80 ms.
+// 300k (nine) 451 and 423, 16384 x 16384 of 1M (29) 1.96 and 1.80 ms.
 static uint32_t chunk_particles(uint64_t n_total, int32_t nv, bool large_band, uint32_t bands) {
     const uint32_t least = n_total <= kGroupMaxParticles ? 128u : 1024u;
     const uint32_t target = bands > 4                         ? std::max(kMaxChunks / bands, 1u)
